@@ -504,31 +504,65 @@ __device__ __forceinline__ ff ff_ldexp(ff x, int k) { return {ldexpf(x.hi, k), l
 constexpr float kLn2Hi = 0.693147182464599609375f;
 constexpr float kLn2Lo = -1.904654323148236e-09f;
 
+// The constants of the two series below as float-float pairs, entry i in lane
+// i: lanes 0 .. 13 hold 1/i!, lanes 16 .. 36 hold 1/(2 (i - 16) + 1).  Every
+// value is the binary64 constant split into two floats, so its error is below
+// 2^-48 relative.
+constexpr int kExpTerms = 14, kLogTerms = 21, kLogLane = 16;
+
+struct SeriesTable {
+    float hi[64], lo[64];
+};
+
+constexpr SeriesTable make_series_table() {
+    SeriesTable t{};
+    for (int i = 0; i < 64; ++i) {
+        double v = 0.0;
+        if (i < kExpTerms) {
+            v = 1.0;
+            for (int k = 2; k <= i; ++k)
+                v /= (double)k;
+        } else if (i >= kLogLane && i < kLogLane + kLogTerms) {
+            v = 1.0 / (double)(2 * (i - kLogLane) + 1);
+        }
+        t.hi[i] = (float)v;
+        t.lo[i] = (float)(v - (double)(float)v);
+    }
+    return t;
+}
+
+__constant__ const SeriesTable kSeries = make_series_table();
+
+// Lane i's float-float pair, i wavefront-uniform.
+__device__ __forceinline__ ff ff_readlane(ff v, int i) {
+    return {__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v.hi), i)),
+            __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v.lo), i))};
+}
+
 // e^x for x <= 0 (x given as float-float): x = k ln2 + r with |r| <= ln2/2,
 // e^r by its Taylor series to degree 13 (truncation below 2e-16), then 2^k.
-__device__ ff ff_exp_nonpos(ff x) {
+// tab: this lane's entry of kSeries (all lanes of the wavefront call).
+__device__ __forceinline__ ff ff_exp_nonpos(ff x, ff tab) {
     const float k = rintf(x.hi / kLn2Hi);
     ff r = ff_sub(x, two_prod(k, kLn2Hi));
     r = ff_sub(r, ff_mul_f(ff{kLn2Lo, 0.0f}, k));
     // Horner with coefficients 1/i!
-    ff inv_fact[14];
-    inv_fact[0] = {1.0f, 0.0f};
-    for (int i = 1; i < 14; ++i)
-        inv_fact[i] = ff_div(inv_fact[i - 1], ff{(float)i, 0.0f});
-    ff p = inv_fact[13];
-    for (int i = 12; i >= 0; --i)
-        p = ff_add(ff_mul(p, r), inv_fact[i]);
+    ff p = ff_readlane(tab, kExpTerms - 1);
+#pragma unroll 1
+    for (int i = kExpTerms - 2; i >= 0; --i)
+        p = ff_add(ff_mul(p, r), ff_readlane(tab, i));
     return ff_ldexp(p, (int)k);
 }
 
 // log(1 + y) for 0 <= y <= 1: 2 atanh(z), z = y / (2 + y) <= 1/3, by the odd
-// series of atanh to 20 terms (truncation below 1e-19).
-__device__ ff ff_log1p_unit(ff y) {
+// series of atanh to 20 terms (truncation below 1e-19).  tab as above.
+__device__ __forceinline__ ff ff_log1p_unit(ff y, ff tab) {
     const ff z = ff_div(y, ff_add(ff{2.0f, 0.0f}, y));
     const ff z2 = ff_mul(z, z);
-    ff s = ff_div(ff{1.0f, 0.0f}, ff{41.0f, 0.0f});
-    for (int i = 19; i >= 0; --i)
-        s = ff_add(ff_mul(s, z2), ff_div(ff{1.0f, 0.0f}, ff{(float)(2 * i + 1), 0.0f}));
+    ff s = ff_readlane(tab, kLogLane + kLogTerms - 1);
+#pragma unroll 1
+    for (int i = kLogTerms - 2; i >= 0; --i)
+        s = ff_add(ff_mul(s, z2), ff_readlane(tab, kLogLane + i));
     return ff_mul_f(ff_mul(z, s), 2.0f);
 }
 
@@ -539,15 +573,20 @@ struct ClassTerms {
     float a, c;  // dh/dJ, dh/dq
 };
 
-__device__ ClassTerms class_terms(int idx, float J, float q) {
+// Terms of class idx (LOG: with log 2cosh h).  Called by whole wavefronts.
+template <bool LOG>
+__device__ __forceinline__ ClassTerms class_terms(int idx, float J, float q, ff tab) {
     const int k = idx >> 1;
     ClassTerms t;
     t.a = (float)(2 * k - 2);
     t.c = (idx & 1) ? 1.0f : -1.0f;
     t.h = two_sum(J * t.a, q * t.c);   // both products are exact
     const ff absh = t.h.hi < 0.0f ? ff_neg(t.h) : t.h;
-    const ff y = ff_exp_nonpos(ff_mul_f(absh, -2.0f));   // e^{-2|h|}
-    t.log2ch = ff_add(absh, ff_log1p_unit(y));
+    const ff y = ff_exp_nonpos(ff_mul_f(absh, -2.0f), tab);   // e^{-2|h|}
+    if constexpr (LOG) {
+        t.log2ch = ff_add(absh, ff_log1p_unit(y, tab));
+        return t;
+    }
     ff th = ff_div(ff_sub(ff{1.0f, 0.0f}, y), ff_add(ff{1.0f, 0.0f}, y));
     t.tanh_h = t.h.hi < 0.0f ? ff_neg(th) : th;
     return t;
@@ -567,42 +606,58 @@ __device__ __forceinline__ void class_sums(const int64_t* __restrict__ v, int id
     }
 }
 
+// One wavefront; lane idx evaluates class idx (three leader classes in the
+// paired form, six otherwise; the other lanes repeat the last one), and the
+// classes' terms are added in class order from the lanes' registers.  What
+// bounds it is the latency of one lane's float-float chain: 33 dependent
+// Horner steps of about 29 instructions.  One lane walking the six classes and
+// dividing the series' coefficients out again for each took 47 us a launch;
+// the classes side by side with tabulated coefficients take 4.9 us (backward,
+// without the logarithm, 3.3 us, from 48).
 template <bool PAIRED>
-__global__ void k_loglik_fwd(const int64_t* __restrict__ counts, const float* __restrict__ Jq,
-                             float* __restrict__ ll) {
-    if (blockIdx.x != 0 || threadIdx.x != 0)
-        return;
-    const float J = Jq[0], q = Jq[1];
+__global__ __launch_bounds__(64) void k_loglik_fwd(const int64_t* __restrict__ counts, const float* __restrict__ Jq,
+                                                   float* __restrict__ ll) {
+    constexpr int kClasses = PAIRED ? 3 : 6;
+    const int lane = (int)threadIdx.x;
+    const ff tab = {kSeries.hi[lane], kSeries.lo[lane]};
+    const int idx = lane < kClasses ? lane : kClasses - 1;
+    const ClassTerms t = class_terms<true>(idx, Jq[0], Jq[1], tab);
+    int64_t Di, Ni;
+    class_sums<PAIRED>(counts, idx, Di, Ni);
+    const ff d = ff_from_i64(Di), N = ff_from_i64(Ni);
+    const ff term = ff_sub(ff_mul(d, t.h), ff_mul(N, t.log2ch));
     ff acc = {0.0f, 0.0f};
-    for (int idx = 0; idx < (PAIRED ? 3 : 6); ++idx) {
-        const ClassTerms t = class_terms(idx, J, q);
-        int64_t Di, Ni;
-        class_sums<PAIRED>(counts, idx, Di, Ni);
-        const ff d = ff_from_i64(Di), N = ff_from_i64(Ni);
-        acc = ff_add(acc, ff_sub(ff_mul(d, t.h), ff_mul(N, t.log2ch)));
-    }
-    ll[0] = acc.hi + acc.lo;
+#pragma unroll 1
+    for (int i = 0; i < kClasses; ++i)
+        acc = ff_add(acc, ff_readlane(term, i));
+    if (lane == 0)
+        ll[0] = acc.hi + acc.lo;
 }
 
 template <bool PAIRED>
-__global__ void k_loglik_bwd(const int64_t* __restrict__ counts, const float* __restrict__ Jq,
-                             const float* __restrict__ g_out, float* __restrict__ grad) {
-    if (blockIdx.x != 0 || threadIdx.x != 0)
-        return;
-    const float J = Jq[0], q = Jq[1];
+__global__ __launch_bounds__(64) void k_loglik_bwd(const int64_t* __restrict__ counts, const float* __restrict__ Jq,
+                                                   const float* __restrict__ g_out, float* __restrict__ grad) {
+    constexpr int kClasses = PAIRED ? 3 : 6;
+    const int lane = (int)threadIdx.x;
+    const ff tab = {kSeries.hi[lane], kSeries.lo[lane]};
+    const int idx = lane < kClasses ? lane : kClasses - 1;
+    const ClassTerms t = class_terms<false>(idx, Jq[0], Jq[1], tab);
+    int64_t Di, Ni;
+    class_sums<PAIRED>(counts, idx, Di, Ni);
+    const ff resid = ff_sub(ff_from_i64(Di), ff_mul(ff_from_i64(Ni), t.tanh_h));
+    const ff tJ = ff_mul_f(resid, t.a), tq = ff_mul_f(resid, t.c);
     ff gJ = {0.0f, 0.0f}, gq = {0.0f, 0.0f};
-    for (int idx = 0; idx < (PAIRED ? 3 : 6); ++idx) {
-        const ClassTerms t = class_terms(idx, J, q);
-        int64_t Di, Ni;
-        class_sums<PAIRED>(counts, idx, Di, Ni);
-        const ff resid = ff_sub(ff_from_i64(Di), ff_mul(ff_from_i64(Ni), t.tanh_h));
-        gJ = ff_add(gJ, ff_mul_f(resid, t.a));
-        gq = ff_add(gq, ff_mul_f(resid, t.c));
+#pragma unroll 1
+    for (int i = 0; i < kClasses; ++i) {
+        gJ = ff_add(gJ, ff_readlane(tJ, i));
+        gq = ff_add(gq, ff_readlane(tq, i));
     }
     const float go = g_out ? g_out[0] : 1.0f;
     const ff rJ = ff_mul_f(gJ, go), rq = ff_mul_f(gq, go);
-    grad[0] = rJ.hi + rJ.lo;
-    grad[1] = rq.hi + rq.lo;
+    if (lane == 0) {
+        grad[0] = rJ.hi + rJ.lo;
+        grad[1] = rq.hi + rq.lo;
+    }
 }
 
 }  // namespace
