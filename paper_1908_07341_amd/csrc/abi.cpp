@@ -127,6 +127,27 @@ DrawParams dynamics_params(double J, double q, uint64_t seed, uint32_t stream, u
     return dp;
 }
 
+sd_status init_params(const char* name, int32_t kind, double p_up, uint64_t seed, uint32_t stream, DrawParams* dp,
+                      bool* random, bool* up) {
+    if (kind != SD_INIT_UP && kind != SD_INIT_DOWN && kind != SD_INIT_RANDOM)
+        return fail(SD_EINVAL, "%s: unknown kind %d", name, kind);
+    if (kind == SD_INIT_RANDOM && !(p_up >= 0.0 && p_up <= 1.0))
+        return fail(SD_EINVAL, "%s: p_up must lie in [0, 1]", name);
+    *dp = DrawParams{};
+    const double P = kind == SD_INIT_RANDOM ? std::nearbyint(p_up * 4294967296.0) : 0.0;
+    *up = kind == SD_INIT_UP || P >= 4294967296.0;
+    *random = kind == SD_INIT_RANDOM && !*up;
+    if (*random) {
+        for (int i = 0; i < 6; ++i)
+            dp->T[i] = (uint32_t)P;
+        dp->key0 = (uint32_t)(seed & 0xFFFFFFFFu);
+        dp->key1 = (uint32_t)(seed >> 32);
+        dp->stream = stream;
+        dp->tag2 = 2u * kTagInit;
+    }
+    return SD_OK;
+}
+
 bool overlap(const void* a, const void* b, size_t n) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
     return x < y + n && y < x + n;
@@ -359,33 +380,14 @@ sd_status sd_init(void* lattice, int32_t L, int32_t layout, int32_t kind, double
     sd_status s = check_lattice(lattice, L, layout, "sd_init");
     if (s != SD_OK)
         return s;
-    if (kind != SD_INIT_UP && kind != SD_INIT_DOWN && kind != SD_INIT_RANDOM)
-        return fail(SD_EINVAL, "sd_init: unknown kind %d", kind);
-    if (kind == SD_INIT_RANDOM && !(p_up >= 0.0 && p_up <= 1.0))
-        return fail(SD_EINVAL, "sd_init: p_up must lie in [0, 1]");
+    DrawParams dp;
+    bool random = false, up = false;
+    s = init_params("sd_init", kind, p_up, seed, stream, &dp, &random, &up);
+    if (s != SD_OK)
+        return s;
     const int klay = kernel_layout(L, layout, lattice);
-    const Geom G = make_geom(L, klay);
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    hipError_t e;
-    if (kind == SD_INIT_RANDOM) {
-        const double Pd = std::nearbyint(p_up * 4294967296.0);
-        if (Pd >= 4294967296.0) {
-            e = launch_init(klay, lattice, G, 1, false, DrawParams{}, st);
-        } else {
-            DrawParams dp;
-            for (int i = 0; i < 6; ++i)
-                dp.T[i] = (uint32_t)Pd;
-            dp.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
-            dp.key1 = (uint32_t)(seed >> 32);
-            dp.stream = stream;
-            dp.t = 0;
-            dp.tag2 = 2u * kTagInit;
-            dp.rng_xor = 0;
-            e = launch_init(klay, lattice, G, 0, true, dp, st);
-        }
-    } else {
-        e = launch_init(klay, lattice, G, kind == SD_INIT_UP ? 1 : 0, false, DrawParams{}, st);
-    }
+    const hipError_t e = launch_init(klay, lattice, make_geom(L, klay), up ? 1 : 0, random, dp,
+                                     static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? SD_OK : hip_fail(e, "sd_init");
 }
 

@@ -497,14 +497,22 @@ sd_status sd_batch_launch_shape(const sd_batch_plan* plan, int32_t bucket, int32
 sd_status sd_batch_init(sd_batch_plan* plan, void* lattices, int32_t kind, double p_up, void* hip_stream) {
     if (!plan || !lattices)
         return fail(SD_EINVAL, "sd_batch_init: null plan or lattices");
-    for (int32_t c = 0; c < plan->n_chains; ++c) {
-        const ChainDesc& d = plan->descs[(size_t)c];
-        sd_status s = sd_init(static_cast<uint8_t*>(lattices) + d.sig_offset, (int32_t)d.L, plan->layout, kind, p_up,
-                              plan->seed, d.stream, hip_stream);
-        if (s != SD_OK)
-            return s;
-    }
-    return SD_OK;
+    // every chain's lattice lies at a multiple of 256 bytes from the buffer's start
+    sd_status s = check_lattice(lattices, (int32_t)plan->descs[0].L, plan->layout, "sd_batch_init");
+    if (s != SD_OK)
+        return s;
+    DrawParams dp;
+    bool random = false, up = false;
+    s = init_params("sd_batch_init", kind, p_up, plan->seed, 0u, &dp, &random, &up);
+    if (s != SD_OK)
+        return s;
+    const int klay = plan->layout == SD_P64                                   ? kLayP64
+                     : (reinterpret_cast<uintptr_t>(lattices) & 15u) == 0u ? kLayI8Row
+                                                                              : kLayI8Any;
+    const hipError_t e = launch_init_batch(klay, static_cast<uint8_t*>(lattices), plan->d_descs,
+                                           (uint32_t)plan->n_chains, plan->buckets[0].max_words, random, up, dp,
+                                           static_cast<hipStream_t>(hip_stream));
+    return e == hipSuccess ? SD_OK : hip_fail(e, "sd_batch_init");
 }
 
 sd_status sd_batch_run(sd_batch_plan* plan, void* lattices, int64_t* traces, uint64_t step0, void* hip_stream) {

@@ -10,13 +10,12 @@
 // with the rest of the workgroup.  Half-step B can also fold the observables
 // M, A, B of the new pair (sigma', tau) into the same pass, since it already
 // holds tau_x, tau_up and tau_right of every site it writes.
+#include "sd_batch.hpp"
 #include "sd_kernels.hpp"
 
 namespace sd {
 
 namespace {
-
-constexpr int kTailCap = 1024;
 
 // The 64-bit-word layout when every row is a whole number of 64-word chunks
 // (L % 4096 == 0): the 64 words a wavefront handles at once then lie in one
@@ -562,30 +561,87 @@ __global__ __launch_bounds__(256) void k_half_step_many(ManyChains mc, Geom G, D
         partials + 4u * (size_t)chain * mc.blocks_per_chain, block, mc.blocks_per_chain, sh, red);
 }
 
-// Random initial lattice: site s is +1 iff r_s(t = 0, tag 1) < P, the same
-// threshold for every site (all six table entries equal P).
+// Sites of 64-site group g that lie in a lattice of n_sites sites.
+__device__ __forceinline__ uint64_t valid_sites(uint32_t g, uint32_t n_sites) {
+    const uint32_t nv = n_sites - 64u * g < 64u ? n_sites - 64u * g : 64u;
+    return nv == 64u ? ~0ull : ((1ull << nv) - 1ull);
+}
+
+// The 64 sites of group g of a random lattice: site s is +1 iff
+// r_s(t = 0, tag 1) < dp.T[0], one threshold for every site, so the scan of
+// the eight planes needs no per-site choice: two three-input ops per plane and
+// half word against the threshold bit's mask S[m].  Sites whose top byte
+// equals the threshold's draw their tail in their own lane; a threshold that
+// is a multiple of 2^24 (p = 1/2 among others) leaves nothing to draw, since
+// no tail is below 0.
+__device__ __forceinline__ uint64_t random_group(const DrawParams& dp, uint32_t g, uint64_t valid,
+                                                 const uint32_t (&S)[8]) {
+    uint64_t P[8];
+    draw_planes(dp, g, P);
+    uint32_t und[2] = {~0u, ~0u}, v[2] = {0u, 0u};
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t r = (uint32_t)(P[m] >> (32 * h));
+            v[h] = __builtin_amdgcn_bitop3_b32(und[h], r, v[h], kScanV);
+            und[h] = __builtin_amdgcn_bitop3_b32(r, S[m], und[h], kScanUnd);
+        }
+    uint64_t u = (uint64_t)und[0] | ((uint64_t)und[1] << 32);
+    uint64_t lt = ((uint64_t)v[0] | ((uint64_t)v[1] << 32)) & ~u;
+    u &= valid;
+    const uint32_t T24 = dp.T[0] & 0xFFFFFFu;
+    if (T24 != 0)
+        while (u) {
+            const int b = __ffsll((unsigned long long)u) - 1;
+            u &= u - 1;
+            if (draw_tail24(dp, 64u * g + (uint32_t)b) < T24)
+                lt |= 1ull << b;
+        }
+    return lt & valid;
+}
+
+__device__ __forceinline__ void threshold_masks(uint32_t T, uint32_t (&S)[8]) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        S[m] = 0u - ((T >> (31 - m)) & 1u);
+}
+
+// Random initial lattice, one lane per 64-site group, no barriers (27 us at
+// 16384^2; 53 us with the six-class scan and a workgroup list of tails).
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void k_init_random(void* __restrict__ dst, Geom G, DrawParams dp) {
-    __shared__ TailScratch<kTailCap> tails;
-    const PlaneMasks pm = make_plane_masks<false>(dp);
+    uint32_t S[8];
+    threshold_masks(dp.T[0], S);
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t base = blockIdx.x * blockDim.x; base < G.n_groups; base += stride) {
-        const uint32_t g = base + threadIdx.x;
-        const bool active = g < G.n_groups;
-        uint64_t valid = 0;
-        if (active) {
-            const uint32_t s0 = 64u * g;
-            const uint32_t nv = G.n_sites - s0 < 64u ? G.n_sites - s0 : 64u;
-            valid = nv == 64u ? ~0ull : ((1ull << nv) - 1ull);
-        }
-        uint64_t P[8];
-        draw_planes(dp, active ? g : 0u, P);
-        WordDraw wd = compare_planes<false, false>(P, 0, 0, 0, pm);
-        uint64_t lt = wd.lt;
-        resolve_tails<kTailCap>(lt, wd.und & valid, 0, 0, 0, 64u * g, dp, tails);
-        if (active)
-            scatter<LAYOUT>(dst, G, g, lt & valid, valid);
+    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < G.n_groups; g += stride) {
+        const uint64_t valid = valid_sites(g, G.n_sites);
+        scatter<LAYOUT>(dst, G, g, random_group(dp, g, valid, S), valid);
     }
+}
+
+// Initial lattices of all the chains of a batch in one launch: workgroups
+// chain * blocks_per_chain ... take chain `chain`'s sigma (L % 8 == 0, so that
+// every group is whole), each chain with its own stream.  kind 0 = all -1,
+// 1 = all +1, 2 = random with threshold base.T[0].  One launch per chain left
+// the device to its launch rate, 4.5 us a chain: 20 ms for 4096 random chains
+// of 128^2 to 512^2 and 3 ms for 1600 constant ones of 200^2; this kernel is
+// bound by the plane draws and takes 46 us and 6 us.
+template <int LAYOUT, bool RANDOM>
+__global__ __launch_bounds__(256) void k_init_batch(uint8_t* __restrict__ lattices, const ChainDesc* __restrict__ chains,
+                                                    uint32_t blocks_per_chain, uint32_t up, DrawParams base) {
+    const uint32_t chain = blockIdx.x / blocks_per_chain;
+    const uint32_t block = blockIdx.x - chain * blocks_per_chain;
+    const ChainDesc& cd = chains[chain];
+    const uint32_t n_words = (uint32_t)(((uint64_t)cd.L * cd.L) / 64u);
+    void* dst = lattices + cd.sig_offset;
+    Geom G;   // scatter needs none of it on these layouts
+    DrawParams dp = base;
+    dp.stream = cd.stream;
+    uint32_t S[8];
+    threshold_masks(base.T[0], S);
+    for (uint32_t g = block * blockDim.x + threadIdx.x; g < n_words; g += blocks_per_chain * blockDim.x)
+        scatter<LAYOUT>(dst, G, g, RANDOM ? random_group(dp, g, ~0ull, S) : (up ? ~0ull : 0ull), ~0ull);
 }
 
 template <int LAYOUT>
@@ -815,6 +871,46 @@ hipError_t launch_init(int layout, void* dst, const Geom& G, int kind_const_up, 
     }
 #undef SD_INIT
     return hipGetLastError();
+}
+
+template <int LAYOUT>
+void launch_init_batch_layout(uint8_t* lattices, const ChainDesc* chains, uint32_t n, uint32_t bpc, bool random,
+                              uint32_t up, const DrawParams& base, hipStream_t st) {
+    if (random)
+        hipLaunchKernelGGL((k_init_batch<LAYOUT, true>), dim3(n * bpc), dim3(256), 0, st, lattices, chains, bpc, up,
+                           base);
+    else
+        hipLaunchKernelGGL((k_init_batch<LAYOUT, false>), dim3(n * bpc), dim3(256), 0, st, lattices, chains, bpc, up,
+                           base);
+}
+
+hipError_t launch_init_batch(int layout, uint8_t* lattices, const ChainDesc* chains, uint32_t n_chains,
+                             uint32_t max_words, bool random, bool up, const DrawParams& base, hipStream_t st) {
+    // four words per thread of the largest lattice; a launch of at most 2^20
+    // chains keeps the grid within 2^31 workgroups (a chain has at most 2^14
+    // words, as both its lattices fit in LDS)
+    const uint32_t bpc = (max_words + 1023u) / 1024u;
+    constexpr uint32_t kPerLaunch = 1u << 20;
+    for (uint32_t c0 = 0; c0 < n_chains; c0 += kPerLaunch) {
+        const uint32_t n = n_chains - c0 < kPerLaunch ? n_chains - c0 : kPerLaunch;
+        switch (layout) {
+            case kLayP64:
+                launch_init_batch_layout<kLayP64>(lattices, chains + c0, n, bpc, random, up, base, st);
+                break;
+            case kLayI8Row:
+                launch_init_batch_layout<kLayI8Row>(lattices, chains + c0, n, bpc, random, up, base, st);
+                break;
+            case kLayI8Any:
+                launch_init_batch_layout<kLayI8Any>(lattices, chains + c0, n, bpc, random, up, base, st);
+                break;
+            default:
+                return hipErrorInvalidValue;
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_fill_i64(int64_t* p, size_t n, int64_t v, hipStream_t st) {

@@ -73,6 +73,12 @@ void set_divisors(ChainDesc& d, uint32_t L);
 
 size_t batch_lds_bytes(uint32_t max_words, uint32_t threads);
 hipError_t launch_batch_chains(const BatchArgs& a, uint32_t blocks, uint32_t threads, hipStream_t st);
+// Every chain's sigma in one launch, as launch_init would write it with the
+// chain's own stream: random with threshold base.T[0], else all +1 (up) or all
+// -1.  layout: kLayP64 for packed lattices, kLayI8Row for int8 ones on 16-byte
+// aligned lattices, kLayI8Any for other int8 ones.
+hipError_t launch_init_batch(int layout, uint8_t* lattices, const ChainDesc* chains, uint32_t n_chains,
+                             uint32_t max_words, bool random, bool up, const DrawParams& base, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, uint32_t n, hipStream_t st);
 // starts[0 .. n) = all ones and ends[0 .. n) = 0, before the launches that time themselves.
 hipError_t launch_times_reset(unsigned long long* starts, unsigned long long* ends, uint32_t n, hipStream_t st);

@@ -141,16 +141,6 @@ __device__ __forceinline__ uint32_t draw_tail24(const DrawParams& dp, uint32_t s
     return (w ^ dp.rng_xor) >> 8;
 }
 
-__device__ __forceinline__ uint32_t threshold_of(const DrawParams& dp, uint32_t idx) {
-    uint32_t v = dp.T[0];
-    v = idx == 1 ? dp.T[1] : v;
-    v = idx == 2 ? dp.T[2] : v;
-    v = idx == 3 ? dp.T[3] : v;
-    v = idx == 4 ? dp.T[4] : v;
-    v = idx == 5 ? dp.T[5] : v;
-    return v;
-}
-
 // Copy of a wavefront-uniform value held in a vector register.  Loop-invariant
 // uniforms of the inner loops (threshold bit masks) are kept this way so that
 // they do not crowd the scalar register file.
@@ -342,83 +332,6 @@ __device__ __forceinline__ WordDraw compare_planes(const uint64_t P[8], uint64_t
 __device__ __forceinline__ uint32_t class_at(uint64_t c, uint64_t n1, uint64_t n2, int b) {
     uint32_t k = (uint32_t)((n1 >> b) & 1u) + (uint32_t)((n2 >> b) & 1u);
     return 2u * k + (uint32_t)((c >> b) & 1u);
-}
-
-// Decision of one undecided site with threshold thr: its top byte equals the
-// threshold's, so r < thr iff the low 24 bits compare below.
-__device__ __forceinline__ bool decide_tail_thr(const DrawParams& dp, uint32_t s, uint32_t thr) {
-    return draw_tail24(dp, s) < (thr & 0xFFFFFFu);
-}
-
-__device__ __forceinline__ bool decide_tail(const DrawParams& dp, uint32_t s, uint32_t idx) {
-    return decide_tail_thr(dp, s, threshold_of(dp, idx));
-}
-
-// Workgroup-shared scratch for resolving undecided sites cooperatively.
-template <int CAP>
-struct TailScratch {
-    uint32_t count;
-    uint32_t site[CAP];
-    uint8_t info[CAP];   // class idx on entry, decision (0/1) on exit
-};
-
-// Resolve the undecided sites of every lane of the workgroup.  Must be called
-// by all threads of the block (it contains barriers).  `und` marks undecided
-// bits of the word whose bit 0 is site `site0`; the decided +1 bits are or-ed
-// into `lt`.  Entries are handed out with one LDS atomic per lane that has
-// undecided bits, resolved one per thread, and read back by their owners in
-// the order they were written.  If more than CAP sites are undecided (never
-// observed: the mean is 0.25 per word) each lane resolves its own bits.
-template <int CAP>
-__device__ __forceinline__ void resolve_tails(uint64_t& lt, uint64_t und, uint64_t c, uint64_t n1, uint64_t n2,
-                                              uint32_t site0, const DrawParams& dp, TailScratch<CAP>& sh) {
-    const uint32_t tid = threadIdx.x;
-    if (tid == 0)
-        sh.count = 0;
-    __syncthreads();
-    const uint32_t cnt = (uint32_t)__popcll(und);
-    uint32_t base = 0;
-    if (cnt)
-        base = atomicAdd(&sh.count, cnt);
-    __syncthreads();
-    const uint32_t total = sh.count;
-    if (total <= (uint32_t)CAP) {
-        if (cnt) {
-            uint64_t u = und;
-            uint32_t e = base;
-            while (u) {
-                int b = __ffsll((unsigned long long)u) - 1;
-                u &= u - 1;
-                sh.site[e] = site0 + (uint32_t)b;
-                sh.info[e] = (uint8_t)class_at(c, n1, n2, b);
-                ++e;
-            }
-        }
-        __syncthreads();
-        for (uint32_t e = tid; e < total; e += blockDim.x)
-            sh.info[e] = decide_tail(dp, sh.site[e], sh.info[e]) ? 1 : 0;
-        __syncthreads();
-        if (cnt) {
-            uint64_t u = und;
-            uint32_t e = base;
-            while (u) {
-                int b = __ffsll((unsigned long long)u) - 1;
-                u &= u - 1;
-                if (sh.info[e])
-                    lt |= 1ull << b;
-                ++e;
-            }
-        }
-    } else if (cnt) {
-        uint64_t u = und;
-        while (u) {
-            int b = __ffsll((unsigned long long)u) - 1;
-            u &= u - 1;
-            if (decide_tail(dp, site0 + (uint32_t)b, class_at(c, n1, n2, b)))
-                lt |= 1ull << b;
-        }
-    }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------

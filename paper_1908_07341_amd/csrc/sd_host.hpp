@@ -19,6 +19,14 @@ int kernel_layout(int32_t L, int32_t layout, const void* p);
 int packed_rows_layout(int32_t L);
 uint32_t threshold(double h);
 void threshold_table(double J, double q, uint32_t T[6]);
+// The initial lattice of sd_init: validates kind and p_up and sets whether the
+// lattice is random (with the draw parameters dp) or constant, all +1 (up) or
+// all -1.
+sd_status init_params(const char* name, int32_t kind, double p_up, uint64_t seed, uint32_t stream, DrawParams* dp,
+                      bool* random, bool* up);
+// The lattice pointer's checks of the entry points (size and layout, null,
+// alignment to the word size).
+sd_status check_lattice(const void* p, int32_t L, int32_t layout, const char* name);
 DrawParams dynamics_params(double J, double q, uint64_t seed, uint32_t stream, uint32_t t, uint32_t flags);
 
 // Device scratch of kPartialsWords int64 for per-workgroup partial sums, one
