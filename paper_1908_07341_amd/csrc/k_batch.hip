@@ -213,17 +213,6 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
     __syncthreads();
 }
 
-__device__ __forceinline__ uint32_t lds_bytes_to_bits4(uint32_t x) {
-    uint32_t y = (~x >> 7) & 0x01010101u;
-    return (y * 0x10204080u) >> 28;
-}
-
-__device__ __forceinline__ uint32_t lds_bits4_to_bytes(uint32_t n) {
-    uint32_t z = (n * 0x00204081u) & 0x01010101u;
-    uint32_t w = z ^ 0x01010101u;
-    return z | ((w << 8) - w);
-}
-
 // Observables of the pair (sig, tau) as sums over the workgroup's threads
 // (a separate pass, used for chains with the general compare).
 template <bool BITS>
@@ -401,18 +390,8 @@ __device__ __forceinline__ void batch_chains_body(const BatchArgs& a) {
         // load sigma (packed words, or int8 bytes converted to bits)
         if (a.int8_io) {
             const int8_t* src8 = reinterpret_cast<const int8_t*>(a.counter ? a.lattices + cd.sig_offset : a.single_sig);
-            for (uint32_t g = threadIdx.x; g < n_words; g += blockDim.x) {
-                const uint4* v = reinterpret_cast<const uint4*>(src8 + (size_t)64u * g);
-                uint64_t bits = 0;
-#pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {
-                    uint4 x = v[qd];
-                    uint32_t b16 = lds_bytes_to_bits4(x.x) | (lds_bytes_to_bits4(x.y) << 4) |
-                                   (lds_bytes_to_bits4(x.z) << 8) | (lds_bytes_to_bits4(x.w) << 12);
-                    bits |= (uint64_t)b16 << (16 * qd);
-                }
-                sig[g] = bits;
-            }
+            for (uint32_t g = threadIdx.x; g < n_words; g += blockDim.x)
+                sig[g] = load_bits64_i8(src8 + (size_t)64u * g);
         } else {
             const uint64_t* src =
                 a.counter ? reinterpret_cast<const uint64_t*>(a.lattices + cd.sig_offset)
@@ -460,18 +439,7 @@ __device__ __forceinline__ void batch_chains_body(const BatchArgs& a) {
             for (uint32_t g = threadIdx.x; g < (a.k_steps ? 2u : 1u) * n_words; g += blockDim.x) {
                 const bool is_tau = g >= n_words;
                 const uint32_t gg = is_tau ? g - n_words : g;
-                const uint64_t bits = is_tau ? tau[gg] : sig[gg];
-                uint4* v = reinterpret_cast<uint4*>((is_tau ? dst8t : dst8) + (size_t)64u * gg);
-#pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {
-                    uint32_t b16 = (uint32_t)(bits >> (16 * qd)) & 0xFFFFu;
-                    uint4 x;
-                    x.x = lds_bits4_to_bytes(b16 & 0xF);
-                    x.y = lds_bits4_to_bytes((b16 >> 4) & 0xF);
-                    x.z = lds_bits4_to_bytes((b16 >> 8) & 0xF);
-                    x.w = lds_bits4_to_bytes((b16 >> 12) & 0xF);
-                    v[qd] = x;
-                }
+                store_bits64_i8((is_tau ? dst8t : dst8) + (size_t)64u * gg, is_tau ? tau[gg] : sig[gg]);
             }
         } else {
             uint64_t* dsig = reinterpret_cast<uint64_t*>(a.counter ? a.lattices + cd.sig_offset : a.single_sig);

@@ -10,6 +10,8 @@
 // with the rest of the workgroup.  Half-step B can also fold the observables
 // M, A, B of the new pair (sigma', tau) into the same pass, since it already
 // holds tau_x, tau_up and tau_right of every site it writes.
+#include <cstring>
+
 #include "sd_batch.hpp"
 #include "sd_kernels.hpp"
 
@@ -93,27 +95,50 @@ __device__ __forceinline__ void gather(const void* src, const Geom& G, uint32_t 
         }
     } else if constexpr (LAYOUT == kLayBits) {
         gather_bits<WHICH>(static_cast<const uint64_t*>(src), G.L, G.n_groups, G.div_L, g, c, n1, n2);
-    } else {  // kLayI8Any: per-site gather, any L >= 2
+    } else {  // kLayI8Any: any L >= 2, any address
         const int8_t* s = static_cast<const int8_t*>(src);
-        const uint32_t s0 = 64u * g;
-        const uint32_t nv = G.n_sites - s0 < 64u ? G.n_sites - s0 : 64u;
-        uint32_t j = fdiv(s0, G.div_L);
-        uint32_t i = s0 - j * G.L;
+        const uint32_t s0 = 64u * g, L = G.L, N = G.n_sites;
+        const uint32_t nv = N - s0 < 64u ? N - s0 : 64u;
+        valid = nv == 64u ? ~0ull : ((1ull << nv) - 1ull);
+        const uint32_t j0 = fdiv(s0, G.div_L);
+        uint32_t i = s0 - j0 * L;
+        if (N >= 64u) {
+            // windows of the byte string: the word itself, the row below
+            // (above), and the word shifted by one site, whose row-wrap
+            // columns (one site of 64 when L >= 64) are patched one by one.
+            // Four 16-byte loads per window instead of a byte per site: one
+            // lane walking 64 sites with four dependent bytes each took
+            // 54 us a half-step on 333^2.
+            c = window_i8(s, N, s0);
+            if constexpr (WHICH == 0) {
+                n1 = window_i8(s, N, s0 >= L ? s0 - L : s0 + N - L);
+                n2 = (c << 1) | (s[s0 == 0 ? 0 : s0 - 1] > 0 ? 1ull : 0ull);
+                for (uint32_t b = i == 0 ? 0u : L - i; b < nv; b += L)           // column 0: its row's last site
+                    n2 = (n2 & ~(1ull << b)) | (s[s0 + b + L - 1u] > 0 ? 1ull << b : 0ull);
+            } else {
+                n1 = window_i8(s, N, s0 + L >= N ? s0 + L - N : s0 + L);
+                n2 = (c >> 1) | (s[s0 + 64u < N ? s0 + 64u : N - 1u] > 0 ? 1ull << 63 : 0ull);
+                for (uint32_t b = L - 1u - i; b < nv; b += L)                    // column L - 1: its row's first site
+                    n2 = (n2 & ~(1ull << b)) | (s[s0 + b + 1u - L] > 0 ? 1ull << b : 0ull);
+            }
+            return;
+        }
+        // lattices of a single word (L < 8), site by site
+        uint32_t j = j0;
         c = 0; n1 = 0; n2 = 0;
         for (uint32_t b = 0; b < nv; ++b) {
-            const size_t row = (size_t)j * G.L;
+            const size_t row = (size_t)j * L;
             const uint64_t bit = 1ull << b;
             if (s[row + i] > 0) c |= bit;
             if constexpr (WHICH == 0) {
-                if (s[(size_t)(j == 0 ? G.L - 1 : j - 1) * G.L + i] > 0) n1 |= bit;
-                if (s[row + (i == 0 ? G.L - 1 : i - 1)] > 0) n2 |= bit;
+                if (s[(size_t)(j == 0 ? L - 1 : j - 1) * L + i] > 0) n1 |= bit;
+                if (s[row + (i == 0 ? L - 1 : i - 1)] > 0) n2 |= bit;
             } else {
-                if (s[(size_t)(j == G.L - 1 ? 0 : j + 1) * G.L + i] > 0) n1 |= bit;
-                if (s[row + (i == G.L - 1 ? 0 : i + 1)] > 0) n2 |= bit;
+                if (s[(size_t)(j == L - 1 ? 0 : j + 1) * L + i] > 0) n1 |= bit;
+                if (s[row + (i == L - 1 ? 0 : i + 1)] > 0) n2 |= bit;
             }
-            if (++i == G.L) { i = 0; ++j; }
+            if (++i == L) { i = 0; ++j; }
         }
-        valid = nv == 64u ? ~0ull : ((1ull << nv) - 1ull);
     }
 }
 
@@ -129,49 +154,37 @@ __device__ __forceinline__ void scatter(void* dst, const Geom& /*G*/, uint32_t g
         store_bits64_i8(static_cast<int8_t*>(dst) + (size_t)64u * g, bits);
     } else {
         int8_t* d = static_cast<int8_t*>(dst) + (size_t)64u * g;
+        if (valid == ~0ull) {
+            store_bits64_i8<false>(d, bits);
+            return;
+        }
         for (int b = 0; b < 64; ++b)
             if ((valid >> b) & 1ull)
                 d[b] = ((bits >> b) & 1ull) ? 1 : -1;
     }
 }
 
-// Partner and neighbour bits of the 64-bit-word layouts (P64, I8Row) for the
-// word at row j, column word w of the row.
-template <int LAYOUT, int WHICH>
+// Partner and neighbour bits of the P64 layout for the word at row j, column
+// word w of the row.
+template <int WHICH>
 __device__ __forceinline__ void gather_row(const void* src, const Geom& G, uint32_t j, uint32_t w, uint64_t& c,
                                            uint64_t& n1, uint64_t& n2) {
     const uint32_t W = G.words_row;
-    if constexpr (LAYOUT == kLayP64) {
-        const uint64_t* s = static_cast<const uint64_t*>(src);
-        const uint32_t row = j * W;
-        c = s[row + w];
-        const uint32_t c_lo = (uint32_t)c, c_hi = (uint32_t)(c >> 32);
-        if constexpr (WHICH == 0) {
-            n1 = s[(j == 0 ? G.L - 1 : j - 1) * W + w];                                  // down
-            const uint32_t prev_hi =
-                reinterpret_cast<const uint32_t*>(s + row + (w == 0 ? W - 1 : w - 1))[1];
-            n2 = (uint64_t)__builtin_amdgcn_alignbit(c_lo, prev_hi, 31) |                 // left
-                 ((uint64_t)__builtin_amdgcn_alignbit(c_hi, c_lo, 31) << 32);
-        } else {
-            n1 = s[(j == G.L - 1 ? 0 : j + 1) * W + w];                                  // up
-            const uint32_t next_lo = reinterpret_cast<const uint32_t*>(s + row + (w == W - 1 ? 0 : w + 1))[0];
-            n2 = (uint64_t)__builtin_amdgcn_alignbit(c_hi, c_lo, 1) |                     // right
-                 ((uint64_t)__builtin_amdgcn_alignbit(next_lo, c_hi, 1) << 32);
-        }
+    const uint64_t* s = static_cast<const uint64_t*>(src);
+    const uint32_t row = j * W;
+    c = s[row + w];
+    const uint32_t c_lo = (uint32_t)c, c_hi = (uint32_t)(c >> 32);
+    if constexpr (WHICH == 0) {
+        n1 = s[(j == 0 ? G.L - 1 : j - 1) * W + w];                                  // down
+        const uint32_t prev_hi =
+            reinterpret_cast<const uint32_t*>(s + row + (w == 0 ? W - 1 : w - 1))[1];
+        n2 = (uint64_t)__builtin_amdgcn_alignbit(c_lo, prev_hi, 31) |                 // left
+             ((uint64_t)__builtin_amdgcn_alignbit(c_hi, c_lo, 31) << 32);
     } else {
-        static_assert(LAYOUT == kLayI8Row, "row walk needs 64-site words");
-        const int8_t* s = static_cast<const int8_t*>(src);
-        const size_t row = (size_t)j * G.L;
-        c = load_bits64_i8(s + row + 64u * w);
-        if constexpr (WHICH == 0) {
-            n1 = load_bits64_i8(s + (size_t)(j == 0 ? G.L - 1 : j - 1) * G.L + 64u * w);
-            const int8_t edge = s[row + (w == 0 ? G.L - 1 : 64u * w - 1)];
-            n2 = (c << 1) | (edge > 0 ? 1ull : 0ull);
-        } else {
-            n1 = load_bits64_i8(s + (size_t)(j == G.L - 1 ? 0 : j + 1) * G.L + 64u * w);
-            const int8_t edge = s[row + (w == W - 1 ? 0 : 64u * w + 64u)];
-            n2 = (c >> 1) | (edge > 0 ? (1ull << 63) : 0ull);
-        }
+        n1 = s[(j == G.L - 1 ? 0 : j + 1) * W + w];                                  // up
+        const uint32_t next_lo = reinterpret_cast<const uint32_t*>(s + row + (w == W - 1 ? 0 : w + 1))[0];
+        n2 = (uint64_t)__builtin_amdgcn_alignbit(c_hi, c_lo, 1) |                     // right
+             ((uint64_t)__builtin_amdgcn_alignbit(next_lo, c_hi, 1) << 32);
     }
 }
 
@@ -200,14 +213,10 @@ __device__ __forceinline__ void store_at(uint64_t* base, uint32_t byte_off, uint
 // obs (half-step B only, may be null) receives the observable contributions
 // of the written pair through 64-bit atomics; it must hold zeros (or earlier
 // partial sums of the same record) before the launch.
-// Words per lane and tile: 4 for the paired compare on bit-packed layouts,
-// 2 where the general compare or the int8 loads need more registers.
-constexpr int words_per_lane(int layout, bool paired) {
-    return (paired && (layout == kLayP64 || layout == kLayP64Rows || layout == kLayP32 || layout == kLayBits)) ? 4
-                                                                                                             : 2;
-}
-constexpr int kMaxWordsPerLane = 4;
-constexpr uint32_t kMaxWaveTile = 64u * kMaxWordsPerLane;
+// These wide tiles serve the layouts of packed words (P64, P32) with the paired
+// compare on large lattices; everything else takes one-word tiles (see below).
+constexpr int kWordsPerLane = 4;
+constexpr uint32_t kMaxWaveTile = 64u * kWordsPerLane;
 constexpr int kWavesPerBlock = 4;
 
 struct WaveList {
@@ -233,7 +242,7 @@ struct HalfStepScratch {
 
 // Layouts whose words are the lattice's 64-bit words: a decided +1 site can be
 // or-ed into a stored word later.
-constexpr bool pooled_layout(int layout) { return layout == kLayP64 || layout == kLayP64Rows || layout == kLayBits; }
+constexpr bool pooled_layout(int layout) { return layout == kLayP64 || layout == kLayP64Rows; }
 
 struct ObsAcc {
     int64_t pc = 0, d_up = 0, d_right = 0, d_self = 0, nsites = 0;
@@ -260,15 +269,14 @@ __device__ __forceinline__ void wave_sync_lds() {
 
 // One tile of 64 * WPL words.  FULL: every word of the tile holds 64 sites
 // of the lattice (no bounds checks).
-template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS, bool FULL, int WPL>
+template <int LAYOUT, int WHICH, bool COMPLEMENT, bool OBS, bool FULL, int WPL>
 __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, void* __restrict__ dst, const Geom& G,
                                                const DrawParams& dp, const PlaneMasks& pm, const uint32_t* T24,
                                                WaveList& wl, uint32_t tile0, uint32_t lane, ObsAcc& acc,
                                                TailPool& pool) {
-    constexpr int kWordsPerLane = WPL;
-    constexpr bool kRowWalk = LAYOUT == kLayP64 || LAYOUT == kLayI8Row;
-    uint64_t lt[kWordsPerLane], c[kWordsPerLane], n1[kWordsPerLane], n2[kWordsPerLane], valid[kWordsPerLane];
-    uint32_t slot[kWordsPerLane];
+    constexpr bool kRowWalk = LAYOUT == kLayP64;
+    uint64_t lt[WPL], c[WPL], n1[WPL], n2[WPL], valid[WPL];
+    uint32_t slot[WPL];
     // all loads of the tile first, so that their latency overlaps the Philox
     // work of the first words
     if constexpr (LAYOUT == kLayP64Rows) {
@@ -278,7 +286,7 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
         const uint64_t* s = static_cast<const uint64_t*>(src);
         const uint32_t W = G.words_row;
 #pragma unroll
-        for (int k = 0; k < kWordsPerLane; ++k) {
+        for (int k = 0; k < WPL; ++k) {
             const uint32_t g0 = tile0 + 64u * k;
             const uint32_t j = fdiv(g0, G.div_row);
             const uint32_t w0 = g0 - j * W;
@@ -314,10 +322,10 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
         uint32_t j = fdiv(g0, G.div_row);
         uint32_t w = g0 - j * G.words_row;
 #pragma unroll
-        for (int k = 0; k < kWordsPerLane; ++k) {
+        for (int k = 0; k < WPL; ++k) {
             const uint32_t g = g0 + 64u * k;
             if (FULL || g < G.n_groups) {
-                gather_row<LAYOUT, WHICH>(src, G, j, w, c[k], n1[k], n2[k]);
+                gather_row<WHICH>(src, G, j, w, c[k], n1[k], n2[k]);
                 valid[k] = ~0ull;
             } else {
                 c[k] = n1[k] = n2[k] = valid[k] = 0;
@@ -331,7 +339,7 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < kWordsPerLane; ++k) {
+        for (int k = 0; k < WPL; ++k) {
             const uint32_t g = tile0 + lane + 64u * k;
             c[k] = n1[k] = n2[k] = valid[k] = 0;
             if (FULL || g < G.n_groups)
@@ -343,7 +351,7 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
     uint32_t listed = 0;   // wavefront-uniform list length
     uint32_t chain = 0;    // orders the words' Philox work, see below
 #pragma unroll
-    for (int k = 0; k < kWordsPerLane; ++k) {
+    for (int k = 0; k < WPL; ++k) {
         uint32_t g = tile0 + lane + 64u * k;
         // The words of a tile are independent; left alone the compiler
         // interleaves all their Philox evaluations and needs far more VGPRs.
@@ -352,7 +360,7 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
         asm volatile("" : "+v"(g) : "v"(chain));
         uint64_t P[8];
         draw_planes(dp, (FULL || g < G.n_groups) ? g : 0u, P);
-        const WordDraw wd = compare_planes<PAIRED, COMPLEMENT>(P, c[k], n1[k], n2[k], pm);
+        const WordDraw wd = compare_planes<true, COMPLEMENT>(P, c[k], n1[k], n2[k], pm);
         lt[k] = wd.lt;
         chain = (uint32_t)wd.lt;
         const uint64_t und = FULL ? wd.und : (wd.und & valid[k]);
@@ -377,9 +385,9 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
     constexpr bool kPool = FULL && pooled_layout(LAYOUT);
     for (uint32_t e = lane; e < listed; e += 64u) {
         const uint32_t g = tile0 + wl.local[e];
+        const uint64_t u = wl.und[e];
         uint64_t cc, a1, a2, v;
         gather<LAYOUT, WHICH>(src, G, g, cc, a1, a2, v);
-        const uint64_t u = wl.und[e];
         if constexpr (kPool) {
             const uint64_t first = u & (0ull - u);
             const uint64_t rest = u ^ first;
@@ -400,7 +408,7 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
     }
     wave_sync_lds();
 #pragma unroll
-    for (int k = 0; k < kWordsPerLane; ++k) {
+    for (int k = 0; k < WPL; ++k) {
         const uint32_t g = tile0 + lane + 64u * k;
         const uint64_t bits = FULL ? (lt[k] | wl.und[slot[k]]) : ((lt[k] | wl.und[slot[k]]) & valid[k]);
         if (FULL || g < G.n_groups) {
@@ -428,15 +436,15 @@ __device__ __forceinline__ void half_step_tile(const void* __restrict__ src, voi
 // up and right neighbours, #differences to the partner, #sites) go to
 // partials[4 * block ...] when partials is non-null (a finishing launch turns
 // them into M, A, B), else straight into obs through 64-bit atomics.
-template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS, int WPL>
+template <int LAYOUT, int WHICH, bool COMPLEMENT, bool OBS>
 __device__ __forceinline__ void half_step_body(const void* __restrict__ src, void* __restrict__ dst, const Geom& G,
                                                const DrawParams& dp, int64_t* __restrict__ obs,
                                                int64_t* __restrict__ partials, uint32_t block, uint32_t n_blocks,
                                                HalfStepScratch& sh, int64_t* red) {
     static_assert(!OBS || WHICH == 1, "observables are folded into half-step B");
-    constexpr uint32_t kWaveTile = 64u * WPL;
+    constexpr uint32_t kWaveTile = kMaxWaveTile;
     ObsAcc acc;
-    const PlaneMasks pm = make_plane_masks<PAIRED>(dp);
+    const PlaneMasks pm = make_plane_masks<true>(dp);
     const uint32_t lane = threadIdx.x & 63u;
     WaveList& wl = sh.list[threadIdx.x >> 6];
     if (lane == 0)
@@ -444,7 +452,7 @@ __device__ __forceinline__ void half_step_body(const void* __restrict__ src, voi
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 0; i < 6; ++i)
-            sh.T24[i] = PAIRED ? paired_tail(dp.T, i) : dp.T[i] & 0xFFFFFFu;
+            sh.T24[i] = paired_tail(dp.T, i);
         sh.pool.count = 0;
     }
     __syncthreads();
@@ -457,12 +465,12 @@ __device__ __forceinline__ void half_step_body(const void* __restrict__ src, voi
     constexpr int kPartLayout = LAYOUT == kLayP64Rows ? kLayP64 : LAYOUT;
     for (uint32_t tile = block * kWavesPerBlock + wave; tile < n_tiles; tile += n_blocks * kWavesPerBlock) {
         if (tile < n_full) {
-            half_step_tile<LAYOUT, WHICH, PAIRED, COMPLEMENT, OBS, true, WPL>(src, dst, G, dp, pm, sh.T24, wl,
+            half_step_tile<LAYOUT, WHICH, COMPLEMENT, OBS, true, kWordsPerLane>(src, dst, G, dp, pm, sh.T24, wl,
                                                                               tile * kWaveTile, lane, acc, sh.pool);
         } else {
             // the last, partial tile: 64 words at a time, with bounds checks
             for (uint32_t sub = tile * kWaveTile; sub < (tile + 1) * kWaveTile; sub += 64u)
-                half_step_tile<kPartLayout, WHICH, PAIRED, COMPLEMENT, OBS, false, 1>(src, dst, G, dp, pm, sh.T24,
+                half_step_tile<kPartLayout, WHICH, COMPLEMENT, OBS, false, 1>(src, dst, G, dp, pm, sh.T24,
                                                                                        wl, sub, lane, acc, sh.pool);
         }
     }
@@ -511,44 +519,74 @@ __device__ __forceinline__ void half_step_body(const void* __restrict__ src, voi
 }
 
 // The half-step kernel, held to six wavefronts per SIMD (80 VGPRs) where that
-// costs no scratch spills (the plain half-steps on 64- and 32-bit words with
-// the paired compare), and left to the compiler's register count otherwise.
-template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
+// costs no scratch spills (the plain half-steps), and left to the compiler's
+// register count with observables.
+template <int LAYOUT, int WHICH, bool COMPLEMENT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_half_step(
-    const void* __restrict__ src, void* __restrict__ dst, Geom G, DrawParams dp, int64_t* __restrict__ obs,
-    int64_t* __restrict__ partials) {
+    const void* __restrict__ src, void* __restrict__ dst, Geom G, DrawParams dp) {
     __shared__ HalfStepScratch sh;
     __shared__ int64_t red[4 * 4];
-    half_step_body<LAYOUT, WHICH, PAIRED, COMPLEMENT, OBS, words_per_lane(LAYOUT, PAIRED)>(
-        src, dst, G, dp, obs, partials, blockIdx.x, gridDim.x, sh, red);
+    half_step_body<LAYOUT, WHICH, COMPLEMENT, false>(src, dst, G, dp, nullptr, nullptr, blockIdx.x, gridDim.x, sh, red);
 }
 
-template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
-__global__ __launch_bounds__(256) void k_half_step_free(const void* __restrict__ src, void* __restrict__ dst, Geom G,
-                                                        DrawParams dp, int64_t* __restrict__ obs,
-                                                        int64_t* __restrict__ partials) {
+template <int LAYOUT, bool COMPLEMENT>
+__global__ __launch_bounds__(256) void k_half_step_obs(const void* __restrict__ src, void* __restrict__ dst, Geom G,
+                                                       DrawParams dp, int64_t* __restrict__ obs,
+                                                       int64_t* __restrict__ partials) {
     __shared__ HalfStepScratch sh;
     __shared__ int64_t red[4 * 4];
-    half_step_body<LAYOUT, WHICH, PAIRED, COMPLEMENT, OBS, words_per_lane(LAYOUT, PAIRED)>(
-        src, dst, G, dp, obs, partials, blockIdx.x, gridDim.x, sh, red);
+    half_step_body<LAYOUT, 1, COMPLEMENT, true>(src, dst, G, dp, obs, partials, blockIdx.x, gridDim.x, sh, red);
 }
 
-constexpr bool six_waves(int layout, bool paired, bool obs) {
-    return paired && !obs && (layout == kLayP64 || layout == kLayP64Rows || layout == kLayP32);
+// One-word tiles: a wavefront's 64 lanes hold one word each.
+//
+// Undecided sites are listed one per lane and round of ballots with the class
+// the owner already has in registers, drawn one per lane, and handed back
+// through an LDS word per lane, so a tile reads global memory once and stores
+// once.  Such launches last as long as one wavefront's chain of latencies (a
+// wavefront per SIMD or less), which is what this form shortens: the wide
+// tiles reload a listed word's neighbours from memory, and leave second sites
+// to a pass after the stores, which pays when the tail draws themselves bound
+// the launch (large lattices of packed words, see wide_tiles).  Against the wide
+// form, us per half-step: 512^2 packed 6.5 -> 3.8, 200^2 9.1 -> 4.0, 512^2 int8
+// 6.6 -> 4.6.
+constexpr uint32_t kSiteCap = 128;   // a round adds at most 64 entries and 64 listed sites are drawn at once
+
+struct SiteList {
+    uint64_t plus[64];          // decided +1 sites of each lane's word
+    uint32_t entry[kSiteCap];   // lane | bit << 6 | class << 12
+};
+
+struct OneWordScratch {
+    SiteList list[kWavesPerBlock];
+    uint32_t T24[6];
+    uint32_t sums[kWavesPerBlock][4];
+};
+
+// The listed sites, one per lane, of the tile whose first word is g0.
+__device__ __forceinline__ void draw_listed(const DrawParams& dp, const uint32_t* T24, SiteList& sl, uint32_t n,
+                                            uint32_t g0) {
+    wave_sync_lds();
+    for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
+        const uint32_t v = sl.entry[e];
+        const uint32_t l = v & 63u, b = (v >> 6) & 63u;
+        if (draw_tail24(dp, 64u * (g0 + l) + b) < T24[v >> 12])
+            atomicOr(reinterpret_cast<unsigned long long*>(&sl.plus[l]), 1ull << b);
+    }
+    wave_sync_lds();
 }
 
-// Several chains of one size advanced together: workgroups
+// Several chains of one size advanced together (or one chain): workgroups
 // chain * blocks_per_chain .. (chain + 1) * blocks_per_chain - 1 take the
 // half-step of chain `chain`, with its own lattices, threshold table and
 // stream id (the per-chain values are wavefront-uniform kernel arguments).
-// Tiles of 64 words (one word per lane) give lattices of a few thousand
-// words enough wavefronts.  Partial sums of recorded steps go to
-// partials[4 * workgroup ...], chain-major.
+// Partial sums of recorded steps go to partials[4 * workgroup ...],
+// chain-major, or (one chain, partials null) by atomics into obs.
 template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
 __global__ __launch_bounds__(256) void k_half_step_many(ManyChains mc, Geom G, DrawParams base,
-                                                        int64_t* __restrict__ partials) {
-    __shared__ HalfStepScratch sh;
-    __shared__ int64_t red[4 * 4];
+                                                        int64_t* __restrict__ obs, int64_t* __restrict__ partials) {
+    static_assert(!OBS || WHICH == 1, "observables are folded into half-step B");
+    __shared__ OneWordScratch sh;
     const uint32_t chain = blockIdx.x / mc.blocks_per_chain;
     const uint32_t block = blockIdx.x - chain * mc.blocks_per_chain;
     DrawParams dp = base;
@@ -556,9 +594,80 @@ __global__ __launch_bounds__(256) void k_half_step_many(ManyChains mc, Geom G, D
     for (int i = 0; i < 6; ++i)
         dp.T[i] = mc.T[chain][i];
     dp.stream = mc.stream[chain];
-    half_step_body<LAYOUT, WHICH, PAIRED, COMPLEMENT, OBS, 1>(
-        WHICH == 0 ? mc.sigma[chain] : mc.tau[chain], WHICH == 0 ? mc.tau[chain] : mc.sigma[chain], G, dp, nullptr,
-        partials + 4u * (size_t)chain * mc.blocks_per_chain, block, mc.blocks_per_chain, sh, red);
+    const void* src = WHICH == 0 ? mc.sigma[chain] : mc.tau[chain];
+    void* dst = WHICH == 0 ? mc.tau[chain] : mc.sigma[chain];
+    const PlaneMasks pm = make_plane_masks<PAIRED>(dp);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    SiteList& sl = sh.list[wave];
+    if (threadIdx.x < 6)
+        sh.T24[threadIdx.x] =
+            PAIRED ? paired_tail(mc.T[chain], (int)threadIdx.x) : mc.T[chain][threadIdx.x] & 0xFFFFFFu;
+    __syncthreads();
+    uint32_t pc = 0, dpair = 0, dself = 0, nsites = 0;   // a wavefront holds far fewer than 2^31 sites
+    const uint32_t n_tiles = (G.n_groups + 63u) / 64u;
+    for (uint32_t tile = block * kWavesPerBlock + wave; tile < n_tiles; tile += mc.blocks_per_chain * kWavesPerBlock) {
+        const uint32_t g0 = 64u * tile, g = g0 + lane;
+        const bool active = g < G.n_groups;
+        uint64_t c = 0, n1 = 0, n2 = 0, valid = 0;
+        if (active)
+            gather<LAYOUT, WHICH>(src, G, g, c, n1, n2, valid);
+        sl.plus[lane] = 0;
+        uint64_t P[8];
+        draw_planes(dp, active ? g : 0u, P);
+        const WordDraw wd = compare_planes<PAIRED, COMPLEMENT>(P, c, n1, n2, pm);
+        uint64_t und = wd.und & valid;
+        uint32_t listed = 0;   // wavefront-uniform
+        for (;;) {
+            const uint64_t m = __ballot(und != 0);
+            if (m == 0)
+                break;
+            if (und != 0) {
+                const uint32_t e = listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                const int b = __ffsll((unsigned long long)und) - 1;
+                und &= und - 1;
+                sl.entry[e] = lane | ((uint32_t)b << 6) | (class_at(c, n1, n2, b) << 12);
+            }
+            listed += (uint32_t)__popcll(m);
+            if (listed >= 64u) {
+                draw_listed(dp, sh.T24, sl, listed, g0);
+                listed = 0;
+            }
+        }
+        draw_listed(dp, sh.T24, sl, listed, g0);
+        const uint64_t bits = (wd.lt | sl.plus[lane]) & valid;
+        if (active) {
+            scatter<LAYOUT>(dst, G, g, bits, valid);
+            if constexpr (OBS) {
+                pc += __popcll(bits);
+                dpair += __popcll((bits ^ n1) & valid) + __popcll((bits ^ n2) & valid);
+                dself += __popcll((bits ^ c) & valid);
+                nsites += __popcll(valid);
+            }
+        }
+    }
+    if constexpr (OBS) {
+        const uint32_t v[4] = {wave_sum_dpp(pc), wave_sum_dpp(dpair), wave_sum_dpp(dself), wave_sum_dpp(nsites)};
+        if (lane == 0)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                sh.sums[wave][i] = v[i];
+        __syncthreads();
+        if (threadIdx.x < 4) {
+            int64_t t = 0, n = 0;
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                t += (int64_t)sh.sums[w][threadIdx.x];
+                n += (int64_t)sh.sums[w][3];
+            }
+            if (partials)
+                partials[4u * (size_t)blockIdx.x + threadIdx.x] = t;
+            else if (threadIdx.x < 3)
+                atomicAdd(reinterpret_cast<unsigned long long*>(obs + threadIdx.x),
+                          (unsigned long long)(threadIdx.x == 0 ? 2 * t - n : (threadIdx.x == 1 ? 2 * n : n) - 2 * t));
+        }
+    }
 }
 
 // Sites of 64-site group g that lie in a lattice of n_sites sites.
@@ -715,34 +824,26 @@ uint32_t grid_for(uint32_t n_groups) {
 
 }  // namespace
 
-template <int LAY, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
-void launch_half_step_kernel(dim3 grid, dim3 block, hipStream_t st, const void* src, void* dst, const Geom& G,
-                             const DrawParams& dp, int64_t* obs, int64_t* partials) {
-    if constexpr (six_waves(LAY, PAIRED, OBS))
-        hipLaunchKernelGGL((k_half_step<LAY, WHICH, PAIRED, COMPLEMENT, OBS>), grid, block, 0, st, src, dst, G, dp,
-                           obs, partials);
-    else
-        hipLaunchKernelGGL((k_half_step_free<LAY, WHICH, PAIRED, COMPLEMENT, OBS>), grid, block, 0, st, src, dst,
-                           G, dp, obs, partials);
-}
+// Which half-steps take the wide tiles: packed words with the paired compare
+// on lattices of at least kWideTiles of them (12 wavefronts of work a SIMD).
+// Below that the launch lasts as long as one wavefront's work and one-word
+// tiles are quicker (us per half-step, wide -> one word: 512^2 6.5 -> 3.8,
+// 2048^2 7.0 -> 4.0, 4096^2 7.4 -> 5.9, 6144^2 10.8 -> 9.5, 6976^2 11.3 ->
+// 11.6, 8192^2 13.0 -> 14.4); on bit strings and int8 words, whose gathers and
+// reloads cost more, they are at every size (8200^2 packed 22.1 -> 19.0,
+// 24008^2 109 -> 101; 2048^2 int8 7.6 -> 5.7, 16384^2 int8 173 -> 166), and the
+// six-class compare is a cross-check that needs no second form.
+constexpr uint32_t kWideTiles = 2816;
 
-template <int LAY, int WHICH, bool OBS>
-void launch_half_step_mode(bool paired, bool complement, dim3 grid, dim3 block, hipStream_t st, const void* src,
-                           void* dst, const Geom& G, const DrawParams& dp, int64_t* obs, int64_t* partials) {
-    if (paired && !complement)
-        launch_half_step_kernel<LAY, WHICH, true, false, OBS>(grid, block, st, src, dst, G, dp, obs, partials);
-    else if (paired)
-        launch_half_step_kernel<LAY, WHICH, true, true, OBS>(grid, block, st, src, dst, G, dp, obs, partials);
-    else if (!complement)
-        launch_half_step_kernel<LAY, WHICH, false, false, OBS>(grid, block, st, src, dst, G, dp, obs, partials);
-    else
-        launch_half_step_kernel<LAY, WHICH, false, true, OBS>(grid, block, st, src, dst, G, dp, obs, partials);
+static bool wide_tiles(int layout, const Geom& G, bool paired) {
+    return paired && (layout == kLayP64 || layout == kLayP32) &&
+           (G.n_groups + kMaxWaveTile - 1) / kMaxWaveTile >= kWideTiles;
 }
 
 uint32_t half_step_blocks(int layout, const Geom& G, bool paired, uint32_t max_blocks) {
     // one workgroup per four wavefront tiles; at most kMaxBlocks by default,
     // at most max_blocks when the caller gives a cap
-    const uint32_t wave_tile = 64u * words_per_lane(layout, paired);
+    const uint32_t wave_tile = wide_tiles(layout, G, paired) ? kMaxWaveTile : 64u;
     const uint32_t tiles = (G.n_groups + wave_tile - 1) / wave_tile;
     uint32_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     blocks = blocks ? blocks : 1u;
@@ -756,57 +857,78 @@ hipError_t launch_obs_finish(const int64_t* partials, uint32_t n_blocks, uint32_
     return hipGetLastError();
 }
 
+template <int LAY, bool COMPLEMENT>
+void launch_wide(int which, uint32_t blocks, hipStream_t st, const void* src, void* dst, const Geom& G,
+                 const DrawParams& dp, int64_t* obs, int64_t* partials) {
+    const dim3 grid(blocks), block(256);
+    if (which == 0)
+        hipLaunchKernelGGL((k_half_step<LAY, 0, COMPLEMENT>), grid, block, 0, st, src, dst, G, dp);
+    else if (obs == nullptr)
+        hipLaunchKernelGGL((k_half_step<LAY, 1, COMPLEMENT>), grid, block, 0, st, src, dst, G, dp);
+    else
+        hipLaunchKernelGGL((k_half_step_obs<LAY, COMPLEMENT>), grid, block, 0, st, src, dst, G, dp, obs, partials);
+}
+
+static hipError_t launch_one_word(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
+                                  bool paired, int64_t* obs, int64_t* partials, hipStream_t st);
+
 hipError_t launch_half_step(int layout, int which, const void* src, void* dst, const Geom& G, const DrawParams& dp,
                             int64_t* obs, hipStream_t st, uint32_t max_blocks, int64_t* partials, bool general,
                             bool finish) {
     const bool paired = !general && thresholds_paired(dp.T);
     const uint32_t blocks = half_step_blocks(layout, G, paired, max_blocks);
-    const dim3 grid(blocks), block(256);
-    const bool complement = dp.rng_xor != 0;
-#define SD_HALF(LAY)                                                                                       \
-    case LAY:                                                                                              \
-        if (which == 0)                                                                                    \
-            launch_half_step_mode<LAY, 0, false>(paired, complement, grid, block, st, src, dst, G, dp,      \
-                                                 nullptr, nullptr);                                        \
-        else if (obs == nullptr)                                                                           \
-            launch_half_step_mode<LAY, 1, false>(paired, complement, grid, block, st, src, dst, G, dp,      \
-                                                 nullptr, nullptr);                                        \
-        else                                                                                               \
-            launch_half_step_mode<LAY, 1, true>(paired, complement, grid, block, st, src, dst, G, dp, obs,  \
-                                                partials);                                                 \
+    const bool record = which == 1 && obs != nullptr;
+    hipError_t e;
+    if (wide_tiles(layout, G, paired)) {
+        const bool complement = dp.rng_xor != 0;
+        const int klay = (layout == kLayP64 && G.words_row % 64u == 0) ? kLayP64Rows : layout;
+#define SD_WIDE(LAY)                                                                                        \
+    case LAY:                                                                                               \
+        if (complement)                                                                                     \
+            launch_wide<LAY, true>(which, blocks, st, src, dst, G, dp, obs, partials);                      \
+        else                                                                                                \
+            launch_wide<LAY, false>(which, blocks, st, src, dst, G, dp, obs, partials);                     \
         break;
-    const int klay = (layout == kLayP64 && G.words_row % 64u == 0) ? kLayP64Rows : layout;
-    switch (klay) {
-        SD_HALF(kLayP64Rows)
-        SD_HALF(kLayP64)
-        SD_HALF(kLayP32)
-        SD_HALF(kLayI8Row)
-        SD_HALF(kLayI8Any)
-        SD_HALF(kLayBits)
-        default:
-            return hipErrorInvalidValue;
+        switch (klay) {
+            SD_WIDE(kLayP64Rows)
+            SD_WIDE(kLayP64)
+            SD_WIDE(kLayP32)
+            default:
+                return hipErrorInvalidValue;
+        }
+#undef SD_WIDE
+        e = hipGetLastError();
+    } else {
+        ManyChains mc;
+        std::memset(&mc, 0, sizeof mc);
+        mc.sigma[0] = which == 0 ? const_cast<void*>(src) : dst;
+        mc.tau[0] = which == 0 ? dst : const_cast<void*>(src);
+        std::memcpy(mc.T[0], dp.T, sizeof dp.T);
+        mc.stream[0] = dp.stream;
+        mc.n_chains = 1;
+        mc.blocks_per_chain = blocks;
+        e = launch_one_word(layout, which, mc, G, dp, paired, record ? obs : nullptr, record ? partials : nullptr, st);
     }
-#undef SD_HALF
-    if (which == 1 && obs != nullptr && partials != nullptr && finish)
-        hipLaunchKernelGGL(k_obs_finish, dim3(1), dim3(1024), 0, st, partials, blocks, 0u, obs);
-    return hipGetLastError();
+    if (e == hipSuccess && record && partials != nullptr && finish)
+        e = launch_obs_finish(partials, blocks, 1, 0, obs, st);
+    return e;
 }
 
 template <int LAY, int WHICH, bool OBS>
 void launch_many_mode(bool paired, bool complement, dim3 grid, hipStream_t st, const ManyChains& mc, const Geom& G,
-                      const DrawParams& dp, int64_t* partials) {
+                      const DrawParams& dp, int64_t* obs, int64_t* partials) {
     if (paired && !complement)
         hipLaunchKernelGGL((k_half_step_many<LAY, WHICH, true, false, OBS>), grid, dim3(256), 0, st, mc, G, dp,
-                           partials);
+                           obs, partials);
     else if (paired)
         hipLaunchKernelGGL((k_half_step_many<LAY, WHICH, true, true, OBS>), grid, dim3(256), 0, st, mc, G, dp,
-                           partials);
+                           obs, partials);
     else if (!complement)
         hipLaunchKernelGGL((k_half_step_many<LAY, WHICH, false, false, OBS>), grid, dim3(256), 0, st, mc, G, dp,
-                           partials);
+                           obs, partials);
     else
         hipLaunchKernelGGL((k_half_step_many<LAY, WHICH, false, true, OBS>), grid, dim3(256), 0, st, mc, G, dp,
-                           partials);
+                           obs, partials);
 }
 
 uint32_t many_blocks_per_chain(const Geom& G) {
@@ -815,22 +937,20 @@ uint32_t many_blocks_per_chain(const Geom& G) {
     return blocks < kMaxBlocks ? (blocks ? blocks : 1u) : kMaxBlocks;
 }
 
-hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
-                                 bool paired, int64_t* partials, hipStream_t st) {
+static hipError_t launch_one_word(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
+                                  bool paired, int64_t* obs, int64_t* partials, hipStream_t st) {
     const dim3 grid(mc.n_chains * mc.blocks_per_chain);
     const bool complement = base.rng_xor != 0;
-    const int klay = (layout == kLayP64 && G.words_row % 64u == 0) ? kLayP64Rows : layout;
-#define SD_MANY(LAY)                                                                                       \
-    case LAY:                                                                                              \
-        if (which == 0)                                                                                    \
-            launch_many_mode<LAY, 0, false>(paired, complement, grid, st, mc, G, base, nullptr);          \
-        else if (partials == nullptr)                                                                      \
-            launch_many_mode<LAY, 1, false>(paired, complement, grid, st, mc, G, base, nullptr);          \
-        else                                                                                               \
-            launch_many_mode<LAY, 1, true>(paired, complement, grid, st, mc, G, base, partials);          \
+#define SD_MANY(LAY)                                                                                        \
+    case LAY:                                                                                               \
+        if (which == 0)                                                                                     \
+            launch_many_mode<LAY, 0, false>(paired, complement, grid, st, mc, G, base, nullptr, nullptr);  \
+        else if (obs == nullptr && partials == nullptr)                                                     \
+            launch_many_mode<LAY, 1, false>(paired, complement, grid, st, mc, G, base, nullptr, nullptr);  \
+        else                                                                                                \
+            launch_many_mode<LAY, 1, true>(paired, complement, grid, st, mc, G, base, obs, partials);      \
         break;
-    switch (klay) {
-        SD_MANY(kLayP64Rows)
+    switch (layout) {
         SD_MANY(kLayP64)
         SD_MANY(kLayP32)
         SD_MANY(kLayI8Row)
@@ -841,6 +961,11 @@ hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, co
     }
 #undef SD_MANY
     return hipGetLastError();
+}
+
+hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
+                                 bool paired, int64_t* partials, hipStream_t st) {
+    return launch_one_word(layout, which, mc, G, base, paired, nullptr, partials, st);
 }
 
 hipError_t launch_obs_finish_many(const int64_t* partials, uint32_t n_blocks, uint32_t n_chains, uint32_t n_rec,

@@ -400,34 +400,55 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
 // ---------------------------------------------------------------------------
 // int8 lattices (+1 -> 0x01, -1 -> 0xFF) and 64-site bit words
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t bytes_to_bits4(uint32_t x) {
-    // byte k of x is 0x01 (+1) or 0xFF (-1); bit k of the result is 1 for +1
-    uint32_t y = (~x >> 7) & 0x01010101u;
-    return (y * 0x10204080u) >> 28;
+// 32 sites, 4 per word of x, as bits (1 = +1).  Bit 1 of a site's byte is its
+// complement; two 4-way byte dot products with powers of two as weights gather
+// eight of them (twice the value, in nine bits): 21 instructions where
+// shifting, masking and multiplying each word took 47.
+__device__ __forceinline__ uint32_t bytes_to_bits32(const uint32_t (&x)[8]) {
+    uint32_t n[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        n[k] = __builtin_amdgcn_udot4(x[2 * k] & 0x02020202u, 0x08040201u, 0u, false);
+        n[k] = __builtin_amdgcn_udot4(x[2 * k + 1] & 0x02020202u, 0x80402010u, n[k], false);
+    }
+    return ~(((n[0] + (n[1] << 8) + (n[2] << 16)) >> 1) | (n[3] << 23));
 }
 
 __device__ __forceinline__ uint32_t bits4_to_bytes(uint32_t n) {
-    uint32_t z = (n * 0x00204081u) & 0x01010101u;   // byte k = bit k of n
-    uint32_t w = z ^ 0x01010101u;                    // 1 where the spin is -1
-    return z | ((w << 8) - w);
+    const uint32_t z = (n * 0x00204081u) & 0x01010101u;   // byte k = bit k of n
+    return ~(z * 0xFEu);                                  // 0x01 where set, else 0xFF
 }
 
-// The 64 sites at p (16-byte aligned) as one word, bit b = site b.
+// 16 bytes at any address: gfx950's global memory takes unaligned dwordx4
+// accesses, so these are one load or store each.
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
+
+// The 64 sites at p as one word, bit b = site b.  ALIGNED: p is 16-byte aligned.
+template <bool ALIGNED = true>
 __device__ __forceinline__ uint64_t load_bits64_i8(const int8_t* p) {
-    const uint4* v = reinterpret_cast<const uint4*>(p);
-    uint64_t bits = 0;
+    uint32_t x[2][8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        uint4 x = v[q];
-        uint32_t b16 = bytes_to_bits4(x.x) | (bytes_to_bits4(x.y) << 4) | (bytes_to_bits4(x.z) << 8) |
-                       (bytes_to_bits4(x.w) << 12);
-        bits |= (uint64_t)b16 << (16 * q);
+        uint4 v;
+        if constexpr (ALIGNED) {
+            v = reinterpret_cast<const uint4*>(p)[q];
+        } else {
+            const Bytes16 b = reinterpret_cast<const Bytes16*>(p)[q];
+            v = make_uint4(b.x, b.y, b.z, b.w);
+        }
+        uint32_t* d = &x[q >> 1][4 * (q & 1)];
+        d[0] = v.x;
+        d[1] = v.y;
+        d[2] = v.z;
+        d[3] = v.w;
     }
-    return bits;
+    return (uint64_t)bytes_to_bits32(x[0]) | ((uint64_t)bytes_to_bits32(x[1]) << 32);
 }
 
+template <bool ALIGNED = true>
 __device__ __forceinline__ void store_bits64_i8(int8_t* p, uint64_t bits) {
-    uint4* v = reinterpret_cast<uint4*>(p);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uint32_t b16 = (uint32_t)(bits >> (16 * q)) & 0xFFFFu;
@@ -436,8 +457,22 @@ __device__ __forceinline__ void store_bits64_i8(int8_t* p, uint64_t bits) {
         x.y = bits4_to_bytes((b16 >> 4) & 0xF);
         x.z = bits4_to_bytes((b16 >> 8) & 0xF);
         x.w = bits4_to_bytes((b16 >> 12) & 0xF);
-        v[q] = x;
+        if constexpr (ALIGNED)
+            reinterpret_cast<uint4*>(p)[q] = x;
+        else
+            reinterpret_cast<Bytes16*>(p)[q] = Bytes16{x.x, x.y, x.z, x.w};
     }
+}
+
+// Sites pos .. pos + 63 (mod n_sites) of an int8 lattice at any address, as
+// one word; 64 <= n_sites, pos < n_sites.  Every load lies inside the lattice.
+__device__ __forceinline__ uint64_t window_i8(const int8_t* s, uint32_t n_sites, uint32_t pos) {
+    const uint32_t room = n_sites - pos;   // sites before the lattice's end
+    if (room >= 64u)
+        return load_bits64_i8<false>(s + pos);
+    const uint64_t tail = load_bits64_i8<false>(s + (n_sites - 64u));
+    const uint64_t head = load_bits64_i8<false>(s);
+    return (tail >> (64u - room)) | (head << room);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,9 +1,11 @@
 """GPU parity of the size-dependent kernel variants at the edges of their
 ranges."""
+import numpy as np
 import pytest
 import torch
 
 import paper_1908_07341_amd as sd
+from paper_1908_07341_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +47,62 @@ def test_batch_init_equals_sd_init_per_chain(layout, offset, kind, p_up):
     with pytest.raises(sd.ShakenError):
         sd.sd_batch_init(plan, buf, sd.SD_INIT_RANDOM, 1.5)
     plan.close()
+
+
+@pytest.mark.parametrize("L", [7, 8, 9, 11, 31, 63, 65, 127, 333])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_int8_windows(oracle, L, offset):
+    # lattices of one word and less (7, 8), rows shorter than a word, rows whose
+    # wrap falls on every bit of a word, a last word of any length, and
+    # neighbour windows across the lattice's end; any address
+    print(f"int8 windows L={L} offset={offset}", flush=True)
+    lat = inputs.random_lattice(L, L)
+    buf = torch.zeros(2 * (L * L + 16), dtype=torch.int8, device="cuda")
+    src = buf[offset:offset + L * L]
+    dst = buf[L * L + 16 - (16 - offset) % 16:][:L * L]
+    for which in (0, 1):
+        src.copy_(torch.from_numpy(lat.reshape(-1)))
+        sd.sd_half_step(src, dst, L, sd.SD_I8, which, 0.4, 0.9, SEED, 3, 6 + which)
+        want = oracle.half_step(lat, 0.4, 0.9, which, SEED, 3, 6 + which)
+        assert np.array_equal(dst.cpu().numpy().reshape(L, L), want)
+        assert np.array_equal(src.cpu().numpy().reshape(L, L), lat)
+
+
+@pytest.mark.parametrize("L,layout", [(6784, sd.SD_P64), (6848, sd.SD_P64), (8192, sd.SD_P64), (6848, sd.SD_P32),
+                                      (6720, sd.SD_P32)])
+def test_wide_and_one_word_tiles_agree(L, layout):
+    # below and above the size from which packed lattices take wide tiles; the
+    # runs of sd_run_many too short for whole steps take one-word tiles
+    print(f"tiles L={L} layout={layout}", flush=True)
+    lat = [sd.new_lattice(L, layout) for _ in range(4)]
+    for x in (lat[0], lat[2]):
+        sd.sd_init(x, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    obs = torch.empty((2, 2, 3), dtype=torch.int64, device="cuda")
+    sd.sd_run(lat[0], lat[1], L, layout, 0.5, 0.5, SEED, 1, 0, 2, obs[0], 1)
+    sd.sd_run_many([lat[2]], [lat[3]], L, layout, [0.5], [0.5], SEED, [1], 0, 2, obs[1], 1)
+    assert torch.equal(lat[0], lat[2]) and torch.equal(lat[1], lat[3]) and torch.equal(obs[0], obs[1])
+
+
+@pytest.mark.parametrize("L,layout", [(100, sd.SD_I8), (200, sd.SD_P64), (576, sd.SD_P64)])
+def test_records_of_one_word_tiles_under_capture(oracle, L, layout):
+    # no partial-sum buffer can be made on a stream first used under capture:
+    # the records come from atomics, and every replay writes the same ones
+    print(f"capture L={L} layout={layout}", flush=True)
+    sigma, tau = sd.new_lattice(L, layout), sd.new_lattice(L, layout)
+    start = inputs.random_lattice(L, 5)
+    host = start if layout == sd.SD_I8 else inputs.pack_bits(start)
+    first = torch.from_numpy(host.reshape(-1).copy()).cuda()
+    flat = sigma.reshape(-1).view(torch.int8 if layout == sd.SD_I8 else torch.uint8)
+    obs = torch.empty((3, 3), dtype=torch.int64, device="cuda")
+    _, _, want = oracle.run(start, 0.4, 0.6, SEED, 2, 0, 3, obs_every=1)
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        flat.copy_(first)
+        sd.sd_run(sigma, tau, L, layout, 0.4, 0.6, SEED, 2, 0, 3, obs, 1, sd.SD_FLAG_GLOBAL_KERNELS)
+    for _ in range(3):
+        obs.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(obs.cpu().numpy(), want)
