@@ -18,6 +18,7 @@
 #include "sd_batch.hpp"
 #include "sd_host.hpp"
 #include "sd_kernels.hpp"
+#include "sd_small.hpp"
 
 namespace sd {
 
@@ -196,6 +197,51 @@ uint32_t lds_max_words() {
     return w;
 }
 
+hipError_t device_limits(uint32_t* n_cu, size_t* max_lds) {
+    int dev = 0, cu = 0, lds = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    *n_cu = (uint32_t)cu;
+    *max_lds = (size_t)lds;
+    return e;
+}
+
+SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stream, uint64_t step0, uint32_t k_steps,
+                     uint32_t flags) {
+    SmallArgs a;
+    std::memset(&a, 0, sizeof a);
+    threshold_table(J, q, a.T);
+    a.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
+    a.key1 = (uint32_t)(seed >> 32);
+    a.stream = stream;
+    a.t0 = (uint32_t)(2 * step0);
+    a.n_half = 2u * k_steps;
+    a.rng_xor = (flags & SD_FLAG_COMPLEMENT_RNG) ? 0xFFFFFFFFu : 0u;
+    a.L = (uint32_t)L;
+    a.n = lattice_words((uint32_t)L);
+    a.div_n = make_fastdiv(a.n);
+    a.div_L = make_fastdiv((uint32_t)L);
+    return a;
+}
+
+static hipError_t launch_small_chain(void* sigma, void* tau, int32_t L, bool int8, double J, double q, uint64_t seed,
+                                     uint32_t stream, uint64_t step0, uint32_t k_steps, int64_t* obs,
+                                     uint32_t obs_every, uint32_t flags, hipStream_t st) {
+    uint32_t n_cu = 0;
+    size_t max_lds = 0;
+    const hipError_t e = device_limits(&n_cu, &max_lds);
+    if (e != hipSuccess)
+        return e;
+    SmallArgs a = small_args(L, J, q, seed, stream, step0, k_steps, flags);
+    a.sigma = sigma;
+    a.tau = tau;
+    a.int8_io = int8 ? 1u : 0u;
+    a.obs = obs;
+    a.obs_every = obs ? obs_every : 1u;
+    return launch_small(a, 1, false, n_cu, max_lds, st);
+}
+
 Workspace* partials_workspace(hipStream_t st) {
     static std::mutex mu;
     static std::map<std::pair<int, hipStream_t>, Workspace*> spaces;   // kept until the process ends
@@ -281,6 +327,18 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                                         : kLayI8Any)
                                  : kernel_layout(L, layout, sigma);
     const RunChoice ch = run_choice(L, layout);
+    // At most 64 words: one workgroup that draws ahead of the chain (k_small),
+    // for every layout (int8 at any address; 64-bit words need their alignment,
+    // which 32-bit-word lattices may lack).  The six-class cross-check keeps
+    // the general kernels.
+    const bool words_ok = layout == SD_I8 || ((reinterpret_cast<uintptr_t>(sigma) | reinterpret_cast<uintptr_t>(tau)) & 7u) == 0;
+    if (small_supported(L) && words_ok && ch.mode != 2 && !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE))) {
+        if (k_steps == 0)
+            return SD_OK;
+        const hipError_t e = launch_small_chain(sigma, tau, L, layout == SD_I8, J, q, seed, stream, step0, k_steps,
+                                                k_steps >= obs_every ? obs : nullptr, obs_every, flags, st);
+        return e == hipSuccess ? SD_OK : hip_fail(e, name);
+    }
     if (layout != SD_I8 && L % 64 == 0)
         klay = ch.width == 32 ? kLayP32 : kLayP64;
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
@@ -712,8 +770,11 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
     // candidates
     std::vector<RunChoice> cands;
     const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
-    const bool lds_layout = L % 64 == 0;
-    if (lds_layout && n_words <= lds_max_words())
+    if (small_supported(L)) {   // the small-lattice kernel picks its own workgroup
+        RunChoice c;
+        c.mode = 1;
+        cands.push_back(c);
+    } else if (L % 64 == 0 && n_words <= lds_max_words())
         for (uint32_t th : {128u, 256u, 512u}) {
             RunChoice c;
             c.mode = 1;

@@ -1,0 +1,509 @@
+// Chains of small lattices (at most 64 words of 64 sites: L % 8 == 0, L <= 64),
+// one workgroup per chain or per coupled pair of chains.
+//
+// A half-step (eqs. (15)-(16)) draws every site from one of six thresholds,
+// picked by the site's class, and its uniform depends only on (seed, stream,
+// half-step, site).  So the draws of all six classes can be made before the
+// lattice is known: the class mask k of a half-step holds, per site, whether
+// r_s < T[k].  Most wavefronts of the workgroup ("workers") compute the masks
+// of the next H half-steps into LDS while one wavefront ("walker", one word
+// per lane) takes the lattice through the current H: per half-step it only
+// fetches the neighbours, picks each site's bit among six masks and writes the
+// new word.  What such a chain waits for is the dependence of a half-step on
+// the last one; drawing ahead leaves about 30 instructions in that chain
+// instead of a whole draw (four plane calls, the scan, the tails, a workgroup
+// barrier): @@FIG@@.
+//
+// Coupled pairs (coupling from the past, section 3.2) share their uniforms, so
+// one set of masks serves two walkers.
+#include "sd_small.hpp"
+
+namespace sd {
+
+namespace {
+
+constexpr uint32_t kListCap = 128;
+
+// A worker wavefront's scratch: the sites of each lane's word whose top byte
+// equals class k's, and the list of sites whose tails are to be drawn.
+struct Worker {
+    uint64_t eq[6][64];
+    uint32_t entry[kListCap];   // lane | bit << 6
+};
+
+__device__ __forceinline__ void small_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Philox4x32-10 with lane-varying second and fourth counter words (a tile of
+// words covers several half-steps).  Rounds 1-3 in plain products, so that
+// the four plane calls of a word share what does not depend on the plane.
+__device__ __forceinline__ U4 philox10_uvuv(uint32_t u0, uint32_t v1, uint32_t u2, uint32_t v3, uint32_t k0,
+                                            uint32_t k1) {
+    const uint64_t a0 = (uint64_t)kPhiloxM0 * u0;
+    const uint64_t a1 = (uint64_t)kPhiloxM1 * u2;
+    U4 c;
+    c.x0 = (hi32(a1) ^ k0) ^ v1;
+    c.x1 = lo32(a1);
+    c.x2 = (hi32(a0) ^ k1) ^ v3;
+    c.x3 = lo32(a0);
+#pragma unroll
+    for (int r = 1; r < 10; ++r) {
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
+        if (r < 3) {
+            const uint64_t p0 = (uint64_t)kPhiloxM0 * c.x0;
+            const uint64_t p1 = (uint64_t)kPhiloxM1 * c.x2;
+            c = U4{hi32(p1) ^ (c.x1 ^ k0), lo32(p1), hi32(p0) ^ (c.x3 ^ k1), lo32(p0)};
+        } else {
+            c = philox_round(c, k0, k1);
+        }
+    }
+    return c;
+}
+
+// Truth tables (operand patterns 0xF0, 0xCC, 0xAA): less-than from the least
+// significant bit up, lt' = r bit 0 and threshold bit 1, or bits equal and lt;
+// equality so far; select b where a else c.
+constexpr uint32_t kLess = ((~kBopA & kBopB) | (~(kBopA ^ kBopB) & kBopC)) & 0xFFu;   // (r, threshold, lt)
+constexpr uint32_t kEqual = (~(kBopA ^ kBopB) & kBopC) & 0xFFu;                      // (r, threshold, eq)
+constexpr uint32_t kPick = ((kBopA & kBopB) | (~kBopA & kBopC)) & 0xFFu;             // (select, b, c)
+
+template <uint32_t TT>
+__device__ __forceinline__ uint32_t op3s(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, TT);
+}
+
+// Draws the tails of the n listed sites of a tile and adds the decided sites
+// to the class masks.  x0: the tile's first (half-step, word) index.
+__device__ __forceinline__ void small_tails(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t n, uint32_t x0,
+                                            uint32_t t_first, uint64_t* masks) {
+    small_sync();
+    for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
+        const uint32_t v = w.entry[e];
+        const uint32_t l = v & 63u, b = v >> 6;
+        const uint32_t x = x0 + l;
+        const uint32_t hs = fdiv(x, a.div_n);
+        const uint32_t g = x - hs * a.n;
+        const U4 y = philox10_uvuv(stream, t_first + hs, 2u * kTagDynamics + 1u, 16u * g + (b >> 2), a.key0, a.key1);
+        const uint32_t lo = (b & 1u) ? y.x1 : y.x0, hi = (b & 1u) ? y.x3 : y.x2;
+        const uint32_t tail = (((b & 2u) ? hi : lo) ^ a.rng_xor) >> 8;
+        const uint32_t bit = 1u << (b & 31u);
+        uint32_t* m = reinterpret_cast<uint32_t*>(masks + (size_t)hs * 6u * a.n + g) + (b >> 5);
+        const uint32_t* q = reinterpret_cast<const uint32_t*>(&w.eq[0][l]) + (b >> 5);
+#pragma unroll
+        for (uint32_t k = 0; k < 6; ++k)
+            if ((q[128u * k] & bit) && tail < (a.T[k] & 0xFFFFFFu))
+                atomicOr(m + 2u * k * a.n, bit);
+    }
+    small_sync();
+}
+
+// The class masks of half-steps t_first .. t_first + count - 1 into masks
+// ([half-step][class][word]), by worker `me` of `workers`.
+__device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t me,
+                                           uint32_t workers, uint32_t t_first, uint32_t count, uint64_t* masks) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t total = count * a.n;
+    for (uint32_t x0 = 64u * me; x0 < total; x0 += 64u * workers) {
+        const uint32_t x = x0 + lane;
+        const bool active = x < total;
+        const uint32_t hs = active ? fdiv(x, a.div_n) : 0u;
+        const uint32_t g = active ? x - hs * a.n : 0u;
+        uint32_t P[8][2];
+#pragma unroll
+        for (uint32_t p = 0; p < 4; ++p) {
+            const U4 y = philox10_uvuv(stream, (t_first + hs) | (p << 30), 2u * kTagDynamics, g, a.key0, a.key1);
+            P[2 * p][0] = y.x0;
+            P[2 * p][1] = y.x1;
+            P[2 * p + 1][0] = y.x2;
+            P[2 * p + 1][1] = y.x3;
+        }
+        if (a.rng_xor) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                P[m][0] = ~P[m][0];
+                P[m][1] = ~P[m][1];
+            }
+        }
+        uint64_t open = 0;   // sites some class leaves to its tail
+        uint64_t* out = masks + (size_t)hs * 6u * a.n + g;
+#pragma unroll
+        for (uint32_t k = 0; k < 6; ++k) {
+            uint32_t lt[2] = {0u, 0u}, eq[2] = {~0u, ~0u};
+#pragma unroll
+            for (int m = 7; m >= 0; --m) {
+                const uint32_t S = 0u - ((a.T[k] >> (31 - m)) & 1u);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    lt[h] = op3s<kLess>(P[m][h], S, lt[h]);
+                    eq[h] = op3s<kEqual>(P[m][h], S, eq[h]);
+                }
+            }
+            const uint64_t e = (uint64_t)eq[0] | ((uint64_t)eq[1] << 32);
+            w.eq[k][lane] = e;
+            if (a.T[k] & 0xFFFFFFu)   // uniform; no tail is below a zero threshold tail
+                open |= e;
+            if (active)
+                out[k * a.n] = (uint64_t)lt[0] | ((uint64_t)lt[1] << 32);
+        }
+        if (!active)
+            open = 0;
+        uint32_t listed = 0;   // wavefront-uniform
+        for (;;) {
+            const uint64_t m = __ballot(open != 0);
+            if (m == 0)
+                break;
+            if (open != 0) {
+                const uint32_t e = listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                w.entry[e] = lane | ((uint32_t)__builtin_ctzll(open) << 6);
+                open &= open - 1;
+            }
+            listed += (uint32_t)__popcll(m);
+            if (listed >= 64u) {
+                small_tails(a, stream, w, listed, x0, t_first, masks);
+                listed = 0;
+            }
+        }
+        if (listed)
+            small_tails(a, stream, w, listed, x0, t_first, masks);
+    }
+}
+
+// A lane's neighbour fetches for one direction on lattices whose rows need not
+// be 32 or 64 sites: windows of the lattice's bit string, all indices fixed.
+struct Window {
+    uint32_t q0, q1, sh;        // neighbour row: bits sh .. of word q0, then q1
+    uint32_t w0, w1, wsh;       // row wrap of the shifted word
+    uint32_t side;              // the word before (after) this one
+    uint64_t wrap;              // sites whose neighbour is across the row's end
+};
+
+template <int WHICH>
+__device__ __forceinline__ Window make_window(const SmallArgs& a, uint32_t g) {
+    const uint32_t n = a.n, N = 64u * n, L = a.L;
+    auto at = [&](uint32_t off, uint32_t& q0, uint32_t& q1, uint32_t& sh) {
+        q0 = g + (off >> 6);
+        q0 = q0 >= n ? q0 - n : q0;
+        q1 = q0 + 1u == n ? 0u : q0 + 1u;
+        sh = off & 63u;
+    };
+    Window w;
+    if constexpr (WHICH == 0) {
+        at(N - L, w.q0, w.q1, w.sh);
+        at(L - 1u, w.w0, w.w1, w.wsh);
+        w.side = g == 0 ? n - 1u : g - 1u;
+        w.wrap = column_mask(g, L, a.div_L, 0u);
+    } else {
+        at(L, w.q0, w.q1, w.sh);
+        at(N + 1u - L, w.w0, w.w1, w.wsh);
+        w.side = g + 1u == n ? 0u : g + 1u;
+        w.wrap = column_mask(g, L, a.div_L, L - 1u);
+    }
+    return w;
+}
+
+__device__ __forceinline__ uint64_t window_bits(uint64_t lo, uint64_t hi, uint32_t sh) {
+    return (lo >> sh) | ((hi << 1) << (63u - sh));
+}
+
+// Neighbour words n1 (down / up) and n2 (left / right) of the word c of every
+// lane, lane l holding word l.  ROWS 64: a row per lane; 32: two rows per
+// lane, 16 lanes; 0: any, from the lattice in LDS (lat).
+template <int ROWS, int WHICH>
+__device__ __forceinline__ void small_neighbours(uint64_t c, const uint64_t* lat, const Window& w, uint64_t& n1,
+                                                 uint64_t& n2) {
+    const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
+    auto pack = [](uint32_t l, uint32_t h) { return (uint64_t)l | ((uint64_t)h << 32); };
+    if constexpr (ROWS == 64) {
+        if constexpr (WHICH == 0) {   // wave_ror:1, lane l takes lane l - 1 mod 64
+            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x13C, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x13C, 0xF, 0xF, true));
+            n2 = pack(__builtin_amdgcn_alignbit(lo, hi, 31), __builtin_amdgcn_alignbit(hi, lo, 31));
+        } else {                      // wave_rol:1
+            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x134, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x134, 0xF, 0xF, true));
+            n2 = pack(__builtin_amdgcn_alignbit(hi, lo, 1), __builtin_amdgcn_alignbit(lo, hi, 1));
+        }
+    } else if constexpr (ROWS == 32) {
+        if constexpr (WHICH == 0) {   // row_ror:1, lane l takes lane l - 1 mod 16
+            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x121, 0xF, 0xF, true), lo);
+            n2 = pack(__builtin_amdgcn_alignbit(lo, lo, 31), __builtin_amdgcn_alignbit(hi, hi, 31));
+        } else {                      // row_ror:15, lane l takes lane l + 1 mod 16
+            n1 = pack(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x12F, 0xF, 0xF, true));
+            n2 = pack(__builtin_amdgcn_alignbit(lo, lo, 1), __builtin_amdgcn_alignbit(hi, hi, 1));
+        }
+    } else {
+        const uint64_t side = lat[w.side];
+        n1 = window_bits(lat[w.q0], lat[w.q1], w.sh);
+        const uint64_t across = window_bits(lat[w.w0], lat[w.w1], w.wsh);
+        const uint64_t base = WHICH == 0 ? (c << 1) | (side >> 63) : (c >> 1) | (side << 63);
+        n2 = (base & ~w.wrap) | (across & w.wrap);
+    }
+}
+
+// The class masks of one half-step's word.
+struct Masks {
+    uint64_t m[6];
+};
+
+__device__ __forceinline__ Masks load_masks(const uint64_t* p, uint32_t n) {
+    Masks r;
+#pragma unroll
+    for (uint32_t k = 0; k < 6; ++k)
+        r.m[k] = p[k * n];
+    return r;
+}
+
+__device__ __forceinline__ uint64_t pick_class(const Masks& r, uint64_t c, uint64_t n1, uint64_t n2) {
+    uint32_t out[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t cc = (uint32_t)(c >> (32 * h)), a = (uint32_t)(n1 >> (32 * h)), b = (uint32_t)(n2 >> (32 * h));
+        const uint32_t one = a ^ b;   // exactly one J-neighbour is +1 (k = 1); else a tells k = 0 from k = 2
+        uint32_t m[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            m[k] = (uint32_t)(r.m[k] >> (32 * h));
+        const uint32_t down = op3s<kPick>(one, m[2], op3s<kPick>(a, m[4], m[0]));
+        const uint32_t up = op3s<kPick>(one, m[3], op3s<kPick>(a, m[5], m[1]));
+        out[h] = op3s<kPick>(cc, up, down);
+    }
+    return (uint64_t)out[0] | ((uint64_t)out[1] << 32);
+}
+
+// Half-steps 0 .. count - 1 of an epoch (A first) on the walker's words: sig
+// and tau are updated; every new word goes to hist[half-step][word] (ring: the
+// two-slot exchange buffer of walkers that keep no history).
+template <int ROWS, bool RING>
+__device__ __forceinline__ void small_walk(const SmallArgs& a, uint32_t count, const uint64_t* masks, uint64_t* hist,
+                                           const Window& wA, const Window& wB, uint64_t& sig, uint64_t& tau) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t n = a.n;
+    const uint32_t g = lane < n ? lane : 0u;
+    const uint64_t* p = masks + g;
+    Masks next = load_masks(p, n);
+    for (uint32_t i = 0; i < count; i += 2) {   // count is even
+        uint64_t n1, n2;
+        Masks cur = next;
+        p += 6u * n;
+        next = load_masks(p, n);
+        const uint64_t* lat = RING ? hist + 64 : (i == 0 ? nullptr : hist + (size_t)(i - 1u) * n);
+        if constexpr (ROWS == 0 && !RING)
+            lat = i == 0 ? hist - n : lat;
+        small_neighbours<ROWS, 0>(sig, lat, wA, n1, n2);
+        tau = pick_class(cur, sig, n1, n2);
+        uint64_t* to = RING ? hist : hist + (size_t)i * n;
+        if (!RING || ROWS == 0) {
+            if (lane < n)
+                to[lane] = tau;
+            if (ROWS == 0)
+                small_sync();
+        }
+        cur = next;
+        p += 6u * n;
+        if (i + 2u < count)
+            next = load_masks(p, n);
+        small_neighbours<ROWS, 1>(tau, to, wB, n1, n2);
+        sig = pick_class(cur, tau, n1, n2);
+        to = RING ? hist + 64 : hist + (size_t)(i + 1u) * n;
+        if (!RING || ROWS == 0) {
+            if (lane < n)
+                to[lane] = sig;
+            if (ROWS == 0)
+                small_sync();
+        }
+    }
+}
+
+// M, A, B of the steps of an epoch (first step index m0 of the run, `count`
+// half-steps in hist) that are recorded, by worker `me` of `workers`.
+__device__ __forceinline__ void small_records(const SmallArgs& a, uint32_t me, uint32_t workers, uint32_t m0,
+                                              uint32_t count, const uint64_t* hist) {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t s = me; 2u * s < count; s += workers) {
+        const uint32_t m = m0 + s + 1u;   // steps done after it
+        if (m % a.obs_every != 0)
+            continue;
+        uint32_t pc = 0, dpair = 0, dself = 0;
+        if (lane < a.n) {
+            const uint64_t* tau = hist + (size_t)(2u * s) * a.n;
+            const uint64_t x = tau[a.n + lane];
+            uint64_t t, up, right;
+            gather_bits<1>(tau, a.L, a.n, a.div_L, lane, t, up, right);
+            pc = (uint32_t)__popcll(x);
+            dpair = (uint32_t)(__popcll(x ^ up) + __popcll(x ^ right));
+            dself = (uint32_t)__popcll(x ^ t);
+        }
+        const uint32_t v0 = wave_sum_dpp(pc), v1 = wave_sum_dpp(dpair), v2 = wave_sum_dpp(dself);
+        if (lane == 0) {
+            const int64_t sites = 64 * (int64_t)a.n;
+            int64_t* o = a.obs + 3u * (size_t)(m / a.obs_every - 1u);
+            o[0] = 2 * (int64_t)v0 - sites;
+            o[1] = 2 * sites - 2 * (int64_t)v1;
+            o[2] = sites - 2 * (int64_t)v2;
+        }
+    }
+}
+
+// PAIR: workgroup b is coupled pair a.pairs[b] (top chain from all +1 on
+// wavefront 0, bottom chain from all -1 on wavefront 1); else the one chain
+// (a.sigma, a.tau) on wavefront 0.  Every other wavefront is a worker.
+template <int ROWS, bool PAIR>
+__global__ __launch_bounds__(1024) void k_small(SmallArgs a) {
+    extern __shared__ uint64_t smem[];
+    constexpr uint32_t kWalkers = PAIR ? 2u : 1u;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t n = a.n, H = a.H;
+    const uint32_t workers = (blockDim.x >> 6) - kWalkers;
+    uint64_t* masks = smem;                                   // [2][H][6][n]
+    // one chain: [n start][2][H][n] new words; pairs: a two-slot buffer per walker
+    uint64_t* hist = masks + (size_t)2 * H * 6u * n;
+    uint64_t* after = hist + (PAIR ? 2u * 128u : (2u * H + 1u) * n);
+    Worker* work = reinterpret_cast<Worker*>(after);
+    const uint32_t pair = PAIR ? a.pairs[blockIdx.x] : 0u;
+    const uint32_t stream = a.stream + pair;
+    const bool walker = wave < kWalkers;
+    Worker& w = work[walker ? 0u : wave - kWalkers];
+    const uint32_t me = wave - kWalkers;
+    const bool record = !PAIR && a.obs != nullptr;
+
+    uint64_t sig = 0, tau = 0;
+    Window wA, wB;
+    if (walker) {
+        const uint32_t g = lane < n ? lane : 0u;
+        if constexpr (ROWS == 0) {
+            wA = make_window<0>(a, g);
+            wB = make_window<1>(a, g);
+        }
+        if constexpr (PAIR) {
+            sig = wave == 0 ? ~0ull : 0ull;
+            hist[128u * wave + 64u + lane] = sig;
+        } else {
+            sig = a.int8_io ? load_bits64_i8<false>(static_cast<const int8_t*>(a.sigma) + 64u * g)
+                            : static_cast<const uint64_t*>(a.sigma)[g];
+            if (lane < n)
+                hist[lane] = sig;
+        }
+    }
+    // epoch e: half-steps e H .. (its masks in slot e & 1, its words in slot e & 1)
+    const uint32_t total = a.n_half;
+    const uint32_t epochs = (total + H - 1u) / H;
+    for (uint32_t e = 0; e <= epochs + (record ? 1u : 0u); ++e) {
+        // workers: masks of epoch e, records of epoch e - 2; walkers: epoch e - 1
+        if (walker) {
+            if (e >= 1u && e <= epochs) {
+                const uint32_t x0 = (e - 1u) * H;
+                const uint32_t count = total - x0 < H ? total - x0 : H;
+                const uint64_t* from = masks + (size_t)((e - 1u) & 1u) * H * 6u * n;
+                if constexpr (PAIR) {
+                    small_walk<ROWS, true>(a, count, from, hist + 128u * wave, wA, wB, sig, tau);
+                } else {
+                    // the word before a slot is the last one of the other slot,
+                    // or for slot 0 its copy in front
+                    uint64_t* to = hist + n + (size_t)((e - 1u) & 1u) * H * n;
+                    if (ROWS == 0 && e > 1u && ((e - 1u) & 1u) == 0) {
+                        if (lane < n)
+                            hist[lane] = sig;
+                        small_sync();
+                    }
+                    small_walk<ROWS, false>(a, count, from, to, wA, wB, sig, tau);
+                }
+            }
+        } else {
+            if (e < epochs) {
+                const uint32_t x0 = e * H;
+                small_draw(a, stream, w, me, workers, a.t0 + x0, total - x0 < H ? total - x0 : H,
+                           masks + (size_t)(e & 1u) * H * 6u * n);
+            }
+            if (record && e >= 2u) {
+                const uint32_t x0 = (e - 2u) * H;
+                const uint32_t done = workers - 1u - me;   // the last worker has the fewest tiles
+                small_records(a, done, workers, x0 / 2u, total - x0 < H ? total - x0 : H,
+                              hist + n + (size_t)((e - 2u) & 1u) * H * n);
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (PAIR) {
+        if (walker)
+            hist[128u * wave + lane] = sig;
+        __syncthreads();
+        if (wave == 0) {
+            const bool differs = lane < n && hist[lane] != hist[128u + lane];
+            if (lane < n)
+                reinterpret_cast<uint64_t*>(a.samples)[(size_t)pair * n + lane] = sig;
+            const uint64_t any = __ballot(differs);
+            if (lane == 0)
+                a.equal[blockIdx.x] = any ? 0u : 1u;
+        }
+    } else if (wave == 0 && lane < n) {
+        if (a.int8_io) {
+            store_bits64_i8<false>(static_cast<int8_t*>(a.sigma) + 64u * lane, sig);
+            store_bits64_i8<false>(static_cast<int8_t*>(a.tau) + 64u * lane, tau);
+        } else {
+            static_cast<uint64_t*>(a.sigma)[lane] = sig;
+            static_cast<uint64_t*>(a.tau)[lane] = tau;
+        }
+    }
+}
+
+template <int ROWS, bool PAIR>
+hipError_t launch_small_t(const SmallArgs& a, uint32_t blocks, uint32_t threads, size_t lds, hipStream_t st) {
+    if (lds > 65536u) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_small<ROWS, PAIR>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL((k_small<ROWS, PAIR>), dim3(blocks), dim3(threads), lds, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool small_supported(int32_t L) { return L >= 8 && L <= 64 && L % 8 == 0; }
+
+// Wavefronts and half-steps per epoch.  A tile of 64 (half-step, word) pairs
+// is one worker's unit of work, so an epoch holds one per worker: 14 half-steps
+// of a 64^2 lattice, 60 of a 32^2 one on 16 wavefronts; when there are more
+// workgroups than CUs two share a CU (8 wavefronts and half the LDS each).
+// Lattices of few words stop at kMaxEpoch, where the walker is the slower side.
+hipError_t launch_small(SmallArgs a, uint32_t blocks, bool pair, uint32_t n_cu, size_t max_lds, hipStream_t st) {
+    constexpr uint32_t kMaxEpoch = 64;
+    const bool share = blocks > n_cu;
+    const uint32_t waves = share ? 8u : 16u;
+    const uint32_t walkers = pair ? 2u : 1u;
+    const size_t budget = share ? max_lds / 2 : max_lds;
+    const size_t scratch = sizeof(Worker) * (waves - walkers);
+    auto lds_of = [&](uint32_t H) {
+        const size_t hist = pair ? 2u * 128u : (size_t)(2u * H + 1u) * a.n;
+        return sizeof(uint64_t) * ((size_t)2 * H * 6u * a.n + hist) + scratch;
+    };
+    uint32_t H = 64u * (waves - walkers) / a.n;
+    H = H > kMaxEpoch ? kMaxEpoch : H;
+    H = H > a.n_half ? a.n_half : H;
+    H = H < 2u ? 2u : H & ~1u;
+    while (H > 2u && lds_of(H) > budget)
+        H -= 2u;
+    a.H = H;
+    const size_t lds = lds_of(H);
+    if (lds > max_lds)
+        return hipErrorInvalidValue;
+    const uint32_t threads = 64u * waves;
+#define SD_SMALL(ROWS)                                                          \
+    return pair ? launch_small_t<ROWS, true>(a, blocks, threads, lds, st)      \
+                : launch_small_t<ROWS, false>(a, blocks, threads, lds, st)
+    if (a.L == 64u)
+        SD_SMALL(64);
+    if (a.L == 32u)
+        SD_SMALL(32);
+    SD_SMALL(0);
+#undef SD_SMALL
+}
+
+}  // namespace sd

@@ -29,11 +29,14 @@ struct PwScratch {
         (void)hipFree(equal);
         (void)hipFree(counter);
     }
-    hipError_t alloc(uint32_t n) {
-        hipError_t e = hipMalloc(&descs, sizeof(ChainDesc) * 2 * (size_t)n);
-        if (e == hipSuccess) e = hipMalloc(&order, sizeof(uint32_t) * 2 * (size_t)n);
-        if (e == hipSuccess) e = hipMalloc(&pairs, sizeof(uint32_t) * (size_t)n);
+    // small: pairs run in the small-lattice kernel, which needs no chain queue
+    hipError_t alloc(uint32_t n, bool small) {
+        hipError_t e = hipMalloc(&pairs, sizeof(uint32_t) * (size_t)n);
         if (e == hipSuccess) e = hipMalloc(&equal, sizeof(uint32_t) * (size_t)n);
+        if (small)
+            return e;
+        if (e == hipSuccess) e = hipMalloc(&descs, sizeof(ChainDesc) * 2 * (size_t)n);
+        if (e == hipSuccess) e = hipMalloc(&order, sizeof(uint32_t) * 2 * (size_t)n);
         if (e == hipSuccess) e = hipMalloc(&counter, sizeof(uint32_t));
         return e;
     }
@@ -72,15 +75,18 @@ sd_status sd_propp_wilson(void* samples, void* work, int32_t n_samples, int32_t 
     if (n == 0)
         return SD_OK;
 
-    int device = 0, max_lds = 0, n_cu = 1;
-    hipError_t e = hipGetDevice(&device);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device);
+    uint32_t n_cu = 1;
+    size_t max_lds = 0;
+    hipError_t e = device_limits(&n_cu, &max_lds);
     if (e != hipSuccess)
         return hip_fail(e, "sd_propp_wilson");
+    // At most 64 words: a workgroup per pair draws the uniforms of both chains
+    // once, ahead of them (k_small); larger lattices run the two chains as two
+    // queue entries of the batched kernel.
+    const bool small = small_supported(L);
     const uint32_t threads = chain_threads(words);
     const size_t lds = batch_lds_bytes(words, threads);
-    if (lds > (size_t)max_lds)
+    if (lds > max_lds)
         return fail(SD_EUNSUPPORTED, "sd_propp_wilson: an L = %d lattice pair does not fit one workgroup's LDS", L);
 
     ChainDesc proto;
@@ -95,7 +101,7 @@ sd_status sd_propp_wilson(void* samples, void* work, int32_t n_samples, int32_t 
     if (e != hipSuccess)
         return hip_fail(e, "sd_propp_wilson");
     PwScratch sc;
-    e = sc.alloc(n);
+    e = sc.alloc(n, small);
     if (e != hipSuccess)
         return hip_fail(e, "sd_propp_wilson: scratch");
 
@@ -108,47 +114,56 @@ sd_status sd_propp_wilson(void* samples, void* work, int32_t n_samples, int32_t 
     std::vector<uint32_t> order, equal;
     for (uint64_t T = T0; T <= T_max && !open.empty(); T *= 2) {
         const uint32_t R = (uint32_t)open.size();
-        descs.assign(2 * (size_t)R, proto);
-        order.resize(2 * (size_t)R);
-        for (uint32_t i = 0; i < R; ++i) {
-            const uint32_t p = open[i];
-            for (uint32_t b = 0; b < 2; ++b) {   // b = 0: top chain, 1: bottom chain
-                ChainDesc& d = descs[2 * i + b];
-                d.stream = stream0 + p;
-                d.sig_offset = (4 * (uint64_t)p + 2 * b) * nb;
-                d.tau_offset = d.sig_offset + nb;
-                order[2 * i + b] = 2 * i + b;
+        e = hipMemcpyAsync(sc.pairs, open.data(), sizeof(uint32_t) * R, hipMemcpyHostToDevice, st);
+        if (small) {
+            SmallArgs a = small_args(L, J, q, seed, stream0, step_end - T, (uint32_t)T, 0u);
+            a.pairs = sc.pairs;
+            a.samples = static_cast<uint8_t*>(samples);
+            a.equal = sc.equal;
+            if (e == hipSuccess)
+                e = launch_small(a, R, true, n_cu, max_lds, st);
+        } else {
+            descs.assign(2 * (size_t)R, proto);
+            order.resize(2 * (size_t)R);
+            for (uint32_t i = 0; i < R; ++i) {
+                const uint32_t p = open[i];
+                for (uint32_t b = 0; b < 2; ++b) {   // b = 0: top chain, 1: bottom chain
+                    ChainDesc& d = descs[2 * i + b];
+                    d.stream = stream0 + p;
+                    d.sig_offset = (4 * (uint64_t)p + 2 * b) * nb;
+                    d.tau_offset = d.sig_offset + nb;
+                    order[2 * i + b] = 2 * i + b;
+                }
             }
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(sc.descs, descs.data(), sizeof(ChainDesc) * descs.size(), hipMemcpyHostToDevice, st);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(sc.order, order.data(), sizeof(uint32_t) * order.size(), hipMemcpyHostToDevice, st);
+            if (e == hipSuccess) e = launch_pw_reset(lat, sc.pairs, R, words, st);
+            if (e == hipSuccess) e = launch_zero_u32(sc.counter, 1, st);
+            if (e == hipSuccess) {
+                BatchArgs a;
+                std::memset(&a, 0, sizeof a);
+                a.chains = sc.descs;
+                a.order = sc.order;
+                a.n_chains = 2 * R;
+                a.counter = sc.counter;
+                a.lattices = lat;
+                a.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
+                a.key1 = (uint32_t)(seed >> 32);
+                a.step0 = (uint32_t)(step_end - T);
+                a.k_steps = (uint32_t)T;
+                a.obs_every = 1;
+                a.max_words = words;
+                a.bits = L % 64 != 0 ? 1u : 0u;
+                a.paired = proto.paired;
+                const uint32_t blocks =
+                    std::max<uint32_t>(1, std::min<uint64_t>(2 * (uint64_t)R, (uint64_t)per_cu * (uint64_t)n_cu));
+                e = launch_batch_chains(a, blocks, threads, st);
+            }
+            if (e == hipSuccess)
+                e = launch_pw_finish(lat, sc.pairs, R, words, static_cast<uint8_t*>(samples), sc.equal, st);
         }
-        e = hipMemcpyAsync(sc.descs, descs.data(), sizeof(ChainDesc) * descs.size(), hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(sc.order, order.data(), sizeof(uint32_t) * order.size(), hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(sc.pairs, open.data(), sizeof(uint32_t) * R, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = launch_pw_reset(lat, sc.pairs, R, words, st);
-        if (e == hipSuccess) e = launch_zero_u32(sc.counter, 1, st);
-        if (e == hipSuccess) {
-            BatchArgs a;
-            std::memset(&a, 0, sizeof a);
-            a.chains = sc.descs;
-            a.order = sc.order;
-            a.n_chains = 2 * R;
-            a.counter = sc.counter;
-            a.lattices = lat;
-            a.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
-            a.key1 = (uint32_t)(seed >> 32);
-            a.step0 = (uint32_t)(step_end - T);
-            a.k_steps = (uint32_t)T;
-            a.obs_every = 1;
-            a.max_words = words;
-            a.bits = L % 64 != 0 ? 1u : 0u;
-            a.paired = proto.paired;
-            const uint32_t blocks =
-                std::max<uint32_t>(1, std::min<uint64_t>(2 * (uint64_t)R, (uint64_t)per_cu * (uint64_t)n_cu));
-            e = launch_batch_chains(a, blocks, threads, st);
-        }
-        if (e == hipSuccess)
-            e = launch_pw_finish(lat, sc.pairs, R, words, static_cast<uint8_t*>(samples), sc.equal, st);
         equal.resize(R);
         if (e == hipSuccess)
             e = hipMemcpyAsync(equal.data(), sc.equal, sizeof(uint32_t) * R, hipMemcpyDeviceToHost, st);

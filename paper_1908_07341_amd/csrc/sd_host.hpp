@@ -7,6 +7,7 @@
 
 #include "shaken.h"
 #include "sd_kernels.hpp"
+#include "sd_small.hpp"
 
 namespace sd {
 
@@ -28,6 +29,13 @@ sd_status init_params(const char* name, int32_t kind, double p_up, uint64_t seed
 // alignment to the word size).
 sd_status check_lattice(const void* p, int32_t L, int32_t layout, const char* name);
 DrawParams dynamics_params(double J, double q, uint64_t seed, uint32_t stream, uint32_t t, uint32_t flags);
+
+// The current device's CUs and LDS bytes a workgroup may have.
+hipError_t device_limits(uint32_t* n_cu, size_t* max_lds);
+// Arguments of the small-lattice kernel for k_steps steps from step0; the
+// caller adds the lattices or pairs.
+SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stream, uint64_t step0, uint32_t k_steps,
+                     uint32_t flags);
 
 // Device scratch of kPartialsWords int64 for per-workgroup partial sums, one
 // per (device, stream), allocated on first use and kept for the process.

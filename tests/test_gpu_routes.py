@@ -106,3 +106,61 @@ def test_records_of_one_word_tiles_under_capture(oracle, L, layout):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(obs.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("L", [8, 16, 24, 32, 40, 48, 56, 64])
+@pytest.mark.parametrize("J,q", [(0.4, 0.6), (0.0, 0.0), (0.5, 1.0), (-0.7, 0.3), (9.0, 20.0)])
+def test_small_lattices_drawn_ahead(oracle, L, J, q):
+    # every side of the small-lattice kernel: one row, two rows and other
+    # fractions of a row per word; runs of one step, below, at and past the
+    # half-steps drawn ahead at a time (14 at 64^2, 64 at 8^2), several rounds
+    # with a ragged end; thresholds with equal top bytes (0, 0), with no tail
+    # (h = 0) and at the ends of their range.  The grid kernels are the general
+    # path; the shortest and a middle run also go through the oracle.
+    print(f"small L={L} J={J} q={q}", flush=True)
+    start = inputs.random_lattice(L, 3 * L)
+    for layout in (sd.SD_P64, sd.SD_I8, sd.SD_P32):
+        if layout == sd.SD_P32 and L % 32:
+            continue
+        host = start if layout == sd.SD_I8 else inputs.pack_bits(start)
+        host = torch.from_numpy(host.reshape(-1).copy()).cuda()
+        for k, every, flags in [(1, 1, 0), (6, 1, 0), (7, 2, 0), (8, 1, sd.SD_FLAG_COMPLEMENT_RNG), (32, 3, 0), (33, 1, 0),
+                                (150, 7, 0), (5, 0, 0)]:
+            got = []
+            for f in (flags, flags | sd.SD_FLAG_GLOBAL_KERNELS):
+                # int8 lattices at an odd address, words at their own alignment
+                pad = 1 if layout == sd.SD_I8 else 8
+                buf = torch.full((2, host.numel() + 64), 3, dtype=host.dtype, device="cuda")
+                sigma, tau = buf[0, pad:pad + host.numel()], buf[1, pad:pad + host.numel()]
+                sigma.copy_(host)
+                obs = torch.full((k // every if every else 0, 3), -1, dtype=torch.int64, device="cuda")
+                sd.sd_run(sigma, tau, L, layout, J, q, SEED, 4, 11, k, obs if every else None, every, f)
+                got.append((buf, obs))
+            assert torch.equal(got[0][0], got[1][0]), (layout, k)
+            assert torch.equal(got[0][1], got[1][1]), (layout, k)
+            if k in (1, 33):
+                sig, tau, rec = oracle.run(start, J, q, SEED, 4, 11, k, obs_every=every)
+                flat = got[0][0][0, pad:pad + host.numel()].cpu().numpy()
+                have = flat.reshape(L, L) if layout == sd.SD_I8 else inputs.unpack_bits(flat, L)
+                assert np.array_equal(have, sig) and np.array_equal(got[0][1].cpu().numpy(), rec)
+
+
+@pytest.mark.parametrize("L", [8, 32, 48, 64])
+def test_exact_samples_shared_and_alone(oracle, L):
+    # more pairs than CUs (two workgroups of 8 wavefronts share a CU) against
+    # the same pairs alone (16 wavefronts), and one pair against the oracle;
+    # at T_max = 16 most pairs stay open
+    J, q, n = 0.3, 0.8, 300
+    print(f"exact samples L={L}", flush=True)
+    nb = sd.sd_lattice_bytes(L, sd.SD_P64)
+    for T0, T_max in ((16, 4096), (1, 16)):
+        out = torch.full((n, nb), 9, dtype=torch.uint8, device="cuda")
+        work = torch.empty(4 * n * nb, dtype=torch.uint8, device="cuda")
+        T = sd.sd_propp_wilson(out, work, n, L, J, q, SEED, 50, 1 << 20, T0, T_max)
+        one = torch.full((7, nb), 9, dtype=torch.uint8, device="cuda")
+        T1 = sd.sd_propp_wilson(one, work, 7, L, J, q, SEED, 60, 1 << 20, T0, T_max)
+        assert T[10:17] == T1
+        assert torch.equal(out[10:17], one)
+        want, t = oracle.propp_wilson(L, J, q, SEED, 60, 1 << 20, T0, T_max)
+        assert t == T1[0]
+        assert np.array_equal(inputs.unpack_bits(one[0].cpu().numpy(), L), want)
