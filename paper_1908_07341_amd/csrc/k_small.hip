@@ -76,46 +76,70 @@ __device__ __forceinline__ uint32_t op3s(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, TT);
 }
 
+// Words of a lattice: known at compile time for the row forms, so that mask and
+// history addresses are immediates.
+template <int ROWS>
+__device__ __forceinline__ uint32_t small_words(const SmallArgs& a) {
+    return ROWS == 64 ? 64u : ROWS == 32 ? 16u : a.n;
+}
+
+// Half-step of index x = (half-step, word) of an epoch.
+template <int ROWS>
+__device__ __forceinline__ uint32_t small_half(const SmallArgs& a, uint32_t x) {
+    return ROWS == 64 ? x >> 6 : ROWS == 32 ? x >> 4 : fdiv(x, a.div_n);
+}
+
 // Draws the tails of the n listed sites of a tile and adds the decided sites
 // to the class masks.  x0: the tile's first (half-step, word) index.
+template <int ROWS>
 __device__ __forceinline__ void small_tails(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t n, uint32_t x0,
                                             uint32_t t_first, uint64_t* masks) {
+    const uint32_t nw = small_words<ROWS>(a);
     small_sync();
     for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
         const uint32_t v = w.entry[e];
         const uint32_t l = v & 63u, b = v >> 6;
         const uint32_t x = x0 + l;
-        const uint32_t hs = fdiv(x, a.div_n);
-        const uint32_t g = x - hs * a.n;
+        const uint32_t hs = small_half<ROWS>(a, x);
+        const uint32_t g = x - hs * nw;
         const U4 y = philox10_uvuv(stream, t_first + hs, 2u * kTagDynamics + 1u, 16u * g + (b >> 2), a.key0, a.key1);
         const uint32_t lo = (b & 1u) ? y.x1 : y.x0, hi = (b & 1u) ? y.x3 : y.x2;
         const uint32_t tail = (((b & 2u) ? hi : lo) ^ a.rng_xor) >> 8;
         const uint32_t bit = 1u << (b & 31u);
-        uint32_t* m = reinterpret_cast<uint32_t*>(masks + (size_t)hs * 6u * a.n + g) + (b >> 5);
+        uint32_t* m = reinterpret_cast<uint32_t*>(masks + (hs * 6u * nw + g)) + (b >> 5);
         const uint32_t* q = reinterpret_cast<const uint32_t*>(&w.eq[0][l]) + (b >> 5);
+        uint32_t open[6];
 #pragma unroll
         for (uint32_t k = 0; k < 6; ++k)
-            if ((q[128u * k] & bit) && tail < (a.T[k] & 0xFFFFFFu))
-                atomicOr(m + 2u * k * a.n, bit);
+            open[k] = q[128u * k] & bit;
+#pragma unroll
+        for (uint32_t k = 0; k < 6; ++k)   // or-ing nothing costs less than a branch per class
+            atomicOr(m + 2u * k * nw, tail < (a.T[k] & 0xFFFFFFu) ? open[k] : 0u);
     }
     small_sync();
 }
 
 // The class masks of half-steps t_first .. t_first + count - 1 into masks
 // ([half-step][class][word]), by worker `me` of `workers`.
+template <int ROWS>
 __device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t me,
                                            uint32_t workers, uint32_t t_first, uint32_t count, uint64_t* masks) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t total = count * a.n;
+    const uint32_t nw = small_words<ROWS>(a);
+    const uint32_t total = count * nw;
     for (uint32_t x0 = 64u * me; x0 < total; x0 += 64u * workers) {
         const uint32_t x = x0 + lane;
         const bool active = x < total;
-        const uint32_t hs = active ? fdiv(x, a.div_n) : 0u;
-        const uint32_t g = active ? x - hs * a.n : 0u;
+        const uint32_t hs = active ? small_half<ROWS>(a, x) : 0u;
+        const uint32_t g = active ? x - hs * nw : 0u;
         uint32_t P[8][2];
 #pragma unroll
         for (uint32_t p = 0; p < 4; ++p) {
-            const U4 y = philox10_uvuv(stream, (t_first + hs) | (p << 30), 2u * kTagDynamics, g, a.key0, a.key1);
+            // a 64-word tile is one half-step of a 64^2 lattice: its index is uniform
+            const U4 y = ROWS == 64 ? philox10_uuuv(stream, (t_first + (x0 >> 6)) | (p << 30), 2u * kTagDynamics, lane,
+                                                    a.key0, a.key1)
+                                    : philox10_uvuv(stream, (t_first + hs) | (p << 30), 2u * kTagDynamics, g, a.key0,
+                                                    a.key1);
             P[2 * p][0] = y.x0;
             P[2 * p][1] = y.x1;
             P[2 * p + 1][0] = y.x2;
@@ -129,13 +153,17 @@ __device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, 
             }
         }
         uint64_t open = 0;   // sites some class leaves to its tail
-        uint64_t* out = masks + (size_t)hs * 6u * a.n + g;
+        uint64_t* out = masks + (hs * 6u * nw + g);
 #pragma unroll
         for (uint32_t k = 0; k < 6; ++k) {
             uint32_t lt[2] = {0u, 0u}, eq[2] = {~0u, ~0u};
+            // the 48 threshold bits are formed where they are used, on the
+            // scalar unit: kept across the tile they would not fit its registers
+            uint32_t T = a.T[k];
+            asm volatile("" : "+s"(T));
 #pragma unroll
             for (int m = 7; m >= 0; --m) {
-                const uint32_t S = 0u - ((a.T[k] >> (31 - m)) & 1u);
+                const uint32_t S = 0u - ((T >> (31 - m)) & 1u);
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     lt[h] = op3s<kLess>(P[m][h], S, lt[h]);
@@ -144,10 +172,10 @@ __device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, 
             }
             const uint64_t e = (uint64_t)eq[0] | ((uint64_t)eq[1] << 32);
             w.eq[k][lane] = e;
-            if (a.T[k] & 0xFFFFFFu)   // uniform; no tail is below a zero threshold tail
+            if (T & 0xFFFFFFu)   // uniform; no tail is below a zero threshold tail
                 open |= e;
             if (active)
-                out[k * a.n] = (uint64_t)lt[0] | ((uint64_t)lt[1] << 32);
+                out[k * nw] = (uint64_t)lt[0] | ((uint64_t)lt[1] << 32);
         }
         if (!active)
             open = 0;
@@ -164,12 +192,12 @@ __device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, 
             }
             listed += (uint32_t)__popcll(m);
             if (listed >= 64u) {
-                small_tails(a, stream, w, listed, x0, t_first, masks);
+                small_tails<ROWS>(a, stream, w, listed, x0, t_first, masks);
                 listed = 0;
             }
         }
         if (listed)
-            small_tails(a, stream, w, listed, x0, t_first, masks);
+            small_tails<ROWS>(a, stream, w, listed, x0, t_first, masks);
     }
 }
 
@@ -250,11 +278,13 @@ struct Masks {
     uint64_t m[6];
 };
 
-__device__ __forceinline__ Masks load_masks(const uint64_t* p, uint32_t n) {
+template <int ROWS>
+__device__ __forceinline__ Masks load_masks(const uint64_t* p, const SmallArgs& a) {
+    const uint32_t nw = small_words<ROWS>(a);
     Masks r;
 #pragma unroll
     for (uint32_t k = 0; k < 6; ++k)
-        r.m[k] = p[k * n];
+        r.m[k] = p[k * nw];
     return r;
 }
 
@@ -275,46 +305,44 @@ __device__ __forceinline__ uint64_t pick_class(const Masks& r, uint64_t c, uint6
     return (uint64_t)out[0] | ((uint64_t)out[1] << 32);
 }
 
-// Half-steps 0 .. count - 1 of an epoch (A first) on the walker's words: sig
-// and tau are updated; every new word goes to hist[half-step][word] (ring: the
-// two-slot exchange buffer of walkers that keep no history).
-template <int ROWS, bool RING>
+// Half-steps 0 .. count - 1 of an epoch (A first, count even) on the walker's
+// words, which update sig and tau.  KEEP: every new word goes to
+// hist[half-step][word], from which the records are taken, and the lattice
+// before the epoch lies in front of hist; otherwise hist is a two-slot buffer
+// (tau, sigma) that only the window form reads.  The masks of a half-step are
+// loaded one half-step ahead (the loads past the epoch's last one read other
+// parts of the workgroup's LDS and are not used).
+template <int ROWS, bool KEEP>
 __device__ __forceinline__ void small_walk(const SmallArgs& a, uint32_t count, const uint64_t* masks, uint64_t* hist,
-                                           const Window& wA, const Window& wB, uint64_t& sig, uint64_t& tau) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t n = a.n;
-    const uint32_t g = lane < n ? lane : 0u;
-    const uint64_t* p = masks + g;
-    Masks next = load_masks(p, n);
-    for (uint32_t i = 0; i < count; i += 2) {   // count is even
+                                           uint32_t slot, const Window& wA, const Window& wB, uint64_t& sig,
+                                           uint64_t& tau) {
+    const uint32_t nw = small_words<ROWS>(a);
+    const uint64_t* p = masks + slot;
+    uint64_t* h = hist + slot;
+    const uint64_t* before = KEEP ? hist - nw : hist + 64;   // sigma for the window form
+    Masks ma = load_masks<ROWS>(p, a);
+    for (uint32_t i = 0; i < count; i += 2) {
         uint64_t n1, n2;
-        Masks cur = next;
-        p += 6u * n;
-        next = load_masks(p, n);
-        const uint64_t* lat = RING ? hist + 64 : (i == 0 ? nullptr : hist + (size_t)(i - 1u) * n);
-        if constexpr (ROWS == 0 && !RING)
-            lat = i == 0 ? hist - n : lat;
-        small_neighbours<ROWS, 0>(sig, lat, wA, n1, n2);
-        tau = pick_class(cur, sig, n1, n2);
-        uint64_t* to = RING ? hist : hist + (size_t)i * n;
-        if (!RING || ROWS == 0) {
-            if (lane < n)
-                to[lane] = tau;
-            if (ROWS == 0)
-                small_sync();
-        }
-        cur = next;
-        p += 6u * n;
-        if (i + 2u < count)
-            next = load_masks(p, n);
-        small_neighbours<ROWS, 1>(tau, to, wB, n1, n2);
-        sig = pick_class(cur, tau, n1, n2);
-        to = RING ? hist + 64 : hist + (size_t)(i + 1u) * n;
-        if (!RING || ROWS == 0) {
-            if (lane < n)
-                to[lane] = sig;
-            if (ROWS == 0)
-                small_sync();
+        const Masks mb = load_masks<ROWS>(p + 6u * nw, a);
+        small_neighbours<ROWS, 0>(sig, before, wA, n1, n2);
+        tau = pick_class(ma, sig, n1, n2);
+        if (KEEP || ROWS == 0)
+            h[0] = tau;
+        if (ROWS == 0)
+            small_sync();
+        p += 12u * nw;
+        ma = load_masks<ROWS>(p, a);
+        small_neighbours<ROWS, 1>(tau, KEEP ? h - slot : hist, wB, n1, n2);
+        sig = pick_class(mb, tau, n1, n2);
+        if (KEEP)
+            h[nw] = sig;
+        else if (ROWS == 0)
+            h[64] = sig;
+        if (ROWS == 0)
+            small_sync();
+        if (KEEP) {
+            before = h - slot + nw;
+            h += 2u * nw;
         }
     }
 }
@@ -358,37 +386,37 @@ __global__ __launch_bounds__(1024) void k_small(SmallArgs a) {
     constexpr uint32_t kWalkers = PAIR ? 2u : 1u;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t n = a.n, H = a.H;
+    const uint32_t n = small_words<ROWS>(a), H = a.H;
     const uint32_t workers = (blockDim.x >> 6) - kWalkers;
     uint64_t* masks = smem;                                   // [2][H][6][n]
-    // one chain: [n start][2][H][n] new words; pairs: a two-slot buffer per walker
+    // one chain with records: [n start][2][H][n] new words; otherwise a two-slot
+    // buffer per walker
+    const bool record = !PAIR && a.obs != nullptr;
     uint64_t* hist = masks + (size_t)2 * H * 6u * n;
-    uint64_t* after = hist + (PAIR ? 2u * 128u : (2u * H + 1u) * n);
+    uint64_t* after = hist + (record ? (2u * H + 1u) * n : kWalkers * 128u);
     Worker* work = reinterpret_cast<Worker*>(after);
     const uint32_t pair = PAIR ? a.pairs[blockIdx.x] : 0u;
     const uint32_t stream = a.stream + pair;
     const bool walker = wave < kWalkers;
     Worker& w = work[walker ? 0u : wave - kWalkers];
     const uint32_t me = wave - kWalkers;
-    const bool record = !PAIR && a.obs != nullptr;
+    // the walker's word; lanes past the lattice's words repeat others (the row
+    // form of 32^2 four times over, so that its row shifts stay within them)
+    const uint32_t slot = ROWS == 32 ? lane & 15u : lane < n ? lane : 0u;
 
     uint64_t sig = 0, tau = 0;
     Window wA, wB;
     if (walker) {
-        const uint32_t g = lane < n ? lane : 0u;
         if constexpr (ROWS == 0) {
-            wA = make_window<0>(a, g);
-            wB = make_window<1>(a, g);
+            wA = make_window<0>(a, slot);
+            wB = make_window<1>(a, slot);
         }
-        if constexpr (PAIR) {
+        if constexpr (PAIR)
             sig = wave == 0 ? ~0ull : 0ull;
-            hist[128u * wave + 64u + lane] = sig;
-        } else {
-            sig = a.int8_io ? load_bits64_i8<false>(static_cast<const int8_t*>(a.sigma) + 64u * g)
-                            : static_cast<const uint64_t*>(a.sigma)[g];
-            if (lane < n)
-                hist[lane] = sig;
-        }
+        else
+            sig = a.int8_io ? load_bits64_i8<false>(static_cast<const int8_t*>(a.sigma) + 64u * slot)
+                            : static_cast<const uint64_t*>(a.sigma)[slot];
+        hist[record ? slot : 128u * wave + 64u + slot] = sig;
     }
     // epoch e: half-steps e H .. (its masks in slot e & 1, its words in slot e & 1)
     const uint32_t total = a.n_half;
@@ -400,24 +428,23 @@ __global__ __launch_bounds__(1024) void k_small(SmallArgs a) {
                 const uint32_t x0 = (e - 1u) * H;
                 const uint32_t count = total - x0 < H ? total - x0 : H;
                 const uint64_t* from = masks + (size_t)((e - 1u) & 1u) * H * 6u * n;
-                if constexpr (PAIR) {
-                    small_walk<ROWS, true>(a, count, from, hist + 128u * wave, wA, wB, sig, tau);
+                if (!record) {
+                    small_walk<ROWS, false>(a, count, from, hist + 128u * wave, slot, wA, wB, sig, tau);
                 } else {
                     // the word before a slot is the last one of the other slot,
                     // or for slot 0 its copy in front
                     uint64_t* to = hist + n + (size_t)((e - 1u) & 1u) * H * n;
                     if (ROWS == 0 && e > 1u && ((e - 1u) & 1u) == 0) {
-                        if (lane < n)
-                            hist[lane] = sig;
+                        hist[slot] = sig;
                         small_sync();
                     }
-                    small_walk<ROWS, false>(a, count, from, to, wA, wB, sig, tau);
+                    small_walk<ROWS, true>(a, count, from, to, slot, wA, wB, sig, tau);
                 }
             }
         } else {
             if (e < epochs) {
                 const uint32_t x0 = e * H;
-                small_draw(a, stream, w, me, workers, a.t0 + x0, total - x0 < H ? total - x0 : H,
+                small_draw<ROWS>(a, stream, w, me, workers, a.t0 + x0, total - x0 < H ? total - x0 : H,
                            masks + (size_t)(e & 1u) * H * 6u * n);
             }
             if (record && e >= 2u) {
@@ -481,7 +508,7 @@ hipError_t launch_small(SmallArgs a, uint32_t blocks, bool pair, uint32_t n_cu, 
     const size_t budget = share ? max_lds / 2 : max_lds;
     const size_t scratch = sizeof(Worker) * (waves - walkers);
     auto lds_of = [&](uint32_t H) {
-        const size_t hist = pair ? 2u * 128u : (size_t)(2u * H + 1u) * a.n;
+        const size_t hist = a.obs ? (size_t)(2u * H + 1u) * a.n : walkers * 128u;
         return sizeof(uint64_t) * ((size_t)2 * H * 6u * a.n + hist) + scratch;
     };
     uint32_t H = 64u * (waves - walkers) / a.n;
