@@ -68,7 +68,7 @@ typedef enum { SD_INIT_UP = 0, SD_INIT_DOWN = 1, SD_INIT_RANDOM = 2 } sd_init_ki
 #define SD_FLAG_COMPLEMENT_RNG 1u /* replace every uniform r by 2^32-1-r (global spin-flip check) */
 #define SD_FLAG_MOMENTS 4u        /* batch plans: keep per-chain sums of the records instead of traces */
 #define SD_FLAG_GLOBAL_KERNELS 2u /* sd_run: always use one grid-wide launch per half-step, never the
-                                     single-workgroup LDS-resident kernel used for small lattices */
+                                     kernels that hold a small lattice in one workgroup */
 #define SD_FLAG_GENERAL_COMPARE 8u /* sd_half_step, sd_run, batch plans: decide the sites with the
                                       six-class bit-sliced compare instead of the paired one (same
                                       results, slower; a cross-check of the two forms) */
@@ -116,10 +116,15 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
 
 /*
  * k_steps full steps of one chain, steps step0 .. step0+k_steps-1, in place:
- * (lattices of at most 65536 sites with L % 64 == 0 run in one workgroup with
- * both lattices held in LDS, one launch for all steps; larger ones use two
- * grid-wide launches per step and, with obs, one more launch per chunk of
- * records, whose partial sums wait in a 512 KiB device buffer the library
+ * (lattices of up to 2048 64-site words, L = 362 and below, are drawn ahead:
+ * the device computes, round by round, whether each site's uniform lies below
+ * each of the six thresholds, and one workgroup picks the chain's bits, through
+ * a 16 MiB device buffer the library allocates once per (device, stream) for
+ * at most 16 streams and keeps; without it (stream capture before the first
+ * eager call, more streams) and for lattices of 64 words in short runs a single
+ * workgroup with the lattices in LDS does both, where they fit; larger lattices
+ * use two grid-wide launches per step and, with obs, one more launch per chunk
+ * of records, whose partial sums wait in a 512 KiB device buffer the library
  * allocates once per (device, stream) and keeps; the result is the same bit
  * for bit)
  * sigma (device) is updated, tau (device, same size) receives the last
@@ -160,7 +165,9 @@ SD_API sd_status sd_run_noalloc(void* sigma, void* tau, int32_t L, int32_t layou
  * is exactly sd_run(sigma[a], tau[a], L, layout, J[a], q[a], seed,
  * streams[a], step0, k_steps, ...), but every launch covers all the chains,
  * so that lattices of a few thousand words, which alone fill a small part of
- * the device, run together at the launch rate of one.  Lattices whose rows
+ * the device, run together at the launch rate of one.  Lattices of up to 2048
+ * words are drawn ahead, one workgroup per chain, as in sd_run.  Larger ones
+ * whose rows
  * are whole 64-bit words, at most 64 of them (L = 64 W with W dividing 256;
  * packed, or int8 with 16-byte aligned lattices), run all but the last step
  * as whole steps, up to eight per launch: each workgroup takes a band of rows
@@ -187,7 +194,8 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
 
 /*
  * Measure and fix how sd_run executes chains of this (L, layout) on the
- * current device: the single-workgroup LDS-resident kernel (workgroup size
+ * current device: the kernels that hold a lattice in one workgroup (drawn
+ * ahead up to 2048 words, else LDS-resident with a workgroup size of
  * 128/256/512, lattices up to the device's LDS) or one grid-wide launch per
  * half-step (64- or 32-bit word kernels when L % 64 == 0 — the same bytes —
  * and the number of workgroups).  Each candidate runs a few steps on scratch

@@ -4,6 +4,7 @@
 #include "shaken.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -14,6 +15,7 @@
 #include <tuple>
 #include <vector>
 
+#include "sd_ahead.hpp"
 #include "sd_autotune.hpp"
 #include "sd_batch.hpp"
 #include "sd_host.hpp"
@@ -269,6 +271,75 @@ Workspace* partials_workspace(hipStream_t st) {
     return w;
 }
 
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+void* ahead_scratch(Workspace& ws, hipStream_t st) {
+    static std::atomic<uint32_t> made{0};
+    if (ws.ahead)
+        return ws.ahead;
+    if (capturing(st))
+        return nullptr;
+    if (made.fetch_add(1) >= kAheadBuffers) {
+        made.fetch_sub(1);
+        return nullptr;
+    }
+    if (hipMalloc(&ws.ahead, kAheadBytes) != hipSuccess) {
+        (void)hipGetLastError();
+        ws.ahead = nullptr;
+        made.fetch_sub(1);
+    }
+    return ws.ahead;
+}
+
+// True for lattices the draw-ahead kernels take: int8 at any address, packed
+// words at 8-byte alignment (which 32-bit-word lattices may lack).
+static bool ahead_lattice(int32_t L, int32_t layout, const void* sigma, const void* tau) {
+    return ahead_size(L) &&
+           (layout == SD_I8 || ((reinterpret_cast<uintptr_t>(sigma) | reinterpret_cast<uintptr_t>(tau)) & 7u) == 0);
+}
+
+// Runs chains through the draw-ahead kernel if the stream's scratch is there;
+// *done tells whether it did.  obs: n_chains x n_rec records, chain-major.
+static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_t n_chains, int32_t L, int32_t layout,
+                                   const uint32_t (*T)[6], uint64_t seed, const uint32_t* streams, uint64_t step0,
+                                   uint32_t k_steps, int64_t* obs, uint32_t obs_every, uint32_t flags, hipStream_t st,
+                                   bool* done) {
+    *done = false;
+    Workspace* ws = partials_workspace(st);
+    if (!ws)
+        return hipSuccess;
+    std::unique_lock<std::mutex> hold(ws->mu);   // keeps this call's use of the scratch contiguous on the stream
+    void* scratch = ahead_scratch(*ws, st);
+    if (!scratch)
+        return hipSuccess;
+    const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
+    AheadArgs a;
+    std::memset(&a, 0, sizeof a);
+    for (uint32_t c = 0; c < n_chains; ++c) {
+        a.sigma[c] = sigma[c];
+        a.tau[c] = tau[c];
+        std::memcpy(a.T[c], T[c], sizeof a.T[c]);
+        a.stream[c] = streams[c];
+    }
+    a.n_chains = n_chains;
+    a.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
+    a.key1 = (uint32_t)(seed >> 32);
+    a.rng_xor = (flags & SD_FLAG_COMPLEMENT_RNG) ? 0xFFFFFFFFu : 0u;
+    a.L = (uint32_t)L;
+    a.int8_io = layout == SD_I8 ? 1u : 0u;
+    a.obs = n_rec ? obs : nullptr;
+    a.obs_chain = 3ull * n_rec;
+    a.obs_every = n_rec ? obs_every : 1u;
+    return run_ahead(a, step0, k_steps, scratch, kAheadBytes, st, done);
+}
+
 // Scratch memory of sd_run_noalloc: a file-scope device array (each device
 // holds its own copy until the process ends), so that the call allocates
 // nothing.  Host code never uses the array's name as an address: its device
@@ -296,6 +367,13 @@ sd_status scratch_ptr(const char* name, int64_t** out) {
     *out = p;
     return SD_OK;
 }
+
+// Word draws (words x half-steps) from which a lattice of at most 64 words is
+// drawn ahead by the whole device rather than by its own workgroup, which
+// saves a launch (us a call, own workgroup against device: 64^2, 10 steps 11.4
+// against 12.8, 20 steps 17.6 against 12.9; 32^2, 40 steps 12.3 against 13.4,
+// 100 steps 25 against 20).
+constexpr uint64_t kAheadDraws = 2048;
 
 // The step loop behind sd_run and sd_run_noalloc.  The grid kernels of a
 // recorded half-step B leave per-workgroup partial sums in a device buffer of
@@ -327,14 +405,26 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                                         : kLayI8Any)
                                  : kernel_layout(L, layout, sigma);
     const RunChoice ch = run_choice(L, layout);
-    // At most 64 words: one workgroup that draws ahead of the chain (k_small),
-    // for every layout (int8 at any address; 64-bit words need their alignment,
-    // which 32-bit-word lattices may lack).  The six-class cross-check keeps
-    // the general kernels.
-    const bool words_ok = layout == SD_I8 || ((reinterpret_cast<uintptr_t>(sigma) | reinterpret_cast<uintptr_t>(tau)) & 7u) == 0;
-    if (small_supported(L) && words_ok && ch.mode != 2 && !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE))) {
-        if (k_steps == 0)
+    // Small lattices draw ahead of the chain: runs of kAheadHalfSteps and more
+    // with the whole device drawing (k_ahead, needs scratch), shorter ones and
+    // those without scratch in one workgroup if they have at most 64 words
+    // (k_small).  The six-class cross-check keeps the general kernels.
+    const bool ahead_ok = ahead_lattice(L, layout, sigma, tau) && ch.mode != 2 &&
+                          !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE));
+    if (ahead_ok && k_steps == 0)
+        return SD_OK;
+    if (ahead_ok && !no_alloc && (!small_supported(L) || 2ull * k_steps * lattice_words((uint32_t)L) >= kAheadDraws)) {
+        uint32_t T[1][6];
+        threshold_table(J, q, T[0]);
+        bool done = false;
+        const hipError_t e = run_chains_ahead(&sigma, &tau, 1, L, layout, T, seed, &stream, step0, k_steps, obs,
+                                              obs_every, flags, st, &done);
+        if (e != hipSuccess)
+            return hip_fail(e, name);
+        if (done)
             return SD_OK;
+    }
+    if (ahead_ok && small_supported(L)) {
         const hipError_t e = launch_small_chain(sigma, tau, L, layout == SD_I8, J, q, seed, stream, step0, k_steps,
                                                 k_steps >= obs_every ? obs : nullptr, obs_every, flags, st);
         return e == hipSuccess ? SD_OK : hip_fail(e, name);
@@ -554,6 +644,18 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
                     "the scratch buffer", name, mc.n_chains, mc.blocks_per_chain, kPartialsWords);
     if (k_steps == 0)
         return SD_OK;
+    bool ahead = !(flags & SD_FLAG_GENERAL_COMPARE);
+    for (int32_t c = 0; c < n_chains; ++c)
+        ahead = ahead && ahead_lattice(L, layout, sigma[c], tau[c]);
+    if (ahead) {
+        bool done = false;
+        const hipError_t ea = run_chains_ahead(sigma, tau, mc.n_chains, L, layout, mc.T, seed, streams, step0, k_steps,
+                                               obs, obs_every, flags, st, &done);
+        if (ea != hipSuccess)
+            return hip_fail(ea, name);
+        if (done)
+            return SD_OK;
+    }
     int64_t* partials = nullptr;
     std::unique_lock<std::mutex> hold;   // keeps this call's use of the workspace contiguous on the stream
     if (n_rec) {
@@ -770,7 +872,7 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
     // candidates
     std::vector<RunChoice> cands;
     const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
-    if (small_supported(L)) {   // the small-lattice kernel picks its own workgroup
+    if (ahead_size(L)) {   // drawn ahead, whatever the threads
         RunChoice c;
         c.mode = 1;
         cands.push_back(c);

@@ -16,65 +16,12 @@
 //
 // Coupled pairs (coupling from the past, section 3.2) share their uniforms, so
 // one set of masks serves two walkers.
+#include "sd_class.hpp"
 #include "sd_small.hpp"
 
 namespace sd {
 
 namespace {
-
-constexpr uint32_t kListCap = 128;
-
-// A worker wavefront's scratch: the sites of each lane's word whose top byte
-// equals class k's, and the list of sites whose tails are to be drawn.
-struct Worker {
-    uint64_t eq[6][64];
-    uint32_t entry[kListCap];   // lane | bit << 6
-};
-
-__device__ __forceinline__ void small_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Philox4x32-10 with lane-varying second and fourth counter words (a tile of
-// words covers several half-steps).  Rounds 1-3 in plain products, so that
-// the four plane calls of a word share what does not depend on the plane.
-__device__ __forceinline__ U4 philox10_uvuv(uint32_t u0, uint32_t v1, uint32_t u2, uint32_t v3, uint32_t k0,
-                                            uint32_t k1) {
-    const uint64_t a0 = (uint64_t)kPhiloxM0 * u0;
-    const uint64_t a1 = (uint64_t)kPhiloxM1 * u2;
-    U4 c;
-    c.x0 = (hi32(a1) ^ k0) ^ v1;
-    c.x1 = lo32(a1);
-    c.x2 = (hi32(a0) ^ k1) ^ v3;
-    c.x3 = lo32(a0);
-#pragma unroll
-    for (int r = 1; r < 10; ++r) {
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-        if (r < 3) {
-            const uint64_t p0 = (uint64_t)kPhiloxM0 * c.x0;
-            const uint64_t p1 = (uint64_t)kPhiloxM1 * c.x2;
-            c = U4{hi32(p1) ^ (c.x1 ^ k0), lo32(p1), hi32(p0) ^ (c.x3 ^ k1), lo32(p0)};
-        } else {
-            c = philox_round(c, k0, k1);
-        }
-    }
-    return c;
-}
-
-// Truth tables (operand patterns 0xF0, 0xCC, 0xAA): less-than from the least
-// significant bit up, lt' = r bit 0 and threshold bit 1, or bits equal and lt;
-// equality so far; select b where a else c.
-constexpr uint32_t kLess = ((~kBopA & kBopB) | (~(kBopA ^ kBopB) & kBopC)) & 0xFFu;   // (r, threshold, lt)
-constexpr uint32_t kEqual = (~(kBopA ^ kBopB) & kBopC) & 0xFFu;                      // (r, threshold, eq)
-constexpr uint32_t kPick = ((kBopA & kBopB) | (~kBopA & kBopC)) & 0xFFu;             // (select, b, c)
-
-template <uint32_t TT>
-__device__ __forceinline__ uint32_t op3s(uint32_t a, uint32_t b, uint32_t c) {
-    return __builtin_amdgcn_bitop3_b32(a, b, c, TT);
-}
 
 // Words of a lattice: known at compile time for the row forms, so that mask and
 // history addresses are immediates.
@@ -89,40 +36,10 @@ __device__ __forceinline__ uint32_t small_half(const SmallArgs& a, uint32_t x) {
     return ROWS == 64 ? x >> 6 : ROWS == 32 ? x >> 4 : fdiv(x, a.div_n);
 }
 
-// Draws the tails of the n listed sites of a tile and adds the decided sites
-// to the class masks.  x0: the tile's first (half-step, word) index.
-template <int ROWS>
-__device__ __forceinline__ void small_tails(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t n, uint32_t x0,
-                                            uint32_t t_first, uint64_t* masks) {
-    const uint32_t nw = small_words<ROWS>(a);
-    small_sync();
-    for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
-        const uint32_t v = w.entry[e];
-        const uint32_t l = v & 63u, b = v >> 6;
-        const uint32_t x = x0 + l;
-        const uint32_t hs = small_half<ROWS>(a, x);
-        const uint32_t g = x - hs * nw;
-        const U4 y = philox10_uvuv(stream, t_first + hs, 2u * kTagDynamics + 1u, 16u * g + (b >> 2), a.key0, a.key1);
-        const uint32_t lo = (b & 1u) ? y.x1 : y.x0, hi = (b & 1u) ? y.x3 : y.x2;
-        const uint32_t tail = (((b & 2u) ? hi : lo) ^ a.rng_xor) >> 8;
-        const uint32_t bit = 1u << (b & 31u);
-        uint32_t* m = reinterpret_cast<uint32_t*>(masks + (hs * 6u * nw + g)) + (b >> 5);
-        const uint32_t* q = reinterpret_cast<const uint32_t*>(&w.eq[0][l]) + (b >> 5);
-        uint32_t open[6];
-#pragma unroll
-        for (uint32_t k = 0; k < 6; ++k)
-            open[k] = q[128u * k] & bit;
-#pragma unroll
-        for (uint32_t k = 0; k < 6; ++k)   // or-ing nothing costs less than a branch per class
-            atomicOr(m + 2u * k * nw, tail < (a.T[k] & 0xFFFFFFu) ? open[k] : 0u);
-    }
-    small_sync();
-}
-
 // The class masks of half-steps t_first .. t_first + count - 1 into masks
 // ([half-step][class][word]), by worker `me` of `workers`.
 template <int ROWS>
-__device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, Worker& w, uint32_t me,
+__device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, ClassList& w, uint32_t me,
                                            uint32_t workers, uint32_t t_first, uint32_t count, uint64_t* masks) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t nw = small_words<ROWS>(a);
@@ -132,72 +49,16 @@ __device__ __forceinline__ void small_draw(const SmallArgs& a, uint32_t stream, 
         const bool active = x < total;
         const uint32_t hs = active ? small_half<ROWS>(a, x) : 0u;
         const uint32_t g = active ? x - hs * nw : 0u;
-        uint32_t P[8][2];
-#pragma unroll
-        for (uint32_t p = 0; p < 4; ++p) {
-            // a 64-word tile is one half-step of a 64^2 lattice: its index is uniform
-            const U4 y = ROWS == 64 ? philox10_uuuv(stream, (t_first + (x0 >> 6)) | (p << 30), 2u * kTagDynamics, lane,
-                                                    a.key0, a.key1)
-                                    : philox10_uvuv(stream, (t_first + hs) | (p << 30), 2u * kTagDynamics, g, a.key0,
-                                                    a.key1);
-            P[2 * p][0] = y.x0;
-            P[2 * p][1] = y.x1;
-            P[2 * p + 1][0] = y.x2;
-            P[2 * p + 1][1] = y.x3;
-        }
-        if (a.rng_xor) {
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                P[m][0] = ~P[m][0];
-                P[m][1] = ~P[m][1];
-            }
-        }
-        uint64_t open = 0;   // sites some class leaves to its tail
-        uint64_t* out = masks + (hs * 6u * nw + g);
-#pragma unroll
-        for (uint32_t k = 0; k < 6; ++k) {
-            uint32_t lt[2] = {0u, 0u}, eq[2] = {~0u, ~0u};
-            // the 48 threshold bits are formed where they are used, on the
-            // scalar unit: kept across the tile they would not fit its registers
-            uint32_t T = a.T[k];
-            asm volatile("" : "+s"(T));
-#pragma unroll
-            for (int m = 7; m >= 0; --m) {
-                const uint32_t S = 0u - ((T >> (31 - m)) & 1u);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    lt[h] = op3s<kLess>(P[m][h], S, lt[h]);
-                    eq[h] = op3s<kEqual>(P[m][h], S, eq[h]);
-                }
-            }
-            const uint64_t e = (uint64_t)eq[0] | ((uint64_t)eq[1] << 32);
-            w.eq[k][lane] = e;
-            if (T & 0xFFFFFFu)   // uniform; no tail is below a zero threshold tail
-                open |= e;
-            if (active)
-                out[k * nw] = (uint64_t)lt[0] | ((uint64_t)lt[1] << 32);
-        }
-        if (!active)
-            open = 0;
-        uint32_t listed = 0;   // wavefront-uniform
-        for (;;) {
-            const uint64_t m = __ballot(open != 0);
-            if (m == 0)
-                break;
-            if (open != 0) {
-                const uint32_t e = listed + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                w.entry[e] = lane | ((uint32_t)__builtin_ctzll(open) << 6);
-                open &= open - 1;
-            }
-            listed += (uint32_t)__popcll(m);
-            if (listed >= 64u) {
-                small_tails<ROWS>(a, stream, w, listed, x0, t_first, masks);
-                listed = 0;
-            }
-        }
-        if (listed)
-            small_tails<ROWS>(a, stream, w, listed, x0, t_first, masks);
+        // a 64-word tile is one half-step of a 64^2 lattice: its index is uniform
+        const uint32_t t = ROWS == 64 ? t_first + (x0 >> 6) : t_first + hs;
+        class_masks<ROWS == 64>(a.key0, a.key1, stream, t, g, a.rng_xor, a.T, active, w, masks + (hs * 6u * nw + g),
+                                nw, [&](uint32_t l, uint32_t& tt, uint32_t& gg, uint64_t*& m)
+                                        __attribute__((always_inline)) {
+                                            const uint32_t h = small_half<ROWS>(a, x0 + l);
+                                            tt = t_first + h;
+                                            gg = x0 + l - h * nw;
+                                            m = masks + (h * 6u * nw + gg);
+                                        });
     }
 }
 
@@ -244,26 +105,8 @@ __device__ __forceinline__ uint64_t window_bits(uint64_t lo, uint64_t hi, uint32
 template <int ROWS, int WHICH>
 __device__ __forceinline__ void small_neighbours(uint64_t c, const uint64_t* lat, const Window& w, uint64_t& n1,
                                                  uint64_t& n2) {
-    const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
-    auto pack = [](uint32_t l, uint32_t h) { return (uint64_t)l | ((uint64_t)h << 32); };
-    if constexpr (ROWS == 64) {
-        if constexpr (WHICH == 0) {   // wave_ror:1, lane l takes lane l - 1 mod 64
-            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x13C, 0xF, 0xF, true),
-                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x13C, 0xF, 0xF, true));
-            n2 = pack(__builtin_amdgcn_alignbit(lo, hi, 31), __builtin_amdgcn_alignbit(hi, lo, 31));
-        } else {                      // wave_rol:1
-            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x134, 0xF, 0xF, true),
-                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x134, 0xF, 0xF, true));
-            n2 = pack(__builtin_amdgcn_alignbit(hi, lo, 1), __builtin_amdgcn_alignbit(lo, hi, 1));
-        }
-    } else if constexpr (ROWS == 32) {
-        if constexpr (WHICH == 0) {   // row_ror:1, lane l takes lane l - 1 mod 16
-            n1 = pack((uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x121, 0xF, 0xF, true), lo);
-            n2 = pack(__builtin_amdgcn_alignbit(lo, lo, 31), __builtin_amdgcn_alignbit(hi, hi, 31));
-        } else {                      // row_ror:15, lane l takes lane l + 1 mod 16
-            n1 = pack(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x12F, 0xF, 0xF, true));
-            n2 = pack(__builtin_amdgcn_alignbit(lo, lo, 1), __builtin_amdgcn_alignbit(hi, hi, 1));
-        }
+    if constexpr (ROWS != 0) {
+        row_neighbours<ROWS, WHICH>(c, n1, n2);
     } else {
         const uint64_t side = lat[w.side];
         n1 = window_bits(lat[w.q0], lat[w.q1], w.sh);
@@ -273,36 +116,14 @@ __device__ __forceinline__ void small_neighbours(uint64_t c, const uint64_t* lat
     }
 }
 
-// The class masks of one half-step's word.
-struct Masks {
-    uint64_t m[6];
-};
-
 template <int ROWS>
-__device__ __forceinline__ Masks load_masks(const uint64_t* p, const SmallArgs& a) {
+__device__ __forceinline__ ClassMasks load_masks(const uint64_t* p, const SmallArgs& a) {
     const uint32_t nw = small_words<ROWS>(a);
-    Masks r;
+    ClassMasks r;
 #pragma unroll
     for (uint32_t k = 0; k < 6; ++k)
         r.m[k] = p[k * nw];
     return r;
-}
-
-__device__ __forceinline__ uint64_t pick_class(const Masks& r, uint64_t c, uint64_t n1, uint64_t n2) {
-    uint32_t out[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t cc = (uint32_t)(c >> (32 * h)), a = (uint32_t)(n1 >> (32 * h)), b = (uint32_t)(n2 >> (32 * h));
-        const uint32_t one = a ^ b;   // exactly one J-neighbour is +1 (k = 1); else a tells k = 0 from k = 2
-        uint32_t m[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            m[k] = (uint32_t)(r.m[k] >> (32 * h));
-        const uint32_t down = op3s<kPick>(one, m[2], op3s<kPick>(a, m[4], m[0]));
-        const uint32_t up = op3s<kPick>(one, m[3], op3s<kPick>(a, m[5], m[1]));
-        out[h] = op3s<kPick>(cc, up, down);
-    }
-    return (uint64_t)out[0] | ((uint64_t)out[1] << 32);
 }
 
 // Half-steps 0 .. count - 1 of an epoch (A first, count even) on the walker's
@@ -320,16 +141,16 @@ __device__ __forceinline__ void small_walk(const SmallArgs& a, uint32_t count, c
     const uint64_t* p = masks + slot;
     uint64_t* h = hist + slot;
     const uint64_t* before = KEEP ? hist - nw : hist + 64;   // sigma for the window form
-    Masks ma = load_masks<ROWS>(p, a);
+    ClassMasks ma = load_masks<ROWS>(p, a);
     for (uint32_t i = 0; i < count; i += 2) {
         uint64_t n1, n2;
-        const Masks mb = load_masks<ROWS>(p + 6u * nw, a);
+        const ClassMasks mb = load_masks<ROWS>(p + 6u * nw, a);
         small_neighbours<ROWS, 0>(sig, before, wA, n1, n2);
         tau = pick_class(ma, sig, n1, n2);
         if (KEEP || ROWS == 0)
             h[0] = tau;
         if (ROWS == 0)
-            small_sync();
+            class_sync();
         p += 12u * nw;
         ma = load_masks<ROWS>(p, a);
         small_neighbours<ROWS, 1>(tau, KEEP ? h - slot : hist, wB, n1, n2);
@@ -339,7 +160,7 @@ __device__ __forceinline__ void small_walk(const SmallArgs& a, uint32_t count, c
         else if (ROWS == 0)
             h[64] = sig;
         if (ROWS == 0)
-            small_sync();
+            class_sync();
         if (KEEP) {
             before = h - slot + nw;
             h += 2u * nw;
@@ -394,11 +215,11 @@ __global__ __launch_bounds__(1024) void k_small(SmallArgs a) {
     const bool record = !PAIR && a.obs != nullptr;
     uint64_t* hist = masks + (size_t)2 * H * 6u * n;
     uint64_t* after = hist + (record ? (2u * H + 1u) * n : kWalkers * 128u);
-    Worker* work = reinterpret_cast<Worker*>(after);
+    ClassList* work = reinterpret_cast<ClassList*>(after);
     const uint32_t pair = PAIR ? a.pairs[blockIdx.x] : 0u;
     const uint32_t stream = a.stream + pair;
     const bool walker = wave < kWalkers;
-    Worker& w = work[walker ? 0u : wave - kWalkers];
+    ClassList& w = work[walker ? 0u : wave - kWalkers];
     const uint32_t me = wave - kWalkers;
     // the walker's word; lanes past the lattice's words repeat others (the row
     // form of 32^2 four times over, so that its row shifts stay within them)
@@ -436,7 +257,7 @@ __global__ __launch_bounds__(1024) void k_small(SmallArgs a) {
                     uint64_t* to = hist + n + (size_t)((e - 1u) & 1u) * H * n;
                     if (ROWS == 0 && e > 1u && ((e - 1u) & 1u) == 0) {
                         hist[slot] = sig;
-                        small_sync();
+                        class_sync();
                     }
                     small_walk<ROWS, true>(a, count, from, to, slot, wA, wB, sig, tau);
                 }
@@ -506,7 +327,7 @@ hipError_t launch_small(SmallArgs a, uint32_t blocks, bool pair, uint32_t n_cu, 
     const uint32_t waves = share ? 8u : 16u;
     const uint32_t walkers = pair ? 2u : 1u;
     const size_t budget = share ? max_lds / 2 : max_lds;
-    const size_t scratch = sizeof(Worker) * (waves - walkers);
+    const size_t scratch = sizeof(ClassList) * (waves - walkers);
     auto lds_of = [&](uint32_t H) {
         const size_t hist = a.obs ? (size_t)(2u * H + 1u) * a.n : walkers * 128u;
         return sizeof(uint64_t) * ((size_t)2 * H * 6u * a.n + hist) + scratch;

@@ -47,8 +47,17 @@ SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stre
 constexpr size_t kPartialsWords = 65536;
 struct Workspace {
     int64_t* p = nullptr;
+    void* ahead = nullptr;   // kAheadBytes, made by the first run that draws ahead (ahead_scratch)
     std::mutex mu;
 };
 Workspace* partials_workspace(hipStream_t st);
+
+// Scratch of the draw-ahead runs (class masks of two rounds), kept with the
+// workspace; the caller holds ws.mu.  At most kAheadBuffers exist in a process
+// (256 MiB); null past that, under capture, or out of memory, and the caller
+// takes the kernels that need none.
+constexpr size_t kAheadBytes = 16u << 20;
+constexpr uint32_t kAheadBuffers = 16;
+void* ahead_scratch(Workspace& ws, hipStream_t st);
 
 }  // namespace sd

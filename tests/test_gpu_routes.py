@@ -164,3 +164,70 @@ def test_exact_samples_shared_and_alone(oracle, L):
         want, t = oracle.propp_wilson(L, J, q, SEED, 60, 1 << 20, T0, T_max)
         assert t == T1[0]
         assert np.array_equal(inputs.unpack_bits(one[0].cpu().numpy(), L), want)
+
+
+@pytest.mark.parametrize("L,layout,k,every", [
+    (8, sd.SD_P64, 1100, 1), (9, sd.SD_I8, 40, 1), (32, sd.SD_P32, 300, 7), (64, sd.SD_I8, 700, 1), (63, sd.SD_I8, 20, 2),
+    (65, sd.SD_I8, 33, 1), (72, sd.SD_P64, 1, 1), (127, sd.SD_I8, 5, 0), (128, sd.SD_P64, 90, 3), (160, sd.SD_P32, 9, 1),
+    (181, sd.SD_I8, 12, 1), (182, sd.SD_I8, 12, 1), (192, sd.SD_P64, 150, 4), (200, sd.SD_P64, 150, 1), (256, sd.SD_I8, 200, 1),
+    (257, sd.SD_I8, 30, 1), (320, sd.SD_P64, 100, 1), (360, sd.SD_P64, 64, 5), (362, sd.SD_I8, 70, 1), (363, sd.SD_I8, 3, 1)])
+def test_drawn_ahead_by_the_device(L, layout, k, every):
+    # every form of the walker (rows in registers, whole words, bit strings; one
+    # and two words a thread; partial last words), the sizes where they change
+    # hands, one round and several with a ragged last one, records of rounds
+    # that end between two of them; against the grid kernels
+    print(f"ahead L={L} layout={layout} k={k}", flush=True)
+    start = sd.new_lattice(L, layout)
+    sd.sd_init(start, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    for flags in (0, sd.SD_FLAG_COMPLEMENT_RNG):
+        got = []
+        for f in (flags, flags | sd.SD_FLAG_GLOBAL_KERNELS):
+            sigma, tau = start.clone(), torch.zeros_like(start)
+            obs = torch.full((k // every if every else 0, 3), -1, dtype=torch.int64, device="cuda")
+            sd.sd_run(sigma, tau, L, layout, 0.45, 0.9, SEED, 8, 5, k, obs if every else None, every, f)
+            got.append((sigma, tau, obs))
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("L,layout,n", [(16, sd.SD_P64, 16), (64, sd.SD_I8, 3), (100, sd.SD_I8, 5), (200, sd.SD_P64, 2),
+                                        (256, sd.SD_I8, 16), (320, sd.SD_P32, 3)])
+def test_several_chains_drawn_ahead(L, layout, n):
+    # chains of different couplings and streams share a launch; each is its own sd_run
+    print(f"several chains ahead L={L} n={n}", flush=True)
+    k, every = 40, 3
+    J, q, streams = [0.2 + 0.1 * a for a in range(n)], [1.5 - 0.1 * a for a in range(n)], [7 * a + 1 for a in range(n)]
+    sig, tau = [], []
+    for a in range(n):
+        x = sd.new_lattice(L, layout)
+        sd.sd_init(x, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, a)
+        sig.append(x)
+        tau.append(torch.zeros_like(x))
+    first = [x.clone() for x in sig]
+    obs = torch.full((n, k // every, 3), -1, dtype=torch.int64, device="cuda")
+    sd.sd_run_many(sig, tau, L, layout, J, q, SEED, streams, 3, k, obs, every)
+    for a in range(n):
+        one, two = first[a].clone(), torch.zeros_like(first[a])
+        rec = torch.empty((k // every, 3), dtype=torch.int64, device="cuda")
+        sd.sd_run(one, two, L, layout, J[a], q[a], SEED, streams[a], 3, k, rec, every, sd.SD_FLAG_GLOBAL_KERNELS)
+        assert torch.equal(one, sig[a]) and torch.equal(two, tau[a]) and torch.equal(rec, obs[a])
+
+
+def test_more_streams_than_scratch_buffers():
+    # the scratch of drawn-ahead runs is made for a bounded number of streams;
+    # runs on further ones take other kernels and give the same chains
+    L, k = 96, 30
+    start = sd.new_lattice(L, sd.SD_P64)
+    sd.sd_init(start, L, sd.SD_P64, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    torch.cuda.synchronize()
+    out = []
+    streams = [torch.cuda.Stream() for _ in range(20)]
+    for st in streams:
+        sigma, tau = start.clone(), torch.zeros_like(start)
+        obs = torch.zeros((k, 3), dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        sd.sd_run(sigma, tau, L, sd.SD_P64, 0.4, 0.6, SEED, 1, 0, k, obs, 1, hip_stream=st)
+        out.append((sigma, tau, obs))
+    torch.cuda.synchronize()
+    for o in out[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(o, out[0]))
