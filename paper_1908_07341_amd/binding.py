@@ -8,6 +8,7 @@ has not been built, loading fails.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -132,14 +133,18 @@ def _need(t, nbytes: int, what: str) -> None:
 
 
 def _lattice(t, L: int, layout: int, what: str) -> None:
-    nb = sd_lattice_bytes(L, layout)
+    nb = _lattice_bytes(L, layout)
     if nb:   # an unsupported (L, layout) is reported by the library itself
         _need(t, nb, what)
 
 
 def _stream(hip_stream):
     if hip_stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        # the raw handle of torch's current stream: making a torch.cuda.Stream
+        # object for it cost as much as the rest of a call (8 us)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     if isinstance(hip_stream, torch.cuda.Stream):
         return ctypes.c_void_p(hip_stream.cuda_stream)
     return ctypes.c_void_p(hip_stream)
@@ -147,6 +152,11 @@ def _stream(hip_stream):
 
 def sd_abi_version() -> int:
     return int(lib().sd_abi_version())
+
+
+@functools.lru_cache(maxsize=256)
+def _lattice_bytes(L: int, layout: int) -> int:
+    return int(lib().sd_lattice_bytes(L, layout))
 
 
 def sd_lattice_bytes(L: int, layout: int) -> int:

@@ -231,27 +231,33 @@ __global__ __launch_bounds__(1024) void k_corr_row64(CorrLattices cl, uint32_t L
 
 // Diagonal correlation sums (section 3.3, Table 1).  Block (x, y): direction
 // d = x / (lmax + 1) (0: partner (i+l, j+l), SW-NE; 1: partner (i+l, j-l),
-// NW-SE) and l = x % (lmax + 1), rows j = y, y + gridDim.y, ...; the block's
-// count of unequal pairs goes to out[x] as (pairs - 2 * unequal) by one atomic.
+// NW-SE) and l = x % (lmax + 1), rows j = y, y + gridDim.y, ..., a row's words
+// (or sites) on 2^row_shift neighbouring threads, so that short rows share the
+// workgroup; the block's count of unequal pairs goes to out[x] as
+// (pairs - 2 * unequal): stored when the block has all the rows (gridDim.y
+// == 1: out need not be zeroed first), else added by one atomic.
 // Packed: rows are L / 32 words (L % 32 == 0); the partner row's bits from
 // column l on are a funnel shift of two of its words.
 template <int PACKED>
 __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigma, Geom G, int32_t lmax,
-                                                    int64_t* __restrict__ out) {
+                                                    uint32_t row_shift, int64_t* __restrict__ out) {
     __shared__ int64_t red[2 * 4];
     const uint32_t L = G.L;
     const uint32_t n_l = (uint32_t)lmax + 1u;
     const uint32_t dir = blockIdx.x / n_l, l = blockIdx.x % n_l;
     int64_t diff = 0, pairs = 0;
+    const uint32_t rows = blockDim.x >> row_shift;                 // rows the block takes at once
+    const uint32_t cols = 1u << row_shift, col = threadIdx.x & (cols - 1u);
+    const uint32_t row0 = blockIdx.y * rows + (threadIdx.x >> row_shift), row_step = gridDim.y * rows;
     if constexpr (PACKED == 1) {
         const uint32_t* s = static_cast<const uint32_t*>(sigma);
         const uint32_t W = L / 32u;
         const uint32_t sh = l & 31u;
-        for (uint32_t j = blockIdx.y; j < L; j += gridDim.y) {
+        for (uint32_t j = row0; j < L; j += row_step) {
             const uint32_t jp = dir == 0 ? (j + l) % L : (j + L - l) % L;
             const uint32_t* row = s + (size_t)j * W;
             const uint32_t* prow = s + (size_t)jp * W;
-            for (uint32_t k = threadIdx.x; k < W; k += blockDim.x) {
+            for (uint32_t k = col; k < W; k += cols) {
                 uint32_t q0 = k + (l >> 5);
                 q0 = q0 >= W ? q0 - W : q0;
                 const uint32_t q1 = q0 + 1u == W ? 0u : q0 + 1u;
@@ -261,9 +267,9 @@ __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigm
             }
         }
     } else {
-        for (uint32_t j = blockIdx.y; j < L; j += gridDim.y) {
+        for (uint32_t j = row0; j < L; j += row_step) {
             const uint32_t jp = dir == 0 ? (j + l) % L : (j + L - l) % L;
-            for (uint32_t i = threadIdx.x; i < L; i += blockDim.x) {
+            for (uint32_t i = col; i < L; i += cols) {
                 const uint32_t ip = (i + l) % L;
                 const size_t a = (size_t)j * L + i, b = (size_t)jp * L + ip;
                 if constexpr (PACKED == 2) {
@@ -279,7 +285,9 @@ __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigm
     }
     int64_t v[2] = {diff, pairs};
     block_sum_i64<2>(v, red);
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0 && gridDim.y == 1u)
+        out[blockIdx.x] = v[1] - 2 * v[0];
+    else if (threadIdx.x == 0)
         atomicAdd(reinterpret_cast<unsigned long long*>(out + blockIdx.x), (unsigned long long)(v[1] - 2 * v[0]));
 }
 
@@ -313,19 +321,34 @@ hipError_t launch_observe(int layout, const void* sigma, const void* tau, const 
 hipError_t launch_corr_diag(int layout, const void* sigma, const Geom& G, int32_t lmax, int64_t* out,
                             hipStream_t st) {
     const uint32_t n = 2u * ((uint32_t)lmax + 1u);
-    hipError_t e = launch_fill_i64(out, n, 0, st);
-    if (e != hipSuccess)
-        return e;
-    uint32_t row_blocks = kMaxBlocks / n;
-    row_blocks = row_blocks < G.L ? row_blocks : G.L;
-    row_blocks = row_blocks ? row_blocks : 1u;
+    const uint32_t width = layout == kLayP64 || layout == kLayP32 ? G.L / 32u : G.L;   // items of a row
+    uint32_t row_shift = 0;
+    while (row_shift < 8u && (1u << row_shift) < width)
+        ++row_shift;
+    // One workgroup per sum up to kDiagItems words (or sites) a lattice: one
+    // launch instead of two, no atomics (32^2 packed, l <= 16: 8.8 us with the
+    // zeroing and a workgroup per row, 3.4 so); larger lattices split their rows
+    // over about kMaxBlocks workgroups.
+    constexpr uint64_t kDiagItems = 8192;
+    uint32_t row_blocks = 1u;
+    if ((uint64_t)width * G.L > kDiagItems) {
+        const uint32_t groups = (G.L + (256u >> row_shift) - 1u) / (256u >> row_shift);
+        row_blocks = kMaxBlocks / n;
+        row_blocks = row_blocks < groups ? row_blocks : groups;
+        row_blocks = row_blocks ? row_blocks : 1u;
+    }
+    if (row_blocks > 1u) {
+        const hipError_t e = launch_fill_i64(out, n, 0, st);
+        if (e != hipSuccess)
+            return e;
+    }
     const dim3 grid(n, row_blocks);
     if (layout == kLayBits)
-        hipLaunchKernelGGL((k_corr_diag<2>), grid, dim3(256), 0, st, sigma, G, lmax, out);
+        hipLaunchKernelGGL((k_corr_diag<2>), grid, dim3(256), 0, st, sigma, G, lmax, row_shift, out);
     else if (layout == kLayP64 || layout == kLayP32)
-        hipLaunchKernelGGL((k_corr_diag<1>), grid, dim3(256), 0, st, sigma, G, lmax, out);
+        hipLaunchKernelGGL((k_corr_diag<1>), grid, dim3(256), 0, st, sigma, G, lmax, row_shift, out);
     else
-        hipLaunchKernelGGL((k_corr_diag<0>), grid, dim3(256), 0, st, sigma, G, lmax, out);
+        hipLaunchKernelGGL((k_corr_diag<0>), grid, dim3(256), 0, st, sigma, G, lmax, row_shift, out);
     return hipGetLastError();
 }
 

@@ -231,3 +231,19 @@ def test_more_streams_than_scratch_buffers():
     torch.cuda.synchronize()
     for o in out[1:]:
         assert all(torch.equal(x, y) for x, y in zip(o, out[0]))
+
+
+@pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
+                                      (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
+                                      (544, sd.SD_P32)])
+def test_diagonal_correlations_one_or_many_workgroups(oracle, L, layout):
+    # sums kept by one workgroup (which overwrites whatever out holds) and split
+    # over several, rows of 1 to 256 items, on each side of the division
+    print(f"diagonals L={L} layout={layout}", flush=True)
+    lat = inputs.random_lattice(L, L + 1)
+    host = lat if layout == sd.SD_I8 else inputs.pack_bits(lat)
+    dev = torch.from_numpy(host.reshape(-1).copy()).cuda()
+    for lmax in sorted({0, 1, L // 2, L - 1}):
+        out = torch.full((2, lmax + 1), 12345, dtype=torch.int64, device="cuda")
+        sd.sd_corr_diag(dev, L, layout, lmax, out)
+        assert np.array_equal(out.cpu().numpy().reshape(-1), oracle.corr_diag(lat, lmax).reshape(-1))
