@@ -125,8 +125,9 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
  * workgroup with the lattices in LDS does both, where they fit; larger lattices
  * use two grid-wide launches per step and, with obs, one more launch per chunk
  * of records, whose partial sums wait in a 512 KiB device buffer the library
- * allocates once per (device, stream) and keeps; the result is the same bit
- * for bit)
+ * allocates once per (device, stream) and keeps, or, where rows are whole
+ * 64-bit words up to L = 4096, whole steps as in sd_run_many; the result is the
+ * same bit for bit)
  * sigma (device) is updated, tau (device, same size) receives the last
  * half-step-A lattice (its input content is ignored).  If obs (device) is not
  * NULL it receives, after every obs_every-th step, the int64 triple
@@ -167,10 +168,9 @@ SD_API sd_status sd_run_noalloc(void* sigma, void* tau, int32_t L, int32_t layou
  * so that lattices of a few thousand words, which alone fill a small part of
  * the device, run together at the launch rate of one.  Lattices of up to 2048
  * words are drawn ahead, one workgroup per chain, as in sd_run.  Larger ones
- * whose rows
- * are whole 64-bit words, at most 64 of them (L = 64 W with W dividing 256;
- * packed, or int8 with 16-byte aligned lattices), run all but the last step
- * as whole steps, up to eight per launch: each workgroup takes a band of rows
+ * whose rows are whole 64-bit words, at most 64 of them (packed, or int8 with
+ * 16-byte aligned lattices), run all but the last step as whole steps, up to
+ * eight per launch: each workgroup takes a band of rows
  * plus one halo row per step on each side into LDS and recomputes the halo
  * from the same counter-based uniforms (sections 2 and 4: eqs. (15)-(16)
  * drawn site by site), so results do not change; tau's memory holds sigma
@@ -194,10 +194,10 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
 
 /*
  * Measure and fix how sd_run executes chains of this (L, layout) on the
- * current device: the kernels that hold a lattice in one workgroup (drawn
- * ahead up to 2048 words, else LDS-resident with a workgroup size of
- * 128/256/512, lattices up to the device's LDS) or one grid-wide launch per
- * half-step (64- or 32-bit word kernels when L % 64 == 0 — the same bytes —
+ * current device: the built-in rule's kernels of several half-steps a launch
+ * (drawn ahead, or whole steps in bands of rows) where it has them for this L,
+ * or one grid-wide launch per half-step (64- or 32-bit word kernels when
+ * L % 64 == 0 — the same bytes —
  * and the number of workgroups).  Each candidate runs a few steps on scratch
  * lattices (allocated and freed here) with HIP events; the fastest is used by
  * every later sd_run of this process with these (L, layout) and stored under
@@ -209,9 +209,10 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
 SD_API sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* hip_stream);
 
 /* The choice sd_run currently uses for (L, layout): mode 0 = built-in rule,
- * 1 = LDS kernel, 2 = grid kernels; word width; the workgroups of each
- * half-step launch when sd_run takes the grid kernels; the LDS kernel's
- * workgroup size. */
+ * 1 = the rule's kernels of several half-steps a launch, 2 = one grid launch
+ * per half-step; word width; the workgroups of each half-step launch when
+ * sd_run takes the grid kernels; the workgroup size where the rule falls back
+ * to a single workgroup with the lattices in LDS. */
 SD_API sd_status sd_tuned_choice(int32_t L, int32_t layout, int32_t* mode, int32_t* width, int32_t* blocks,
                                  int32_t* threads);
 

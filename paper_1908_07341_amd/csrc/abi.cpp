@@ -169,7 +169,8 @@ sd_status check_lattice(const void* p, int32_t L, int32_t layout, const char* na
 
 // Launch choice of sd_run for one (device, L, layout), set by sd_tune.
 struct RunChoice {
-    int mode = 0;           // 0: built-in rule, 1: single-workgroup LDS kernel, 2: grid kernels
+    int mode = 0;           // 0: built-in rule (run_chain), 1: its kernels of several half-steps a launch,
+                            // 2: grid kernels
     int width = 64;         // packed layouts with L % 64 == 0: 64- or 32-bit word kernels
     uint32_t blocks = 0;    // grid kernels: workgroups (0 = default)
     uint32_t threads = 256; // LDS kernel: workgroup size
@@ -185,18 +186,6 @@ RunChoice run_choice(int32_t L, int32_t layout) {
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_run_choice.find(std::make_tuple(dev, L, layout));
     return it == g_run_choice.end() ? RunChoice{} : it->second;
-}
-
-// Largest lattice (64-bit words) the single-workgroup LDS kernel may hold.
-uint32_t lds_max_words() {
-    int dev = 0, max_lds = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-        return kSingleLdsMaxWords;
-    uint32_t w = kSingleLdsMaxWords;
-    while (batch_lds_bytes(2 * w, 1024) <= (size_t)max_lds - 512)
-        w *= 2;
-    return w;
 }
 
 hipError_t device_limits(uint32_t* n_cu, size_t* max_lds) {
@@ -298,11 +287,15 @@ void* ahead_scratch(Workspace& ws, hipStream_t st) {
     return ws.ahead;
 }
 
+// 64-bit words at their alignment, which 32-bit-word lattices may lack.
+static bool words_aligned(const void* sigma, const void* tau) {
+    return ((reinterpret_cast<uintptr_t>(sigma) | reinterpret_cast<uintptr_t>(tau)) & 7u) == 0;
+}
+
 // True for lattices the draw-ahead kernels take: int8 at any address, packed
-// words at 8-byte alignment (which 32-bit-word lattices may lack).
+// words at 8-byte alignment.
 static bool ahead_lattice(int32_t L, int32_t layout, const void* sigma, const void* tau) {
-    return ahead_size(L) &&
-           (layout == SD_I8 || ((reinterpret_cast<uintptr_t>(sigma) | reinterpret_cast<uintptr_t>(tau)) & 7u) == 0);
+    return ahead_size(L) && (layout == SD_I8 || words_aligned(sigma, tau));
 }
 
 // Runs chains through the draw-ahead kernel if the stream's scratch is there;
@@ -368,6 +361,120 @@ sd_status scratch_ptr(const char* name, int64_t** out) {
     return SD_OK;
 }
 
+// The step loop of several chains in the grid kernels (or of one): whole steps,
+// several per launch, where rows are whole words, else half-steps; records
+// through partials (kPartialsWords int64; n_rec > 0 needs a record's sums of
+// either kernel to fit).
+static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, bool whole_words, bool paired, int32_t L,
+                                uint64_t seed, uint64_t step0, uint32_t k_steps, int64_t* obs, uint32_t n_rec,
+                                uint32_t obs_every, uint32_t flags, int64_t* partials, hipStream_t st) {
+    const uint32_t stride = 4u * mc.blocks_per_chain * mc.n_chains;   // partial sums of one record
+    DrawParams base = dynamics_params(0.0, 0.0, seed, 0u, 0u, flags & SD_FLAG_COMPLEMENT_RNG);
+    const uint32_t chunk = n_rec ? (uint32_t)(kPartialsWords / stride) : 1u;
+    const uint64_t obs_chain = 3ull * n_rec;
+    uint32_t pending = 0;
+    hipError_t e = hipSuccess;
+    // Rows of at most 64 words: whole steps, several per launch (bands with
+    // halo rows, sigma alternating between the two lattices of each chain),
+    // for all but the last step, in an even number of launches so that sigma
+    // ends where it started; the last step takes the half-step kernels, which
+    // leave tau in place.
+    uint32_t n_cu = 0;
+    size_t max_lds = 0;
+    if (const hipError_t ed = device_limits(&n_cu, &max_lds); ed != hipSuccess)
+        return ed;
+    const BandPlan plan = band_plan(L, mc.n_chains, n_cu);
+    uint32_t depth = plan.depth;
+    if (depth && n_rec) {   // the records of one launch must fit the partial-sum buffer
+        const uint64_t per_rec = 4ull * plan.bands * mc.n_chains;
+        depth = (uint32_t)std::min<uint64_t>(depth, kPartialsWords / per_rec);
+    }
+    const bool band_ok = depth != 0 && whole_words && k_steps >= 3;
+    uint32_t n_fused = band_ok ? k_steps - 1u : 0u;
+    // an even number of launches of at most `depth` steps, none empty
+    uint32_t n_launch = n_fused ? (n_fused + depth - 1) / depth : 0u;
+    n_launch += n_launch % 2;
+    if (n_launch > n_fused)   // one step per launch and an odd count: leave one more step to the half-steps
+        n_launch = --n_fused;
+    if (n_fused) {
+        BandArgs ba;
+        std::memset(&ba, 0, sizeof ba);
+        for (uint32_t a = 0; a < mc.n_chains; ++a) {
+            std::memcpy(ba.T[a], mc.T[a], sizeof ba.T[a]);
+            ba.stream[a] = mc.stream[a];
+        }
+        ba.n_chains = mc.n_chains;
+        ba.L = (uint32_t)L;
+        ba.W = (uint32_t)L / 64u;
+        ba.bands = plan.bands;
+        ba.divW = make_fastdiv(ba.W);
+        const uint32_t R = ((uint32_t)L + ba.bands - 1u) / ba.bands;   // of the widest band
+        ba.key0 = base.key0;
+        ba.key1 = base.key1;
+        const uint32_t stride_b = 4u * ba.bands * ba.n_chains;
+        const uint32_t chunk_b = (uint32_t)(kPartialsWords / stride_b);
+        ba.rec_stride = stride_b;
+        const bool complement = (flags & SD_FLAG_COMPLEMENT_RNG) != 0;
+        uint32_t m = 0;   // steps done
+        for (uint32_t j = 0; j < n_launch && e == hipSuccess; ++j) {
+            const uint32_t steps = n_fused / n_launch + (j < n_fused % n_launch ? 1u : 0u);
+            for (uint32_t a = 0; a < mc.n_chains; ++a) {
+                ba.src[a] = j % 2 ? mc.tau[a] : mc.sigma[a];
+                ba.dst[a] = j % 2 ? mc.sigma[a] : mc.tau[a];
+            }
+            ba.t0 = (uint32_t)(2 * (step0 + m));
+            ba.steps = steps;
+            ba.threads = band_threads(R, ba.W, steps);
+            ba.rec_mask = 0;
+            uint32_t n_here = 0;
+            if (n_rec)
+                for (uint32_t s = 0; s < steps; ++s)
+                    if ((m + s + 1) % obs_every == 0) {
+                        ba.rec_mask |= 1u << s;
+                        ++n_here;
+                    }
+            if (n_here && pending + n_here > chunk_b) {
+                const uint32_t r_next = (m + obs_every) / obs_every - 1;   // first record of this launch
+                e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
+                                           r_next - pending, st);
+                pending = 0;
+                if (e != hipSuccess)
+                    break;
+            }
+            e = launch_band_step(ba, klay == kLayI8Row, paired, complement,
+                                 n_here ? partials + (size_t)pending * stride_b : nullptr, st);
+            m += steps;
+            pending += n_here;
+            if (e == hipSuccess && pending && j + 1 == n_launch) {
+                e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
+                                           m / obs_every - pending, st);
+                pending = 0;
+            }
+        }
+    }
+    for (uint32_t m = n_fused; m < k_steps && e == hipSuccess; ++m) {
+        const uint64_t n = step0 + m;
+        base.t = (uint32_t)(2 * n);
+        e = launch_half_step_many(klay, 0, mc, G, base, paired, nullptr, st);
+        if (e != hipSuccess)
+            break;
+        base.t = (uint32_t)(2 * n + 1);
+        const bool rec = n_rec && (m + 1) % obs_every == 0 && (m + 1) / obs_every <= n_rec;
+        e = launch_half_step_many(klay, 1, mc, G, base, paired, rec ? partials + (size_t)pending * stride : nullptr,
+                                  st);
+        if (rec && e == hipSuccess) {
+            const uint32_t r = (m + 1) / obs_every - 1;
+            ++pending;
+            if (pending == chunk || r + 1 == n_rec) {
+                e = launch_obs_finish_many(partials, mc.blocks_per_chain, mc.n_chains, pending, stride, obs,
+                                           obs_chain, r + 1 - pending, st);
+                pending = 0;
+            }
+        }
+    }
+    return e;
+}
+
 // Word draws (words x half-steps) from which a lattice of at most 64 words is
 // drawn ahead by the whole device rather than by its own workgroup, which
 // saves a launch (us a call, own workgroup against device: 64^2, 10 steps 11.4
@@ -405,10 +512,10 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                                         : kLayI8Any)
                                  : kernel_layout(L, layout, sigma);
     const RunChoice ch = run_choice(L, layout);
-    // Small lattices draw ahead of the chain: runs of kAheadHalfSteps and more
-    // with the whole device drawing (k_ahead, needs scratch), shorter ones and
-    // those without scratch in one workgroup if they have at most 64 words
-    // (k_small).  The six-class cross-check keeps the general kernels.
+    // Small lattices draw ahead of the chain: runs of kAheadDraws word draws and
+    // more, and lattices past 64 words, with the whole device drawing (k_ahead,
+    // needs scratch), the others and those without scratch in one workgroup if
+    // they have at most 64 words (k_small).  The six-class cross-check keeps the general kernels.
     const bool ahead_ok = ahead_lattice(L, layout, sigma, tau) && ch.mode != 2 &&
                           !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE));
     if (ahead_ok && k_steps == 0)
@@ -433,10 +540,9 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
         klay = ch.width == 32 ? kLayP32 : kLayP64;
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
     const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
-    const uint32_t lds_words = ch.mode == 1 ? lds_max_words() : kSingleLdsMaxWords;
     const bool lds_ok = (klay == kLayP64 || klay == kLayI8Row || (klay == kLayP32 && L % 64 == 0) ||
                          klay == kLayBits) &&
-                        n_words <= lds_words && ch.mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS);
+                        n_words <= kSingleLdsMaxWords && ch.mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS);
     if (lds_ok) {
         if (k_steps == 0)
             return SD_OK;
@@ -458,6 +564,32 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
             hold = std::unique_lock<std::mutex>(ws->mu);
             partials = ws->p;
         }
+    }
+    // Rows of whole words up to 4096^2: whole steps in bands of rows, several
+    // per launch, as sd_run_many runs them (us per half-step, a launch each
+    // against this: 512^2 3.8 -> 1.6, 1024^2 3.9 -> 1.7, 2048^2 4.0 -> 2.2,
+    // 4096^2 5.9 -> 3.9).
+    const bool whole_words = klay == kLayI8Row || (klay == kLayP64 && words_aligned(sigma, tau));
+    if (ch.mode != 2 && whole_words && k_steps >= 3 && (!n_rec || partials) &&
+        !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE))) {
+        uint32_t n_cu = 0;
+        size_t max_lds = 0;
+        e = device_limits(&n_cu, &max_lds);
+        if (e == hipSuccess && band_plan(L, 1u, n_cu).bands) {
+            ManyChains mc;
+            std::memset(&mc, 0, sizeof mc);
+            mc.sigma[0] = sigma;
+            mc.tau[0] = tau;
+            threshold_table(J, q, mc.T[0]);
+            mc.stream[0] = stream;
+            mc.n_chains = 1;
+            mc.blocks_per_chain = many_blocks_per_chain(G);
+            e = run_many_grid(mc, G, klay, true, thresholds_paired(mc.T[0]), L, seed, step0, k_steps, obs, n_rec,
+                              obs_every, flags, partials, st);
+            return e == hipSuccess ? SD_OK : hip_fail(e, name);
+        }
+        if (e != hipSuccess)
+            return hip_fail(e, name);
     }
     // the table and keys once; only the time index changes from step to step
     const DrawParams base = dynamics_params(J, q, seed, stream, 0u, flags & SD_FLAG_COMPLEMENT_RNG);
@@ -666,105 +798,9 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
         hold = std::unique_lock<std::mutex>(ws->mu);
         partials = ws->p;
     }
-    DrawParams base = dynamics_params(0.0, 0.0, seed, 0u, 0u, flags & SD_FLAG_COMPLEMENT_RNG);
-    const uint32_t chunk = n_rec ? (uint32_t)(kPartialsWords / stride) : 1u;
-    const uint64_t obs_chain = 3ull * n_rec;
-    uint32_t pending = 0;
-    hipError_t e = hipSuccess;
-    // Rows of at most 64 words: whole steps, several per launch (bands with
-    // halo rows, sigma alternating between the two lattices of each chain),
-    // for all but the last step, in an even number of launches so that sigma
-    // ends where it started; the last step takes the half-step kernels, which
-    // leave tau in place.
-    const uint32_t R = band_rows(L);
-    uint32_t depth = R ? band_depth(L) : 0u;
-    if (depth && n_rec) {   // the records of one launch must fit the partial-sum buffer
-        const uint64_t per_rec = 4ull * ((uint32_t)L / R) * mc.n_chains;
-        depth = std::min<uint64_t>(depth, kPartialsWords / per_rec);
-    }
-    const bool band_ok = depth != 0 && (layout == SD_P64 || klay == kLayI8Row) && k_steps >= 3;
-    uint32_t n_fused = band_ok ? k_steps - 1u : 0u;
-    // an even number of launches of at most `depth` steps, none empty
-    uint32_t n_launch = n_fused ? (n_fused + depth - 1) / depth : 0u;
-    n_launch += n_launch % 2;
-    if (n_launch > n_fused)   // one step per launch and an odd count: leave one more step to the half-steps
-        n_launch = --n_fused;
-    if (n_fused) {
-        BandArgs ba;
-        std::memset(&ba, 0, sizeof ba);
-        for (int32_t a = 0; a < n_chains; ++a) {
-            std::memcpy(ba.T[a], mc.T[a], sizeof ba.T[a]);
-            ba.stream[a] = mc.stream[a];
-        }
-        ba.n_chains = mc.n_chains;
-        ba.L = (uint32_t)L;
-        ba.W = (uint32_t)L / 64u;
-        ba.R = R;
-        ba.bands = (uint32_t)L / R;
-        ba.shW = (uint32_t)__builtin_ctz(ba.W);
-        ba.key0 = base.key0;
-        ba.key1 = base.key1;
-        const uint32_t stride_b = 4u * ba.bands * ba.n_chains;
-        const uint32_t chunk_b = (uint32_t)(kPartialsWords / stride_b);
-        ba.rec_stride = stride_b;
-        const bool complement = (flags & SD_FLAG_COMPLEMENT_RNG) != 0;
-        uint32_t m = 0;   // steps done
-        for (uint32_t j = 0; j < n_launch && e == hipSuccess; ++j) {
-            const uint32_t steps = n_fused / n_launch + (j < n_fused % n_launch ? 1u : 0u);
-            for (int32_t a = 0; a < n_chains; ++a) {
-                ba.src[a] = j % 2 ? tau[a] : sigma[a];
-                ba.dst[a] = j % 2 ? sigma[a] : tau[a];
-            }
-            ba.t0 = (uint32_t)(2 * (step0 + m));
-            ba.steps = steps;
-            ba.threads = band_threads(R, ba.W, steps);
-            ba.rec_mask = 0;
-            uint32_t n_here = 0;
-            if (n_rec)
-                for (uint32_t s = 0; s < steps; ++s)
-                    if ((m + s + 1) % obs_every == 0) {
-                        ba.rec_mask |= 1u << s;
-                        ++n_here;
-                    }
-            if (n_here && pending + n_here > chunk_b) {
-                const uint32_t r_next = (m + obs_every) / obs_every - 1;   // first record of this launch
-                e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
-                                           r_next - pending, st);
-                pending = 0;
-                if (e != hipSuccess)
-                    break;
-            }
-            e = launch_band_step(ba, layout == SD_I8, paired, complement,
-                                 n_here ? partials + (size_t)pending * stride_b : nullptr, st);
-            m += steps;
-            pending += n_here;
-            if (e == hipSuccess && pending && j + 1 == n_launch) {
-                e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
-                                           m / obs_every - pending, st);
-                pending = 0;
-            }
-        }
-    }
-    for (uint32_t m = n_fused; m < k_steps && e == hipSuccess; ++m) {
-        const uint64_t n = step0 + m;
-        base.t = (uint32_t)(2 * n);
-        e = launch_half_step_many(klay, 0, mc, G, base, paired, nullptr, st);
-        if (e != hipSuccess)
-            break;
-        base.t = (uint32_t)(2 * n + 1);
-        const bool rec = n_rec && (m + 1) % obs_every == 0 && (m + 1) / obs_every <= n_rec;
-        e = launch_half_step_many(klay, 1, mc, G, base, paired, rec ? partials + (size_t)pending * stride : nullptr,
-                                  st);
-        if (rec && e == hipSuccess) {
-            const uint32_t r = (m + 1) / obs_every - 1;
-            ++pending;
-            if (pending == chunk || r + 1 == n_rec) {
-                e = launch_obs_finish_many(partials, mc.blocks_per_chain, mc.n_chains, pending, stride, obs,
-                                           obs_chain, r + 1 - pending, st);
-                pending = 0;
-            }
-        }
-    }
+    const bool whole_words = (layout == SD_P64 && L % 64 == 0) || klay == kLayI8Row;
+    const hipError_t e = run_many_grid(mc, G, klay, whole_words, paired, L, seed, step0, k_steps, obs, n_rec, obs_every,
+                                       flags, partials, st);
     return e == hipSuccess ? SD_OK : hip_fail(e, name);
 }
 
@@ -872,17 +908,16 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
     // candidates
     std::vector<RunChoice> cands;
     const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
-    if (ahead_size(L)) {   // drawn ahead, whatever the threads
+    uint32_t n_cu = 0;
+    size_t max_lds = 0;
+    e = device_limits(&n_cu, &max_lds);
+    if (e != hipSuccess)
+        return hip_fail(e, "sd_tune");
+    if (ahead_size(L) || band_plan(L, 1u, n_cu).bands) {   // several half-steps a launch, as the built-in rule runs them
         RunChoice c;
         c.mode = 1;
         cands.push_back(c);
-    } else if (L % 64 == 0 && n_words <= lds_max_words())
-        for (uint32_t th : {128u, 256u, 512u}) {
-            RunChoice c;
-            c.mode = 1;
-            c.threads = th;
-            cands.push_back(c);
-        }
+    }
     for (int width : {64, 32}) {
         if (width == 32 && (layout == SD_I8 || L % 64 != 0))
             continue;

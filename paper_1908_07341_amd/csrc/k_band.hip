@@ -25,8 +25,9 @@
 // the resolver or-ing the decided bits into the LDS word.  On recorded steps
 // half-step B also counts M, A, B of the band's own rows: the owner counts
 // its decided sites, the resolver the rest.
-#include "sd_kernels.hpp"
+#include <cmath>
 
+#include "sd_kernels.hpp"
 
 namespace sd {
 
@@ -81,16 +82,16 @@ __device__ __forceinline__ void band_gather(const uint64_t* src, uint32_t u, uin
 // below the threshold's low 24 bits), with its word and neighbour words.
 template <int WHICH>
 __device__ __forceinline__ uint32_t band_tail(const uint64_t* src, uint32_t u, uint32_t b, uint32_t base, uint32_t L,
-                                              uint32_t W, uint32_t shW, const DrawParams& dp,
+                                              uint32_t W, const FastDiv& divW, const DrawParams& dp,
                                               const uint32_t* T24, uint32_t& i, uint64_t& c, uint64_t& n1,
                                               uint64_t& n2) {
-    i = u >> shW;
-    const uint32_t w = u & (W - 1u);
+    i = fdiv(u, divW);
+    const uint32_t w = u - i * W;
     band_gather<WHICH>(src, u, w, W, c, n1, n2);
     uint32_t row = base + i;
     row = row >= L ? row - L : row;
     row = row >= L ? row - L : row;
-    return draw_tail24(dp, 64u * ((row << shW) + w) + b) < T24[class_at(c, n1, n2, (int)b)] ? 1u : 0u;
+    return draw_tail24(dp, 64u * (row * W + w) + b) < T24[class_at(c, n1, n2, (int)b)] ? 1u : 0u;
 }
 
 template <bool OBS>
@@ -108,7 +109,7 @@ __device__ __forceinline__ void band_count_site(uint32_t bit, uint64_t c, uint64
 template <int WHICH, bool OBS>
 __device__ __forceinline__ void band_resolve(const uint64_t* src, uint64_t* dst, const uint32_t* list, uint32_t k,
                                              uint32_t o0, uint32_t o1, uint32_t base, uint32_t L, uint32_t W,
-                                             uint32_t shW, const DrawParams& dp, const uint32_t* T24,
+                                             const FastDiv& divW, const DrawParams& dp, const uint32_t* T24,
                                              BandSums& acc) {
     band_sync_wave();
     for (uint32_t e = threadIdx.x & 63u; e < k; e += 64u) {
@@ -116,7 +117,7 @@ __device__ __forceinline__ void band_resolve(const uint64_t* src, uint64_t* dst,
         const uint32_t u = v >> 6, b = v & 63u;
         uint32_t i;
         uint64_t c, n1, n2;
-        const uint32_t bit = band_tail<WHICH>(src, u, b, base, L, W, shW, dp, T24, i, c, n1, n2);
+        const uint32_t bit = band_tail<WHICH>(src, u, b, base, L, W, divW, dp, T24, i, c, n1, n2);
         if (bit)
             atomicOr(reinterpret_cast<unsigned long long*>(&dst[u]), 1ull << b);
         if (OBS && i >= o0 && i < o1)
@@ -138,8 +139,8 @@ __device__ __forceinline__ void band_resolve(const uint64_t* src, uint64_t* dst,
 // the end.
 template <int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
 __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, uint32_t r0, uint32_t r1, uint32_t o0,
-                                          uint32_t o1, uint32_t base, uint32_t L, uint32_t W, uint32_t shW,
-                                          const DrawParams& dp, const PlaneMasks& pm, BandShared& sh,
+                                          uint32_t o1, uint32_t base, uint32_t L, uint32_t W,
+                                          const FastDiv& divW, const DrawParams& dp, const PlaneMasks& pm, BandShared& sh,
                                           BandSums& acc) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -151,9 +152,10 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
     for (uint32_t tile = wave; tile < n_tiles; tile += n_waves) {
         const uint32_t uo = 64u * tile + lane;
         const bool active = uo < n_out;
-        const uint32_t i = r0 + (uo >> shW);
-        const uint32_t w = uo & (W - 1u);
-        const uint32_t u = (r0 << shW) + uo;
+        const uint32_t io = fdiv(uo, divW);
+        const uint32_t i = r0 + io;
+        const uint32_t w = uo - io * W;
+        const uint32_t u = r0 * W + uo;
         uint64_t c = 0, n1 = 0, n2 = 0;
         if (active)
             band_gather<WHICH>(src, u, w, W, c, n1, n2);
@@ -161,7 +163,7 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
         row = row >= L ? row - L : row;
         row = row >= L ? row - L : row;
         uint64_t P[8];
-        draw_planes(dp, active ? (row << shW) + w : 0u, P);
+        draw_planes(dp, active ? row * W + w : 0u, P);
         const WordDraw wd = compare_planes<PAIRED, COMPLEMENT>(P, c, n1, n2, pm);
         uint64_t und = active ? wd.und : 0ull;
         if (active) {
@@ -184,13 +186,13 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
             }
             listed += (uint32_t)__popcll(m);
             if (listed >= 64u) {
-                band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, shW, dp, sh.T24, acc);
+                band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, divW, dp, sh.T24, acc);
                 listed = 0;
             }
         }
     }
     if (listed)
-        band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, shW, dp, sh.T24, acc);
+        band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, divW, dp, sh.T24, acc);
     if constexpr (OBS) {
         const uint32_t v[3] = {wave_sum_dpp(acc.pc), wave_sum_dpp(acc.dpair), wave_sum_dpp(acc.dself)};
         if (lane == 0) {
@@ -213,14 +215,15 @@ __global__ __launch_bounds__(kBandMaxThreads) void k_band_step(BandArgs ba, int6
     __shared__ BandShared sh;
     const uint32_t chain = blockIdx.x / ba.bands;
     const uint32_t band = blockIdx.x - chain * ba.bands;
-    const uint32_t L = ba.L, W = ba.W, R = ba.R, n = ba.steps;
-    const uint32_t a = band * R;
+    const uint32_t L = ba.L, W = ba.W, n = ba.steps;
+    const uint32_t a = band * L / ba.bands;               // rows [a, a + R)
+    const uint32_t R = (band + 1u) * L / ba.bands - a;
     const uint32_t H = R + 2u * n;                        // LDS rows: lattice rows a - n .. a + R + n - 1
     const uint32_t base = a + (n / L + 1u) * L - n;       // lattice row of LDS row 0, plus a multiple of L
     const uint32_t base_mod = base % L;
     for (uint32_t q = threadIdx.x; q < H * W; q += blockDim.x) {
-        const uint32_t i = q >> ba.shW;
-        const uint32_t w = q & (W - 1u);
+        const uint32_t i = fdiv(q, ba.divW);
+        const uint32_t w = q - i * W;
         const uint32_t row = (base_mod + i) % L;
         if constexpr (INT8)
             sh.sig[q] = load_bits64_i8(static_cast<const int8_t*>(ba.src[chain]) + (size_t)row * L + 64u * w);
@@ -247,15 +250,15 @@ __global__ __launch_bounds__(kBandMaxThreads) void k_band_step(BandArgs ba, int6
         BandSums acc;
         dp.t = ba.t0 + 2u * (s - 1u);
         // tau on rows s .. H - s (its sigma rows below are valid from s - 1)
-        band_half<0, PAIRED, COMPLEMENT, false>(sh.sig, sh.tau, s, H - s + 1u, 0, 0, base_mod, L, W, ba.shW, dp,
+        band_half<0, PAIRED, COMPLEMENT, false>(sh.sig, sh.tau, s, H - s + 1u, 0, 0, base_mod, L, W, ba.divW, dp,
                                                 pm, sh, acc);
         dp.t += 1u;
         const bool recorded = OBS && ((ba.rec_mask >> (s - 1u)) & 1u);
         if (recorded) {
-            band_half<1, PAIRED, COMPLEMENT, true>(sh.tau, sh.sig, s, H - s, n, n + R, base_mod, L, W, ba.shW, dp,
+            band_half<1, PAIRED, COMPLEMENT, true>(sh.tau, sh.sig, s, H - s, n, n + R, base_mod, L, W, ba.divW, dp,
                                                    pm, sh, acc);
         } else {
-            band_half<1, PAIRED, COMPLEMENT, false>(sh.tau, sh.sig, s, H - s, 0, 0, base_mod, L, W, ba.shW, dp, pm,
+            band_half<1, PAIRED, COMPLEMENT, false>(sh.tau, sh.sig, s, H - s, 0, 0, base_mod, L, W, ba.divW, dp, pm,
                                                     sh, acc);
         }
         if constexpr (OBS) {
@@ -300,36 +303,38 @@ void launch_band_t(const BandArgs& ba, bool paired, bool complement, int64_t* pa
 
 }  // namespace
 
-// Rows per band and steps per launch, measured on five chains with records
-// every step: the small lattices leave most of the device idle, so they take
-// narrow bands and many steps per launch (latency bound: the redundant halo
-// rows cost nothing); the larger ones are issue bound, and the halo's share
-// of the work, (2 steps - 1) / (2 R) of a step, decides.
-uint32_t band_rows(int32_t L) {
-    if (L < 64 || L % 64 != 0)
-        return 0;
+// Bands per chain and steps per launch.  Every workgroup computes its rows and
+// on average `steps` halo rows, 2 (R + steps) W words a step at about
+// kWordNs; a launch costs about kLaunchNs besides (dispatch, the load of sigma,
+// its store).  So steps is near the root of kLaunchNs / (2 W kWordNs), and the
+// bands fill the CUs evenly: n_cu / n_chains bands a chain, or a multiple where
+// a band would not fit the LDS.  A fixed 16 rows a band gave five 1024^2 chains
+// 320 workgroups, two on some CUs and one on others, and 8 rows gave 2048^2
+// half as many halo rows again as rows; us per half-step, five chains: 1024^2
+// 3.17 -> 2.41, 2048^2 7.0 -> 5.3, 4096^2 29.6 -> 15.7 (one 5.1 -> 3.9); sides
+// that are no power of two took a launch per half-step, 640^2 5.2 -> 1.7.
+// kLaunchNs from 2000 to 12000 moves these by at most 7%.
+BandPlan band_plan(int32_t L, uint32_t n_chains, uint32_t n_cu) {
+    BandPlan p{0, 0};
+    if (L < 64 || L % 64 != 0 || L > 64 * (int32_t)kBandMaxWords)
+        return p;
     const uint32_t W = (uint32_t)L / 64u;
-    switch (W) {
-        case 1:
-        case 2:
-        case 4:
-            return 32u / W;   // half a tile of own words
-        case 8:
-            return 16u;       // two tiles
-        case 16:
-            return 16u;       // four tiles
-        case 32:
-            return 8u;
-        case 64:
-            return 4u;
-        default:
-            return 0;         // rows of more than 64 words, or not dividing 256
+    constexpr float kLaunchNs = 6000.0f, kWordNs = 2.25f;
+    uint32_t depth = (uint32_t)(std::sqrt(kLaunchNs / (2.0f * (float)W * kWordNs)) + 0.5f);
+    depth = depth < 1u ? 1u : depth > kBandMaxSteps ? kBandMaxSteps : depth;
+    const uint32_t share = n_cu / n_chains ? n_cu / n_chains : 1u;
+    for (uint32_t m = 1; m <= 64u; ++m) {
+        const uint32_t bands = m * share < (uint32_t)L ? m * share : (uint32_t)L;
+        const uint32_t R = ((uint32_t)L + bands - 1u) / bands;
+        if ((R + 2u * depth) * W <= kBandMaxRowsWords) {
+            p.bands = bands;
+            p.depth = depth;
+            return p;
+        }
+        if (bands == (uint32_t)L)
+            break;
     }
-}
-
-uint32_t band_depth(int32_t L) {
-    const uint32_t W = (uint32_t)L / 64u;
-    return W <= 16u ? 8u : W == 32u ? 4u : 1u;
+    return p;
 }
 
 uint32_t band_threads(uint32_t R, uint32_t W, uint32_t steps) {

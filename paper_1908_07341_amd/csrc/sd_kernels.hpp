@@ -95,13 +95,14 @@ hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, co
 hipError_t launch_obs_finish_many(const int64_t* partials, uint32_t n_blocks, uint32_t n_chains, uint32_t n_rec,
                                   uint32_t stride, int64_t* obs, uint64_t obs_chain, uint32_t rec0, hipStream_t st);
 // Whole steps of several chains, several per launch (lattices whose rows are
-// at most 64 words, L = 64 * W with W dividing 256): workgroup (chain, band)
-// runs `steps` steps of R = band_rows(L) rows (R * W at most 256) from sigma
-// in src, with `steps` rows of halo on each side, writing the last sigma of
-// its rows to dst (the other lattice of the pair).  src, dst, t0, steps and
-// rec_mask change from launch to launch.
+// whole 64-bit words, at most kBandMaxWords of them): workgroup (chain, band)
+// runs `steps` steps of the band's rows, [band L / bands, (band + 1) L / bands),
+// from sigma in src, with `steps` rows of halo on each side, writing the last
+// sigma of its rows to dst (the other lattice of the pair).  src, dst, t0,
+// steps and rec_mask change from launch to launch.
 constexpr uint32_t kBandMaxSteps = 8;
-constexpr uint32_t kBandMaxRowsWords = 256 + 2 * kBandMaxSteps * 64;   // (R + 2 steps) * W
+constexpr uint32_t kBandMaxWords = 64;           // words of a row
+constexpr uint32_t kBandMaxRowsWords = 2304;     // (R + 2 steps) * W, two lattices of 18 KB in LDS
 constexpr uint32_t kBandMaxThreads = 768;
 struct BandArgs {
     const void* src[kManyMax];
@@ -109,9 +110,9 @@ struct BandArgs {
     uint32_t T[kManyMax][6];
     uint32_t stream[kManyMax];
     uint32_t n_chains;
-    uint32_t bands;      // L / R per chain
-    uint32_t L, W, R;
-    uint32_t shW;        // log2 W (W divides 256)
+    uint32_t bands;      // per chain
+    uint32_t L, W;
+    FastDiv divW;
     uint32_t key0, key1;
     uint32_t t0;         // half-step index of the launch's first half-step A
     uint32_t steps;      // 1 .. kBandMaxSteps
@@ -119,10 +120,12 @@ struct BandArgs {
     uint32_t rec_mask;   // bit s: record step s of the launch
     uint32_t rec_stride; // int64 between the partial sums of consecutive records
 };
-// Rows per band for L, or 0 when L does not take the whole-step kernel.
-uint32_t band_rows(int32_t L);
-// Steps per launch of the whole-step kernel for lattices of side L.
-uint32_t band_depth(int32_t L);
+// Bands per chain (0: L does not take the whole-step kernel) and steps per
+// launch for n_chains chains on n_cu CUs.
+struct BandPlan {
+    uint32_t bands, depth;
+};
+BandPlan band_plan(int32_t L, uint32_t n_chains, uint32_t n_cu);
 // Workgroup size for `steps` steps of bands of R rows of W words.
 uint32_t band_threads(uint32_t R, uint32_t W, uint32_t steps);
 // partials (non-null when rec_mask is not zero): the sums of recorded step k

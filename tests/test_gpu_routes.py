@@ -247,3 +247,31 @@ def test_diagonal_correlations_one_or_many_workgroups(oracle, L, layout):
         out = torch.full((2, lmax + 1), 12345, dtype=torch.int64, device="cuda")
         sd.sd_corr_diag(dev, L, layout, lmax, out)
         assert np.array_equal(out.cpu().numpy().reshape(-1), oracle.corr_diag(lat, lmax).reshape(-1))
+
+
+@pytest.mark.parametrize("L,layout,n,k", [(384, sd.SD_P64, 1, 3), (448, sd.SD_I8, 7, 20), (512, sd.SD_P64, 1, 30),
+                                          (576, sd.SD_I8, 5, 9), (1024, sd.SD_P64, 16, 5), (2112, sd.SD_P64, 1, 12),
+                                          (4032, sd.SD_P64, 3, 4), (4096, sd.SD_I8, 1, 6)])
+def test_bands_of_uneven_rows(L, layout, n, k):
+    # whole steps in bands whose rows the side does not divide evenly, from two
+    # rows a band to as many as the LDS holds, rows of 6 to 64 words, shapes
+    # that need several bands per CU; against the half-steps of the grid kernels
+    print(f"bands L={L} layout={layout} n={n}", flush=True)
+    J, q, streams = [0.3 + 0.05 * a for a in range(n)], [0.9] * n, [a + 2 for a in range(n)]
+    sig = []
+    for a in range(n):
+        x = sd.new_lattice(L, layout)
+        sd.sd_init(x, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, a)
+        sig.append(x)
+    tau, first = [torch.zeros_like(x) for x in sig], [x.clone() for x in sig]
+    obs = torch.full((n, k, 3), -1, dtype=torch.int64, device="cuda")
+    sd.sd_run_many(sig, tau, L, layout, J, q, SEED, streams, 2, k, obs, 1)
+    for a in range(n):
+        one, two = first[a].clone(), torch.zeros_like(first[a])
+        rec = torch.empty((k, 3), dtype=torch.int64, device="cuda")
+        sd.sd_run(one, two, L, layout, J[a], q[a], SEED, streams[a], 2, k, rec, 1, sd.SD_FLAG_GLOBAL_KERNELS)
+        assert torch.equal(one, sig[a]) and torch.equal(two, tau[a]) and torch.equal(rec, obs[a])
+        if a == 0:
+            one, two = first[0].clone(), torch.zeros_like(first[0])
+            sd.sd_run(one, two, L, layout, J[0], q[0], SEED, streams[0], 2, k, rec, 1)
+            assert torch.equal(one, sig[0]) and torch.equal(two, tau[0]) and torch.equal(rec, obs[0])
