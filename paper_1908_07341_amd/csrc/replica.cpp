@@ -1,7 +1,7 @@
 // Host side of the replica-coded chains: per-replica threshold data and the
 // C-ABI entry points.
+#include <algorithm>
 #include <cmath>
-#include <cstring>
 
 #include "sd_host.hpp"
 #include "sd_replica.hpp"
@@ -10,15 +10,22 @@ namespace sd {
 
 ReplicaParams replica_params(const double* J, const double* q) {
     ReplicaParams rp;
-    std::memset(&rp, 0, sizeof rp);
+    uint64_t key[3][kReplicas];   // threshold, replica
     for (uint32_t r = 0; r < kReplicas; ++r) {
         uint32_t T[6];
         threshold_table(J[r], q[r], T);
-        for (int m = 0; m < 8; ++m)
-            for (int k = 0; k < 3; ++k)
-                rp.S[m][k] |= (uint64_t)((T[k] >> (31 - m)) & 1u) << r;
-        for (int idx = 0; idx < 6; ++idx)
-            rp.T24[idx][r] = paired_tail(T, idx);
+        for (int k = 0; k < 3; ++k) {
+            rp.top[k][r] = (uint8_t)(T[k] >> 24);
+            key[k][r] = ((uint64_t)T[k] << 32) | r;
+        }
+    }
+    for (int k = 0; k < 3; ++k) {
+        std::sort(key[k], key[k] + kReplicas);
+        rp.from[k][kReplicas] = 0;
+        for (uint32_t n = kReplicas; n-- > 0;) {
+            rp.T[k][n] = (uint32_t)(key[k][n] >> 32);
+            rp.from[k][n] = rp.from[k][n + 1] | (1ull << (uint32_t)key[k][n]);
+        }
     }
     return rp;
 }

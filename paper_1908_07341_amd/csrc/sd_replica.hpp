@@ -10,8 +10,9 @@ constexpr uint32_t kReplicas = 64;
 
 // Per-replica threshold data, passed by value to the kernels.
 struct ReplicaParams {
-    uint64_t S[8][3];             // bit r: bit (31 - m) of T_r[k], leader classes k = 0, 1, 2
-    uint32_t T24[6][kReplicas];   // paired_tail(T_r, idx)
+    uint64_t from[3][kReplicas + 1];   // the replicas from position n of T[k] on
+    uint32_t T[3][kReplicas];          // T_r[k] of all replicas in ascending order, leader classes k = 0, 1, 2
+    uint8_t top[3][kReplicas];         // top byte of T_r[k] by replica
 };
 
 ReplicaParams replica_params(const double* J, const double* q);

@@ -275,3 +275,53 @@ def test_bands_of_uneven_rows(L, layout, n, k):
             one, two = first[0].clone(), torch.zeros_like(first[0])
             sd.sd_run(one, two, L, layout, J[0], q[0], SEED, streams[0], 2, k, rec, 1)
             assert torch.equal(one, sig[0]) and torch.equal(two, tau[0]) and torch.equal(rec, obs[0])
+
+
+@pytest.mark.parametrize("L,q", [(8, 0.0), (24, 1.0), (512, 1.0), (720, 0.4), (1024, 1.0), (1456, 1.0)])
+def test_replica_tables_and_batches(L, q):
+    # 64 replicas against single chains at the sizes where the batch of a
+    # wavefront changes (one group, an odd count of groups, 2, 2 with a rest,
+    # 8 and 16 groups), with thresholds that all replicas share (q alone sets
+    # the classes of unlike neighbours), that share a top byte (strong
+    # coupling), and that the largest fields saturate.  Whole numbers: exact.
+    print(f"replica tables L={L} q={q}", flush=True)
+    J = [1.5 * r / 63 for r in range(62)] + [12.0, -3.0]
+    qs = [q] * 64
+    rng = np.random.default_rng(L)
+    info = np.iinfo(np.int64)
+    start = rng.integers(info.min, info.max, size=L * L, dtype=np.int64, endpoint=True)
+    sig = torch.from_numpy(start).cuda()
+    tau = torch.zeros_like(sig)
+    sd.sd_replica_run(sig, tau, L, J, qs, 77, 3, 5, 3)
+
+    def replica(words, r):
+        return (2 * ((words.view(np.uint64) >> np.uint64(r)) & np.uint64(1)).astype(np.int8) - 1).reshape(L, L)
+
+    for r in (0, 1, 17, 31, 32, 45, 61, 62, 63):
+        s1, t1 = sd.new_lattice(L, sd.SD_P64), sd.new_lattice(L, sd.SD_P64)
+        s1.view(torch.uint8).view(-1).copy_(torch.from_numpy(inputs.pack_bits(replica(start, r))))
+        sd.sd_run(s1, t1, L, sd.SD_P64, J[r], q, 77, 3, 5, 3, None, 0)
+        assert np.array_equal(inputs.unpack_bits(s1.cpu().numpy(), L), replica(sig.cpu().numpy(), r)), r
+        assert np.array_equal(inputs.unpack_bits(t1.cpu().numpy(), L), replica(tau.cpu().numpy(), r)), r
+
+
+@pytest.mark.parametrize("L", [8, 24, 120, 128, 136, 264])
+@pytest.mark.parametrize("fill", ["random", "plus", "opposed"])
+def test_replica_observables_at_counter_edges(L, fill):
+    # less than one site per lane, one workgroup (16384 sites) to the site,
+    # one site row more, several; full counters of every quantity.  Whole
+    # numbers: exact.
+    print(f"replica observables L={L} {fill}", flush=True)
+    rng = np.random.default_rng(L)
+    info = np.iinfo(np.int64)
+    if fill == "random":
+        sw, tw = (rng.integers(info.min, info.max, size=L * L, dtype=np.int64, endpoint=True) for _ in range(2))
+    else:
+        sw = np.full(L * L, -1, dtype=np.int64)
+        tw = sw.copy() if fill == "plus" else np.zeros_like(sw)
+    out = torch.empty((64, 3), dtype=torch.int64, device="cuda")
+    sd.sd_replica_observe(torch.from_numpy(sw).cuda(), torch.from_numpy(tw).cuda(), L, out)
+    s, t = (inputs.unpack_replicas(x.view(np.uint64), L).reshape(64, L, L).astype(np.int64) for x in (sw, tw))
+    up, right = np.roll(t, -1, axis=1), np.roll(t, -1, axis=2)
+    want = np.stack([s.sum((1, 2)), (s * (up + right)).sum((1, 2)), (s * t).sum((1, 2))], axis=1)
+    assert np.array_equal(out.cpu().numpy(), want)
