@@ -27,15 +27,24 @@ namespace sd {
 
 namespace {
 
+// The lattices are written as 64-bit words and read as dwords, too.
+typedef uint32_t __attribute__((may_alias)) lds_dword;
+
 // BITS: rows need not start on a word (L % 64 != 0, L % 8 == 0); neighbours
-// are windows of the lattice's bit string.
+// are windows of the lattice's bit string, and the word behind the lattice
+// repeats its first, so that no window wraps inside.
 template <bool BITS>
 struct HalfCtx {
     const uint64_t* src;
     uint64_t* dst;
     uint32_t L, W, n_words;
     FastDiv divW;   // division by W = L / 64 (rows of whole words)
-    FastDiv divL;   // division by L (bit strings)
+    FastDiv divL;   // division by L
+    // bit strings: where the first row starts in the lane's first word (it
+    // does not if >= 64), and the rows that start in a word whose first does
+    // at bit 0
+    uint32_t pos0;
+    uint64_t starts;
 };
 
 // Rows of whole words: word g = j * W + w (row j, column word w) and its
@@ -58,15 +67,63 @@ __device__ __forceinline__ void gather_lds_g(const HalfCtx<BITS>& h, uint32_t g,
     }
 }
 
-template <int WHICH, bool BITS>
-__device__ __forceinline__ void gather_lds(const HalfCtx<BITS>& h, uint32_t g, uint64_t& c, uint64_t& n1,
-                                           uint64_t& n2) {
-    if constexpr (BITS) {
-        gather_bits<WHICH>(h.src, h.L, h.n_words, h.divL, g, c, n1, n2);
+// Bit strings: word g, whose first row starts at bit pos.  Every window is
+// three dwords and two funnel shifts: its offset from the word is the same for
+// all words.  (64-bit words, a division per word for the row start and wrapped
+// indices took 60 operations more: 200^2, 1600 chains: 4.96 -> @@BITS@@ ms.)
+template <int WHICH>
+__device__ __forceinline__ void gather_lds_bits(const HalfCtx<true>& h, uint32_t g, uint32_t pos, uint64_t& c,
+                                                uint64_t& n1, uint64_t& n2) {
+    const lds_dword* d = reinterpret_cast<const lds_dword*>(h.src);
+    const uint32_t n = 2u * h.n_words, N = 64u * h.n_words;
+    c = h.src[g];
+    const uint32_t c_lo = (uint32_t)c, c_hi = (uint32_t)(c >> 32);
+    auto window = [&](uint32_t off, uint32_t& lo, uint32_t& hi) __attribute__((always_inline)) {
+        uint32_t at = 2u * g + (off >> 5);
+        at = at < at - n ? at : at - n;   // at mod n: at - n wraps to a large value while at < n
+        const uint32_t w0 = d[at], w1 = d[at + 1u], w2 = d[at + 2u];
+        lo = __builtin_amdgcn_alignbit(w1, w0, off & 31u);
+        hi = __builtin_amdgcn_alignbit(w2, w1, off & 31u);
+    };
+    uint32_t n1_lo, n1_hi, lo, hi, wrap_lo, wrap_hi;
+    if constexpr (WHICH == 0) {
+        window(N - h.L, n1_lo, n1_hi);
+        window(h.L - 1u, wrap_lo, wrap_hi);
+        const uint32_t before = 2u * g - 1u;
+        const uint32_t prev = d[before < n - 1u ? before : n - 1u];
+        lo = __builtin_amdgcn_alignbit(c_lo, prev, 31);
+        hi = __builtin_amdgcn_alignbit(c_hi, c_lo, 31);
     } else {
-        const uint32_t j = fdiv(g, h.divW);
-        gather_lds_g<WHICH>(h, g, j, g - j * h.W, c, n1, n2);
+        window(h.L, n1_lo, n1_hi);
+        window(N + 1u - h.L, wrap_lo, wrap_hi);
+        const uint32_t next = d[2u * g + 2u];
+        lo = __builtin_amdgcn_alignbit(c_hi, c_lo, 1);
+        hi = __builtin_amdgcn_alignbit(next, c_hi, 1);
+        pos = pos - 1u < h.L - 1u ? pos - 1u : h.L - 1u;   // the rows' last columns
     }
+    const uint64_t edge = pos < 64u ? h.starts << pos : 0ull;
+    const uint32_t e_lo = (uint32_t)edge, e_hi = (uint32_t)(edge >> 32);
+    n1 = (uint64_t)n1_lo | ((uint64_t)n1_hi << 32);
+    n2 = (uint64_t)((lo & ~e_lo) | (wrap_lo & e_lo)) | ((uint64_t)((hi & ~e_hi) | (wrap_hi & e_hi)) << 32);
+}
+
+// The partner and neighbour bits of site s.
+template <int WHICH, bool BITS>
+__device__ __forceinline__ void site_bits(const HalfCtx<BITS>& h, uint32_t s, uint32_t& c, uint32_t& n1, uint32_t& n2) {
+    const lds_dword* d = reinterpret_cast<const lds_dword*>(h.src);
+    const uint32_t N = 64u * h.n_words;
+    const uint32_t i = s - fdiv(s, h.divL) * h.L;
+    uint32_t s1, s2;
+    if constexpr (WHICH == 0) {
+        s1 = s - h.L < s - h.L + N ? s - h.L : s - h.L + N;   // s - L, + N where that is negative
+        s2 = s - 1u + (i == 0 ? h.L : 0u);
+    } else {
+        s1 = s + h.L < s + h.L - N ? s + h.L : s + h.L - N;
+        s2 = s + 1u - (i == h.L - 1u ? h.L : 0u);
+    }
+    c = (d[s >> 5] >> (s & 31u)) & 1u;
+    n1 = (d[s1 >> 5] >> (s1 & 31u)) & 1u;
+    n2 = (d[s2 >> 5] >> (s2 & 31u)) & 1u;
 }
 
 // Per-wavefront list of undecided sites (64 * word + bit).  A round of
@@ -96,16 +153,21 @@ __device__ __forceinline__ void resolve_list(const HalfCtx<BITS>& h, const DrawP
                                              WaveWordList& wl, uint32_t n, ObsSums& acc) {
     for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
         const uint32_t v = wl.site[e];
-        const uint32_t g = v >> 6, b = v & 63u;
-        uint64_t c, n1, n2;
-        gather_lds<WHICH>(h, g, c, n1, n2);
-        const uint32_t bit = draw_tail24(dp, v) < T24[class_at(c, n1, n2, (int)b)] ? 1u : 0u;
-        if (bit)
-            atomicOr(reinterpret_cast<unsigned long long*>(&h.dst[g]), 1ull << b);
+        uint32_t c, n1, n2;
+        site_bits<WHICH>(h, v, c, n1, n2);
+        const uint32_t bit = draw_tail24(dp, v) < T24[2u * (n1 + n2) + c] ? 1u : 0u;
+        if (bit) {
+            lds_dword* to = reinterpret_cast<lds_dword*>(h.dst) + (v >> 5);
+            atomicOr(to, 1u << (v & 31u));
+            if constexpr (BITS) {
+                if (v < 64u)   // the copy of the first word
+                    atomicOr(to + 2u * h.n_words, 1u << (v & 31u));
+            }
+        }
         if constexpr (OBS) {
             acc.pc += bit;
-            acc.dpair += (bit ^ (uint32_t)((n1 >> b) & 1u)) + (bit ^ (uint32_t)((n2 >> b) & 1u));
-            acc.dself += bit ^ (uint32_t)((c >> b) & 1u);
+            acc.dpair += (bit ^ n1) + (bit ^ n2);
+            acc.dself += bit ^ c;
         }
     }
 }
@@ -145,7 +207,12 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
     // rows of whole words: (row, column word) of the lane's word, stepped by
     // the 64 * n_waves words between a wavefront's tiles
     uint32_t j = 0, w = 0, step_rows = 0, step_cols = 0;
-    if constexpr (!BITS) {
+    // bit strings: where the first row starts in the lane's word
+    uint32_t pos = 0, pos_step = 0;
+    if constexpr (BITS) {
+        pos = h.pos0;
+        pos_step = (64u * 64u * n_waves) % h.L;
+    } else {
         const uint32_t g0 = 64u * (threadIdx.x >> 6) + lane;
         j = fdiv(g0, h.divW);
         w = g0 - j * h.W;
@@ -158,14 +225,14 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
         // rows of whole words hold L * L / 64 = 64 * L * (L / 64) words: every
         // tile is full
         const bool active = !BITS || g < h.n_words;
-        uint64_t c = 0, n1 = 0, n2 = 0;
-        if (active) {
-            if constexpr (BITS)
-                gather_lds<WHICH>(h, g, c, n1, n2);
-            else
-                gather_lds_g<WHICH>(h, g, j, w, c, n1, n2);
-        }
-        if constexpr (!BITS) {
+        const uint32_t ga = active ? g : h.n_words - 1u;   // a word to read and draw in any case
+        uint64_t c, n1, n2;
+        if constexpr (BITS) {
+            gather_lds_bits<WHICH>(h, ga, pos, c, n1, n2);
+            // later by pos_step, mod L
+            pos = pos - pos_step < pos - pos_step + h.L ? pos - pos_step : pos - pos_step + h.L;
+        } else {
+            gather_lds_g<WHICH>(h, ga, j, w, c, n1, n2);
             w += step_cols;
             j += step_rows;
             if (w >= h.W) {
@@ -174,11 +241,15 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
             }
         }
         uint64_t P[8];
-        draw_planes(dp, active ? g : 0u, P);
+        draw_planes(dp, ga, P);
         const WordDraw wd = compare_planes<PAIRED, COMPLEMENT>(P, c, n1, n2, pm);
         uint64_t und = active ? wd.und : 0ull;
         if (active) {
             h.dst[g] = wd.lt;
+            if constexpr (BITS) {
+                if (tile == 0 && lane == 0)   // the copy of the first word
+                    h.dst[h.n_words] = wd.lt;
+            }
             if constexpr (OBS) {
                 acc.pc += __popcll(wd.lt);
                 acc.dpair += __popcll((wd.lt ^ n1) & ~und) + __popcll((wd.lt ^ n2) & ~und);
@@ -317,8 +388,8 @@ __device__ __forceinline__ void batch_chains_body(const BatchArgs& a) {
     __shared__ ChainShared s_ch;
     __shared__ unsigned long long s_obs[3];   // a recorded step's sums, added by every wavefront
     uint64_t* sig = smem;
-    uint64_t* tau = smem + a.max_words;
-    WaveWordList& wl = reinterpret_cast<WaveWordList*>(tau + a.max_words)[threadIdx.x >> 6];
+    uint64_t* tau = smem + a.max_words + 1u;
+    WaveWordList& wl = reinterpret_cast<WaveWordList*>(tau + a.max_words + 1u)[threadIdx.x >> 6];
 
     if (threadIdx.x == 0) {
         s_queue = 0;
@@ -386,6 +457,15 @@ __device__ __forceinline__ void batch_chains_body(const BatchArgs& a) {
         hA.src = sig; hA.dst = tau;
         hB.src = tau; hB.dst = sig;
         const uint32_t n_words = hA.n_words;
+        if constexpr (BITS) {
+            const uint32_t s = 64u * threadIdx.x;   // the lane's first word starts at column s mod L
+            const uint32_t m = s - fdiv(s, hA.divL) * cd.L;
+            hA.pos0 = hB.pos0 = m ? cd.L - m : 0u;
+            uint64_t starts = 1u;
+            for (uint32_t b = cd.L; b < 64u; b += cd.L)
+                starts |= 1ull << b;
+            hA.starts = hB.starts = starts;
+        }
 
         // load sigma (packed words, or int8 bytes converted to bits)
         if (a.int8_io) {
@@ -403,6 +483,8 @@ __device__ __forceinline__ void batch_chains_body(const BatchArgs& a) {
 #pragma unroll
             for (int i = 0; i < 6; ++i)
                 s_ch.T24[i] = PAIRED ? paired_tail(cd.T, i) : cd.T[i] & 0xFFFFFFu;
+            if constexpr (BITS)
+                sig[n_words] = sig[0];   // word 0 is this thread's
         }
         __syncthreads();
 
@@ -479,7 +561,7 @@ __global__ void k_zero_u32(uint32_t* p, uint32_t n) {
 }  // namespace
 
 size_t batch_lds_bytes(uint32_t max_words, uint32_t threads) {
-    return (size_t)2 * max_words * sizeof(uint64_t) + (size_t)((threads + 63u) / 64u) * sizeof(WaveWordList);
+    return (size_t)2 * (max_words + 1u) * sizeof(uint64_t) + (size_t)((threads + 63u) / 64u) * sizeof(WaveWordList);
 }
 
 template <bool BITS>

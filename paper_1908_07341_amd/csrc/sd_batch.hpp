@@ -61,8 +61,9 @@ struct BatchArgs {
 // compare takes at most 512 threads).
 constexpr uint32_t kBatchMaxThreads = 640;
 
-// Dynamic LDS of a launch: the two lattice buffers and one list of undecided
-// words per wavefront of a threads-sized workgroup.
+// Dynamic LDS of a launch: the two lattice buffers, each with one word behind
+// it, and one list of undecided sites per wavefront of a threads-sized
+// workgroup.
 constexpr uint32_t kMomentWords = 5;
 
 // 64-site words of an L x L lattice (L % 8 == 0).
