@@ -284,6 +284,13 @@ hipError_t launch_trajectories_lds(const void* sigma0, void* traj, uint32_t n_tr
     a.paired = a.single.paired;
     a.traj = static_cast<uint8_t*>(traj);
     a.traj_chain_bytes = (2ull * k_steps + 1ull) * a.max_words * sizeof(uint64_t);
+    if (a.paired && a.max_words <= kRecordedMaxWords) {
+        int dev = 0, n_cu = 1;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+        return e == hipSuccess ? launch_batch_recorded(a, (uint32_t)n_cu, st) : e;
+    }
     hipError_t e = batch_kernel_attributes(batch_lds_bytes(a.max_words, threads));
     if (e != hipSuccess)
         return e;

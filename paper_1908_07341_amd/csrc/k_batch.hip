@@ -70,7 +70,8 @@ __device__ __forceinline__ void gather_lds_g(const HalfCtx<BITS>& h, uint32_t g,
 // Bit strings: word g, whose first row starts at bit pos.  Every window is
 // three dwords and two funnel shifts: its offset from the word is the same for
 // all words.  (64-bit words, a division per word for the row start and wrapped
-// indices took 60 operations more: 200^2, 1600 chains: 4.96 -> @@BITS@@ ms.)
+// indices took 50 operations more: 200^2, 1600 chains, 200 recorded steps:
+// 4.96 -> 4.44 ms.)
 template <int WHICH>
 __device__ __forceinline__ void gather_lds_bits(const HalfCtx<true>& h, uint32_t g, uint32_t pos, uint64_t& c,
                                                 uint64_t& n1, uint64_t& n2) {
@@ -553,6 +554,202 @@ __global__ __launch_bounds__(512) void k_batch_chains_general(BatchArgs a) {
     batch_chains_body<COMPLEMENT, false, BITS>(a);
 }
 
+// Recorded trajectories of lattices with at most one word per lane of a
+// workgroup: chain blockIdx.x of the n_uniform chains, every half-step's
+// lattice written to a.traj.
+//
+// A half-step has two phases.  In the first every lane compares its word with
+// the planes it holds and lists its undecided sites in one list for the
+// workgroup; in the second the first lanes resolve the list, one site each,
+// and every lane draws the planes of the next half-step, which do not depend
+// on the lattice.  So a tail's chain of reads and its Philox call hide behind
+// the draws, and the resolvers' lanes are all busy: with a list per wavefront
+// only a quarter of them is, as about 16 of a tile's 4096 sites are undecided.
+// The finished word is written out by the lane that reads it as its partner
+// word a half-step later.  Lattices that leave most of a CU's wavefronts idle
+// draw with SPLIT lanes per word, 4 / SPLIT Philox calls each, and pass the
+// planes through LDS.
+// Bound by the vector unit (82% of its issue slots).  256 chains, one
+// workgroup per CU, per half-step: 256^2 2.95 us with a list per wavefront and
+// two tiles per wavefront (2.9 with one), 2.67 here; 200^2 4.1 -> 2.3; 128^2
+// 1.60 -> 1.32; 32^2 2.0 -> 1.2.
+__host__ __device__ inline uint32_t recorded_list_cap(uint32_t n_words) {
+    // a quarter of a site per word is listed on average; what does not fit is
+    // resolved by the lane that found it
+    return n_words / 4u + 32u;
+}
+
+template <int WHICH, bool BITS>
+__device__ __forceinline__ void resolve_site(const HalfCtx<BITS>& h, const DrawParams& dp, const uint32_t* T24,
+                                             uint32_t v) {
+    uint32_t c, n1, n2;
+    site_bits<WHICH>(h, v, c, n1, n2);
+    if (draw_tail24(dp, v) < T24[2u * (n1 + n2) + c]) {
+        lds_dword* to = reinterpret_cast<lds_dword*>(h.dst) + (v >> 5);
+        atomicOr(to, 1u << (v & 31u));
+        if constexpr (BITS) {
+            if (v < 64u)   // the copy of the first word
+                atomicOr(to + 2u * h.n_words, 1u << (v & 31u));
+        }
+    }
+}
+
+// What a workgroup keeps in LDS besides its lattices.
+struct RecordedShared {
+    uint32_t* list;    // undecided sites of the half-step, up to cap
+    uint4* planes;     // SPLIT > 1: the words of call p for word g at p * lanes + g
+    uint32_t cap, lanes;
+    uint32_t* counts;   // by WHICH: sites listed
+    const uint32_t* T24;
+};
+
+// The planes of word g: SPLIT == 1 in P, else this lane's share of the calls
+// to LDS.
+template <int SPLIT>
+__device__ __forceinline__ void recorded_draw(const DrawParams& dp, uint32_t g, uint32_t lane_g, uint32_t part,
+                                              uint64_t (&P)[8], const RecordedShared& sh) {
+    if constexpr (SPLIT == 1) {
+        draw_planes(dp, g, P);
+    } else {
+#pragma unroll
+        for (uint32_t k = 0; k < 4u / SPLIT; ++k) {
+            const uint32_t p = part * (4u / SPLIT) + k;
+            const U4 x = philox10_uuuv(dp.stream, dp.t | (p << 30), dp.tag2, g, dp.key0, dp.key1);
+            sh.planes[p * sh.lanes + lane_g] = make_uint4(x.x0, x.x1, x.x2, x.x3);
+        }
+    }
+}
+
+// One half-step from the planes of dp.t, after which those of dp.t + 1 are
+// drawn.  Wavefronts with part > 0 only draw and resolve.
+template <int WHICH, bool BITS, int SPLIT>
+__device__ __forceinline__ void recorded_half_step(const HalfCtx<BITS>& h, DrawParams& dp, uint32_t code, uint32_t g,
+                                                   uint32_t part, uint32_t j, uint32_t w, uint64_t (&P)[8],
+                                                   uint64_t* record, const RecordedShared& sh) {
+    const bool active = g < h.n_words;
+    const uint32_t ga = active ? g : h.n_words - 1u;
+    if (threadIdx.x == 0)
+        sh.counts[1 - WHICH] = 0;   // last read before the barrier that ended the previous half-step
+    if (SPLIT == 1 || part == 0) {
+        if constexpr (SPLIT > 1) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const uint4 x = sh.planes[p * sh.lanes + g];
+                P[2 * p] = (uint64_t)x.x | ((uint64_t)x.y << 32);
+                P[2 * p + 1] = (uint64_t)x.z | ((uint64_t)x.w << 32);
+            }
+        }
+        uint64_t c, n1, n2;
+        if constexpr (BITS)
+            gather_lds_bits<WHICH>(h, ga, h.pos0, c, n1, n2);
+        else
+            gather_lds_g<WHICH>(h, ga, j, w, c, n1, n2);
+        const WordDraw wd = compare_planes_paired<false>(P, c, n1, n2, code);
+        uint64_t und = active ? wd.und : 0ull;
+        if (active) {
+            h.dst[g] = wd.lt;
+            if constexpr (BITS) {
+                if (g == 0)   // the copy of the first word
+                    h.dst[h.n_words] = wd.lt;
+            }
+            record[g] = c;
+        }
+        const uint32_t mine = (uint32_t)__popcll(und);
+        const uint32_t upto = wave_prefix_dpp(mine);
+        uint32_t base = 0;
+        if ((threadIdx.x & 63u) == 63u)
+            base = atomicAdd(&sh.counts[WHICH], upto);
+        uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)base, 63) + upto - mine;
+        for (; und; und &= und - 1, ++e) {
+            const uint32_t v = 64u * g + (uint32_t)__builtin_ctzll(und);
+            if (e < sh.cap)
+                sh.list[e] = v;
+            else
+                resolve_site<WHICH>(h, dp, sh.T24, v);
+        }
+    }
+    __syncthreads();
+    const uint32_t n = sh.counts[WHICH] < sh.cap ? sh.counts[WHICH] : sh.cap;
+    if (threadIdx.x < n)
+        resolve_site<WHICH>(h, dp, sh.T24, sh.list[threadIdx.x]);
+    ++dp.t;
+    recorded_draw<SPLIT>(dp, ga, g, part, P, sh);
+    __syncthreads();
+}
+
+template <bool BITS, int SPLIT>
+__global__ __launch_bounds__(kRecordedMaxWords) void k_batch_recorded(BatchArgs a) {
+    extern __shared__ uint64_t smem[];
+    __shared__ uint32_t T24[6];
+    __shared__ uint32_t counts[2];
+    const ChainDesc& cd = a.single;
+    HalfCtx<BITS> hA, hB;
+    hA.L = hB.L = cd.L;
+    hA.W = hB.W = cd.L / 64u;
+    hA.n_words = hB.n_words = a.max_words;
+    hA.divW = hB.divW = cd.divW;
+    hA.divL = hB.divL = cd.divL;
+    uint64_t* sig = smem;
+    uint64_t* tau = smem + a.max_words + 1u;
+    RecordedShared sh;
+    sh.lanes = 64u * ((a.max_words + 63u) / 64u);
+    sh.planes = reinterpret_cast<uint4*>(tau + a.max_words + 1u);   // 16-byte aligned: behind 2 n + 2 words
+    sh.cap = recorded_list_cap(a.max_words);
+    sh.list = reinterpret_cast<uint32_t*>(sh.planes + (SPLIT > 1 ? 4u * sh.lanes : 0u));
+    sh.counts = counts;
+    sh.T24 = T24;
+    hA.src = sig; hA.dst = tau;
+    hB.src = tau; hB.dst = sig;
+    const uint32_t part = SPLIT == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / sh.lanes);
+    const uint32_t g = threadIdx.x - part * sh.lanes;
+    const bool active = part == 0 && g < a.max_words;
+    uint32_t j = 0, w = 0;
+    if constexpr (BITS) {
+        const uint32_t m = 64u * g - fdiv(64u * g, cd.divL) * cd.L;
+        hA.pos0 = hB.pos0 = m ? cd.L - m : 0u;
+        uint64_t starts = 1u;
+        for (uint32_t b = cd.L; b < 64u; b += cd.L)
+            starts |= 1ull << b;
+        hA.starts = hB.starts = starts;
+    } else {
+        j = fdiv(g, cd.divW);
+        w = g - j * hA.W;
+    }
+    DrawParams dp;
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+        dp.T[i] = cd.T[i];
+    dp.key0 = a.key0;
+    dp.key1 = a.key1;
+    dp.stream = cd.stream + blockIdx.x;
+    dp.t = 2u * a.step0;
+    dp.tag2 = 0;
+    dp.rng_xor = 0;
+    const uint32_t code = make_plane_masks<true>(dp).code;
+    if (active)
+        sig[g] = (reinterpret_cast<const uint64_t*>(a.single_sig) + (size_t)blockIdx.x * a.max_words)[g];
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            T24[i] = paired_tail(cd.T, i);
+        counts[0] = 0;
+        if constexpr (BITS)
+            sig[a.max_words] = sig[0];
+    }
+    uint64_t* record = reinterpret_cast<uint64_t*>(a.traj + (size_t)blockIdx.x * a.traj_chain_bytes);
+    uint64_t P[8];
+    recorded_draw<SPLIT>(dp, g < a.max_words ? g : a.max_words - 1u, g, part, P, sh);
+    __syncthreads();
+    for (uint32_t m = 0; m < a.k_steps; ++m) {
+        recorded_half_step<0, BITS, SPLIT>(hA, dp, code, g, part, j, w, P, record, sh);
+        record += a.max_words;
+        recorded_half_step<1, BITS, SPLIT>(hB, dp, code, g, part, j, w, P, record, sh);
+        record += a.max_words;
+    }
+    if (active)
+        record[g] = sig[g];
+}
+
 __global__ void k_zero_u32(uint32_t* p, uint32_t n) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
         p[i] = 0;
@@ -574,6 +771,33 @@ void launch_batch_chains_t(const BatchArgs& a, uint32_t blocks, uint32_t threads
         hipLaunchKernelGGL((k_batch_chains<false, BITS>), dim3(blocks), dim3(threads), lds, st, a);
     else
         hipLaunchKernelGGL((k_batch_chains_general<false, BITS>), dim3(blocks), dim3(threads), lds, st, a);
+}
+
+template <int SPLIT>
+void launch_batch_recorded_t(const BatchArgs& a, uint32_t lanes, hipStream_t st) {
+    const size_t lds = (size_t)2 * (a.max_words + 1u) * sizeof(uint64_t) +
+                       (SPLIT > 1 ? (size_t)4 * lanes * sizeof(uint4) : 0) +
+                       (size_t)recorded_list_cap(a.max_words) * sizeof(uint32_t);
+    if (a.bits)
+        hipLaunchKernelGGL((k_batch_recorded<true, SPLIT>), dim3(a.n_uniform), dim3(SPLIT * lanes), lds, st, a);
+    else
+        hipLaunchKernelGGL((k_batch_recorded<false, SPLIT>), dim3(a.n_uniform), dim3(SPLIT * lanes), lds, st, a);
+}
+
+hipError_t launch_batch_recorded(const BatchArgs& a, uint32_t n_cu, hipStream_t st) {
+    // As many lanes per word as a workgroup has room for, unless CUs have more
+    // than one chain, whose wavefronts then fill each other's waits: 128^2, four
+    // and one lane per word, 256 chains 1.32 and 1.68 us per half-step, 600
+    // chains 3.8 and 2.3.
+    const uint32_t lanes = 64u * ((a.max_words + 63u) / 64u);
+    const bool alone = a.n_uniform <= n_cu;
+    if (alone && 4u * lanes <= kRecordedMaxWords)
+        launch_batch_recorded_t<4>(a, lanes, st);
+    else if (alone && 2u * lanes <= kRecordedMaxWords)
+        launch_batch_recorded_t<2>(a, lanes, st);
+    else
+        launch_batch_recorded_t<1>(a, lanes, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_chains(const BatchArgs& a, uint32_t blocks, uint32_t threads, hipStream_t st) {

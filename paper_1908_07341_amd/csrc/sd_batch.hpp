@@ -74,6 +74,12 @@ void set_divisors(ChainDesc& d, uint32_t L);
 
 size_t batch_lds_bytes(uint32_t max_words, uint32_t threads);
 hipError_t launch_batch_chains(const BatchArgs& a, uint32_t blocks, uint32_t threads, hipStream_t st);
+
+// Largest lattice of launch_batch_recorded: a word per lane of one workgroup.
+constexpr uint32_t kRecordedMaxWords = 1024;
+// The n_uniform chains of a recorded launch (a.traj set, a.paired, no
+// complement), max_words <= kRecordedMaxWords.
+hipError_t launch_batch_recorded(const BatchArgs& a, uint32_t n_cu, hipStream_t st);
 // Every chain's sigma in one launch, as launch_init would write it with the
 // chain's own stream: random with threshold base.T[0], else all +1 (up) or all
 // -1.  layout: kLayP64 for packed lattices, kLayI8Row for int8 ones on 16-byte

@@ -325,3 +325,24 @@ def test_replica_observables_at_counter_edges(L, fill):
     up, right = np.roll(t, -1, axis=1), np.roll(t, -1, axis=2)
     want = np.stack([s.sum((1, 2)), (s * (up + right)).sum((1, 2)), (s * t).sum((1, 2))], axis=1)
     assert np.array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("L,n", [(8, 3), (24, 3), (64, 2), (64, 300), (72, 3), (128, 3), (128, 300), (136, 3), (176, 3),
+                                 (184, 3), (256, 3), (256, 258), (264, 2)])
+def test_recorded_trajectories_by_lanes_per_word(L, n):
+    # four, two and one lane per word, partly filled tiles, more chains than
+    # CUs, the largest one-word-per-lane lattice and the next size; enough
+    # half-steps that some list more sites than the workgroup's list holds.
+    # Bits: exact.
+    print(f"recorded trajectories L={L} n={n}", flush=True)
+    k, W = (60 if n < 10 else 4), L * L // 64
+    rng = np.random.default_rng(L + n)
+    info = np.iinfo(np.int64)
+    starts = torch.from_numpy(rng.integers(info.min, info.max, size=n * W, dtype=np.int64, endpoint=True)).cuda()
+    traj = torch.zeros(n * (2 * k + 1) * W, dtype=torch.int64, device="cuda")
+    for J, q in ((0.45, 0.7), (1.1, 0.0)):
+        sd.sd_trajectories(starts, traj, n, L, sd.SD_P64, J, q, SEED, 7, 3, k)
+        for a in {0, 1, n - 1}:
+            one = torch.zeros((2 * k + 1) * W, dtype=torch.int64, device="cuda")
+            sd.sd_trajectory(starts[a * W:(a + 1) * W].clone(), one, L, sd.SD_P64, J, q, SEED, 7 + a, 3, k)
+            assert torch.equal(one, traj.view(n, -1)[a]), (J, q, a)
