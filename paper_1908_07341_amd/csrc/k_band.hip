@@ -78,50 +78,49 @@ __device__ __forceinline__ void band_gather(const uint64_t* src, uint32_t u, uin
     }
 }
 
-// Decision of undecided site b of LDS word u of a half-step (tail uniform
-// below the threshold's low 24 bits), with its word and neighbour words.
+// Decision of undecided site v = 64 * LDS word + bit of a half-step (tail
+// uniform below the threshold's low 24 bits), with its LDS row i and its
+// partner and neighbour bits.  (The bits alone: three dwords, where the words
+// and their windows took 25 operations more in the chain that ends every
+// half-step; recorded half-steps of five 1024^2 chains 2.61 -> 2.56 us, of one
+// 2048^2 chain 2.39 either way.)
 template <int WHICH>
-__device__ __forceinline__ uint32_t band_tail(const uint64_t* src, uint32_t u, uint32_t b, uint32_t base, uint32_t L,
-                                              uint32_t W, const FastDiv& divW, const DrawParams& dp,
-                                              const uint32_t* T24, uint32_t& i, uint64_t& c, uint64_t& n1,
-                                              uint64_t& n2) {
-    i = fdiv(u, divW);
-    const uint32_t w = u - i * W;
-    band_gather<WHICH>(src, u, w, W, c, n1, n2);
+__device__ __forceinline__ uint32_t band_tail(const uint64_t* src, uint32_t v, uint32_t base, uint32_t L,
+                                              const FastDiv& divW, const DrawParams& dp, const uint32_t* T24,
+                                              uint32_t& i, uint32_t& c, uint32_t& n1, uint32_t& n2) {
+    const lds_dword* d = reinterpret_cast<const lds_dword*>(src);
+    i = fdiv(v >> 6, divW);
+    const uint32_t x = v - i * L;   // column
+    const uint32_t v1 = WHICH == 0 ? v - L : v + L;
+    const uint32_t v2 = WHICH == 0 ? v - 1u + (x == 0 ? L : 0u) : v + 1u - (x == L - 1u ? L : 0u);
+    c = (d[v >> 5] >> (v & 31u)) & 1u;
+    n1 = (d[v1 >> 5] >> (v1 & 31u)) & 1u;
+    n2 = (d[v2 >> 5] >> (v2 & 31u)) & 1u;
     uint32_t row = base + i;
     row = row >= L ? row - L : row;
     row = row >= L ? row - L : row;
-    return draw_tail24(dp, 64u * (row * W + w) + b) < T24[class_at(c, n1, n2, (int)b)] ? 1u : 0u;
-}
-
-template <bool OBS>
-__device__ __forceinline__ void band_count_site(uint32_t bit, uint64_t c, uint64_t n1, uint64_t n2, uint32_t b,
-                                                BandSums& acc) {
-    if constexpr (OBS) {
-        acc.pc += bit;
-        acc.dpair += (bit ^ (uint32_t)((n1 >> b) & 1u)) + (bit ^ (uint32_t)((n2 >> b) & 1u));
-        acc.dself += bit ^ (uint32_t)((c >> b) & 1u);
-    }
+    return draw_tail24(dp, row * L + x) < T24[2u * (n1 + n2) + c] ? 1u : 0u;
 }
 
 // Resolve the first k sites of a wavefront's list, one per lane, or-ing the
 // decided bits into dst (several sites may share a word).
 template <int WHICH, bool OBS>
 __device__ __forceinline__ void band_resolve(const uint64_t* src, uint64_t* dst, const uint32_t* list, uint32_t k,
-                                             uint32_t o0, uint32_t o1, uint32_t base, uint32_t L, uint32_t W,
+                                             uint32_t o0, uint32_t o1, uint32_t base, uint32_t L,
                                              const FastDiv& divW, const DrawParams& dp, const uint32_t* T24,
                                              BandSums& acc) {
     band_sync_wave();
     for (uint32_t e = threadIdx.x & 63u; e < k; e += 64u) {
         const uint32_t v = list[e];
-        const uint32_t u = v >> 6, b = v & 63u;
-        uint32_t i;
-        uint64_t c, n1, n2;
-        const uint32_t bit = band_tail<WHICH>(src, u, b, base, L, W, divW, dp, T24, i, c, n1, n2);
+        uint32_t i, c, n1, n2;
+        const uint32_t bit = band_tail<WHICH>(src, v, base, L, divW, dp, T24, i, c, n1, n2);
         if (bit)
-            atomicOr(reinterpret_cast<unsigned long long*>(&dst[u]), 1ull << b);
-        if (OBS && i >= o0 && i < o1)
-            band_count_site<OBS>(bit, c, n1, n2, b, acc);
+            atomicOr(reinterpret_cast<lds_dword*>(dst) + (v >> 5), 1u << (v & 31u));
+        if (OBS && i >= o0 && i < o1) {
+            acc.pc += bit;
+            acc.dpair += (bit ^ n1) + (bit ^ n2);
+            acc.dself += bit ^ c;
+        }
     }
     band_sync_wave();
 }
@@ -186,13 +185,13 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
             }
             listed += (uint32_t)__popcll(m);
             if (listed >= 64u) {
-                band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, divW, dp, sh.T24, acc);
+                band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, divW, dp, sh.T24, acc);
                 listed = 0;
             }
         }
     }
     if (listed)
-        band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, W, divW, dp, sh.T24, acc);
+        band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, divW, dp, sh.T24, acc);
     if constexpr (OBS) {
         const uint32_t v[3] = {wave_sum_dpp(acc.pc), wave_sum_dpp(acc.dpair), wave_sum_dpp(acc.dself)};
         if (lane == 0) {

@@ -27,9 +27,6 @@ namespace sd {
 
 namespace {
 
-// The lattices are written as 64-bit words and read as dwords, too.
-typedef uint32_t __attribute__((may_alias)) lds_dword;
-
 // BITS: rows need not start on a word (L % 64 != 0, L % 8 == 0); neighbours
 // are windows of the lattice's bit string, and the word behind the lattice
 // repeats its first, so that no window wraps inside.

@@ -50,6 +50,9 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+// LDS lattices are written as 64-bit words and read as dwords, too.
+typedef uint32_t __attribute__((may_alias)) lds_dword;
+
 struct U4 { uint32_t x0, x1, x2, x3; };
 
 // The full 64-bit product a * m in one v_mad_u64_u32.  Left to itself the
