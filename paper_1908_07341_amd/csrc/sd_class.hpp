@@ -144,6 +144,24 @@ __device__ __forceinline__ void class_masks(uint32_t key0, uint32_t key1, uint32
     }
     if (!active)
         open = 0;
+    // Each lane writes its sites behind those of the lanes before it: five or
+    // six rounds of 7 operations, where a round of ballots takes 14 and two
+    // trips to the scalar unit (512 samples of 32^2: 10.9 -> 9.4 ms).
+    uint32_t half[2] = {lo32(open), hi32(open)};
+    const uint32_t mine = (uint32_t)__popcll(open);
+    const uint32_t upto = wave_prefix_dpp(mine);
+    const uint32_t sites = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    if (sites <= kClassListCap) {
+        uint32_t e = upto - mine;
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h)
+            for (; half[h]; half[h] &= half[h] - 1u)
+                w.entry[e++] = lane | ((uint32_t)__builtin_ctz(half[h]) << 6) | (h << 11);
+        if (sites)
+            class_tails(key0, key1, stream, rng_xor, T24, w, sites, stride, at);
+        return;
+    }
+    // more than the list holds: one site per lane and round, emptied in between
     uint32_t listed = 0;   // wavefront-uniform
     for (;;) {
         const uint64_t m = __ballot(open != 0);
