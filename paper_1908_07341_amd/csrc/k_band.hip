@@ -102,16 +102,17 @@ __device__ __forceinline__ uint32_t band_tail(const uint64_t* src, uint32_t v, u
     return draw_tail24(dp, row * L + x) < T24[2u * (n1 + n2) + c] ? 1u : 0u;
 }
 
-// Resolve the first k sites of a wavefront's list, one per lane, or-ing the
-// decided bits into dst (several sites may share a word).
+// Resolve k <= 64 sites of a list, one per lane, or-ing the decided bits into
+// dst (several sites may share a word).
 template <int WHICH, bool OBS>
 __device__ __forceinline__ void band_resolve(const uint64_t* src, uint64_t* dst, const uint32_t* list, uint32_t k,
                                              uint32_t o0, uint32_t o1, uint32_t base, uint32_t L,
                                              const FastDiv& divW, const DrawParams& dp, const uint32_t* T24,
                                              BandSums& acc) {
     band_sync_wave();
-    for (uint32_t e = threadIdx.x & 63u; e < k; e += 64u) {
-        const uint32_t v = list[e];
+    const uint32_t lane = threadIdx.x & 63u;
+    if (lane < k) {
+        const uint32_t v = list[lane];
         uint32_t i, c, n1, n2;
         const uint32_t bit = band_tail<WHICH>(src, v, base, L, divW, dp, T24, i, c, n1, n2);
         if (bit)
@@ -185,8 +186,8 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
             }
             listed += (uint32_t)__popcll(m);
             if (listed >= 64u) {
-                band_resolve<WHICH, OBS>(src, dst, list, listed, o0, o1, base, L, divW, dp, sh.T24, acc);
-                listed = 0;
+                listed -= 64u;
+                band_resolve<WHICH, OBS>(src, dst, list + listed, 64u, o0, o1, base, L, divW, dp, sh.T24, acc);
             }
         }
     }

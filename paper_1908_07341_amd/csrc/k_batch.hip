@@ -145,12 +145,14 @@ struct ObsSums {
     uint32_t pc = 0, dpair = 0, dself = 0;   // #+1, #differences to up+right, to the partner
 };
 
-// Resolves the first n sites of the wavefront's list into the lattice.
+// Resolves n <= 64 sites of the wavefront's list, from `first` on, into the
+// lattice.
 template <int WHICH, bool OBS, bool BITS>
 __device__ __forceinline__ void resolve_list(const HalfCtx<BITS>& h, const DrawParams& dp, const uint32_t* T24,
-                                             WaveWordList& wl, uint32_t n, ObsSums& acc) {
-    for (uint32_t e = threadIdx.x & 63u; e < n; e += 64u) {
-        const uint32_t v = wl.site[e];
+                                             WaveWordList& wl, uint32_t first, uint32_t n, ObsSums& acc) {
+    const uint32_t lane = threadIdx.x & 63u;
+    if (lane < n) {
+        const uint32_t v = wl.site[first + lane];
         uint32_t c, n1, n2;
         site_bits<WHICH>(h, v, c, n1, n2);
         const uint32_t bit = draw_tail24(dp, v) < T24[2u * (n1 + n2) + c] ? 1u : 0u;
@@ -266,16 +268,16 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
             }
             listed += (uint32_t)__popcll(m);
             if (listed >= 64u) {
+                listed -= 64u;
                 wave_sync_lds();
-                resolve_list<WHICH, OBS>(h, dp, T24, wl, listed, acc);
+                resolve_list<WHICH, OBS>(h, dp, T24, wl, listed, 64u, acc);
                 wave_sync_lds();
-                listed = 0;
             }
         }
     }
     if (listed) {
         wave_sync_lds();
-        resolve_list<WHICH, OBS>(h, dp, T24, wl, listed, acc);
+        resolve_list<WHICH, OBS>(h, dp, T24, wl, 0u, listed, acc);
     }
     if constexpr (OBS)
         add_wave_obs(acc, obs_sum);
