@@ -126,12 +126,12 @@ def traffic_from_counters(fetch_csv: str, write_csv: str, sq_csv: str | None = N
             kernels[k] = {"fetch_kib": fetch[k], "write_kib": write[k],
                           "bytes": f_fac * fetch[k] * 1024.0 + w_fac * write[k] * 1024.0}
     # the plain half-step A kernel (no observables) stands for the launch:
-    # template arguments <layout, half-step, paired, complemented, observables>
+    # template arguments <layout, half-step, complemented>
     def plain_a(name):
         if "k_half_step<" not in name:
             return False
         args = [a.strip() for a in name.split("<", 1)[1].split(">", 1)[0].split(",")]
-        return len(args) == 5 and args[1] == "0" and args[4] == "false"
+        return len(args) == 3 and args[1] == "0"
 
     main = min((k for k in kernels if plain_a(k)), key=lambda k: kernels[k]["bytes"], default=None)
     valu = None
