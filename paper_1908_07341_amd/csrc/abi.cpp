@@ -271,10 +271,12 @@ static bool capturing(hipStream_t st) {
 
 void* ahead_scratch(Workspace& ws, hipStream_t st) {
     static std::atomic<uint32_t> made{0};
-    if (ws.ahead)
-        return ws.ahead;
+    // a graph may be replayed beside the stream it was captured on: it takes
+    // none of the stream's scratch
     if (capturing(st))
         return nullptr;
+    if (ws.ahead)
+        return ws.ahead;
     if (made.fetch_add(1) >= kAheadBuffers) {
         made.fetch_sub(1);
         return nullptr;

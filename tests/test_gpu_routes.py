@@ -346,3 +346,43 @@ def test_recorded_trajectories_by_lanes_per_word(L, n):
             one = torch.zeros((2 * k + 1) * W, dtype=torch.int64, device="cuda")
             sd.sd_trajectory(starts[a * W:(a + 1) * W].clone(), one, L, sd.SD_P64, J, q, SEED, 7 + a, 3, k)
             assert torch.equal(one, traj.view(n, -1)[a]), (J, q, a)
+
+
+@pytest.mark.parametrize("L,layout,k", [(64, sd.SD_I8, 100), (100, sd.SD_I8, 40), (256, sd.SD_P64, 40), (200, sd.SD_P64, 40)])
+def test_captured_small_run_replayed_beside_its_stream(L, layout, k):
+    # a run that is drawn ahead when called eagerly, captured on a stream that
+    # has its scratch buffer, then replayed on another stream while eager runs
+    # use that buffer: every replay gives the eager run's lattices and records.
+    # (The eager runs beside it record nothing: the partial sums of recorded
+    # half-step launches are the stream's, in a graph as in a call.)
+    print(f"captured small run L={L} layout={layout}", flush=True)
+    pair = [[sd.new_lattice(L, layout) for _ in range(2)] for _ in range(2)]
+    first = sd.new_lattice(L, layout)
+    sd.sd_init(first, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    obs = torch.empty((k, 3), dtype=torch.int64, device="cuda")
+
+    def run(i, stream_id):
+        pair[i][0].copy_(first)
+        sd.sd_run(pair[i][0], pair[i][1], L, layout, 0.4, 0.6, SEED, stream_id, 0, k, obs if i == 0 else None,
+                  1 if i == 0 else 0)
+
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        run(0, 5)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (*pair[0], obs)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run(0, 5)
+    for _ in range(4):
+        for t in (*pair[0], obs):
+            t.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            for _ in range(3):
+                run(1, 6)
+        with torch.cuda.stream(other):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((*pair[0], obs), want))
