@@ -120,8 +120,8 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
  * the device computes, round by round, whether each site's uniform lies below
  * each of the six thresholds, and one workgroup picks the chain's bits, through
  * a 16 MiB device buffer the library allocates once per (device, stream) for
- * at most 16 streams and keeps; without it (stream capture before the first
- * eager call, more streams) and for lattices of 64 words in short runs a single
+ * at most 16 streams and keeps; without it (under stream capture, on further
+ * streams) and for lattices of 64 words in short runs a single
  * workgroup with the lattices in LDS does both, where they fit; larger lattices
  * use two grid-wide launches per step and, with obs, one more launch per chunk
  * of records, whose partial sums wait in a 512 KiB device buffer the library
