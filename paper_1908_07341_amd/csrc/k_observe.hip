@@ -169,64 +169,79 @@ __global__ __launch_bounds__(256) void k_corr_row(const void* __restrict__ sigma
 
 // Rows of whole 64-bit words (the packed string with L % 64 == 0, or int8
 // rows whose 64-site groups are 16-byte aligned): workgroup (x, y) takes the
-// 64 shifts r = 64 x + lane and the R rows from y R on, staged in LDS as
-// W = L / 64 words each; wavefront w sums popcount(row ^ row rotated by r)
-// over the W words of its rows w, w + 16, ..., the rotation a funnel shift of
-// consecutive words.  r >> 6 = x is uniform in the workgroup, so the LDS reads
-// are broadcasts.  The 16 wavefronts' sums are added in LDS and each r gets
-// one atomic add into out[r] (zeroed first) per workgroup.  Several
-// lattices of one size in one launch: lattice z = blockIdx.z, its sums at
-// out + z (rmax + 1).
-constexpr uint32_t kCorr64Words = 4096;   // staged words (32 KB)
+// R <= 16 rows from y R on, one per wavefront, and the `chunks` 64-shift chunks
+// r = 64 s + lane from s = x chunks on.  A wavefront stages its row in LDS with
+// its first words repeated behind it, so that no shift wraps, and for each s
+// sums popcount(row ^ row rotated by r) over the W words, the rotation two
+// funnel shifts of consecutive dwords (lanes past 31 start one dword later).
+// s is uniform, so the LDS reads are broadcasts of at most two dwords.  The
+// wavefronts' sums are added in LDS and each r gets one atomic add into out[r]
+// (zeroed first) per workgroup.  Several lattices of one size in one launch:
+// lattice z = blockIdx.z, its sums at out + z (rmax + 1).
+// Bound by the vector unit (6 operations per word, shift and row).  With one
+// chunk per workgroup every chunk's workgroups staged the rows again, and 64-bit
+// shifts with wrapped indices took 10 operations; us a call before and now: five
+// 1024^2 int8 lattices, r <= 512, 32.1 -> 21.5; two of 2048^2, r <= 1024, 68 ->
+// 47; 16384^2, r <= 512, 905 -> 529.
+constexpr uint32_t kCorr64Words = 6144;   // staged words (48 KB)
 constexpr uint32_t kCorrWaves = 16;
+constexpr uint32_t kCorrChunks = 16;
+constexpr uint32_t kCorrTarget = 1024;   // workgroups aimed at: four per CU
+
+// Rows are staged as 64-bit words and read as dwords.
+typedef uint32_t __attribute__((may_alias)) row_dword;
 
 template <bool INT8>
-__global__ __launch_bounds__(1024) void k_corr_row64(CorrLattices cl, uint32_t L, uint32_t R, int32_t rmax,
-                                                     int64_t* __restrict__ out) {
+__global__ __launch_bounds__(1024) void k_corr_row64(CorrLattices cl, uint32_t L, uint32_t R, uint32_t chunks,
+                                                     int32_t rmax, int64_t* __restrict__ out) {
     __shared__ uint64_t rows[kCorr64Words];
-    __shared__ int64_t part[kCorrWaves][64];
+    __shared__ uint32_t tot[kCorrChunks][64];   // differing pairs by shift
     const void* __restrict__ sigma = cl.p[blockIdx.z];
     out += (size_t)blockIdx.z * ((uint32_t)rmax + 1u);
     const uint32_t W = L / 64u;
+    const uint32_t over = (uint32_t)rmax / 64u + 1u;   // words repeated behind a row
+    const uint32_t pitch = W + over;
     const uint32_t j0 = blockIdx.y * R;
     const uint32_t n = j0 + R < L ? R : L - j0;
-    for (uint32_t q = threadIdx.x; q < n * W; q += blockDim.x) {
-        if constexpr (INT8)
-            rows[q] = load_bits64_i8(static_cast<const int8_t*>(sigma) + (size_t)j0 * L + 64u * q);
-        else
-            rows[q] = static_cast<const uint64_t*>(sigma)[(size_t)j0 * W + q];
-    }
-    __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t s = blockIdx.x;   // r >> 6, at most (L - 1) >> 6 = W - 1
-    const uint32_t sh = lane;        // r & 63
-    int64_t acc = 0;
-    for (uint32_t i = wave; i < n; i += kCorrWaves) {
-        const uint64_t* row = rows + i * W;
-        uint32_t diff = 0;
-        // words s .. W - 1 of the row, then 0 .. s - 1: word w + s (mod W) pairs with word w
-#pragma unroll 8
-        for (uint32_t w = 0; w < W; ++w) {
-            uint32_t q0 = w + s;
-            q0 = q0 >= W ? q0 - W : q0;
-            const uint32_t q1 = q0 + 1u == W ? 0u : q0 + 1u;
-            const uint64_t rot = (row[q0] >> sh) | ((row[q1] << 1) << (63u - sh));
-            diff += (uint32_t)__popcll(row[w] ^ rot);
-        }
-        acc += (int64_t)L - 2 * (int64_t)diff;
-    }
-    part[wave][lane] = acc;
+    const uint32_t s0 = blockIdx.x * chunks;   // r >> 6 of the first chunk
+    const uint32_t s1 = s0 + chunks < over ? s0 + chunks : over;
+    if (threadIdx.x < 64u * chunks)
+        tot[threadIdx.x >> 6][lane] = 0u;
     __syncthreads();
-    if (wave == 0) {
-        int64_t t = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < kCorrWaves; ++k)
-            t += part[k][lane];
-        const uint32_t r = 64u * blockIdx.x + lane;
-        if (r <= (uint32_t)rmax)
-            atomicAdd(reinterpret_cast<unsigned long long*>(out + r), (unsigned long long)t);
+    for (uint32_t i = wave; i < n; i += kCorrWaves) {
+        uint64_t* row = rows + i * pitch;
+        for (uint32_t w = lane; w < W; w += 64u) {
+            const size_t q = (size_t)(j0 + i) * W + w;
+            const uint64_t x = INT8 ? load_bits64_i8(static_cast<const int8_t*>(sigma) + 64u * q)
+                                    : static_cast<const uint64_t*>(sigma)[q];
+            row[w] = x;
+            if (w < over)
+                row[W + w] = x;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const row_dword* own = reinterpret_cast<const row_dword*>(row);
+        for (uint32_t s = s0; s < s1; ++s) {
+            const row_dword* d = own + 2u * s + (lane >> 5);
+            uint32_t diff = 0, before = d[0];
+#pragma unroll 8
+            for (uint32_t w = 0; w < W; ++w) {
+                const uint32_t mid = d[2u * w + 1u], after = d[2u * w + 2u];
+                diff += (uint32_t)__popc(own[2u * w] ^ __builtin_amdgcn_alignbit(mid, before, lane & 31u));
+                diff += (uint32_t)__popc(own[2u * w + 1u] ^ __builtin_amdgcn_alignbit(after, mid, lane & 31u));
+                before = after;
+            }
+            atomicAdd(&tot[s - s0][lane], diff);
+        }
     }
+    __syncthreads();
+    const uint32_t r = 64u * s0 + threadIdx.x;
+    if (threadIdx.x < 64u * (s1 - s0) && r <= (uint32_t)rmax)
+        atomicAdd(reinterpret_cast<unsigned long long*>(out + r),
+                  (unsigned long long)((int64_t)n * L - 2 * (int64_t)tot[threadIdx.x >> 6][lane]));
 }
 
 // Diagonal correlation sums (section 3.3, Table 1).  Block (x, y): direction
@@ -378,20 +393,25 @@ hipError_t launch_corr_row_many(int layout, const void* const* sigma, uint32_t n
     if (e != hipSuccess)
         return e;
     if (layout == kLayP64 || layout == kLayI8Row) {
-        // 16 rows per workgroup (fewer when 16 rows exceed the staging
-        // buffer: W > 256), one 64-shift chunk of r per workgroup column,
-        // one lattice per grid layer
+        // A row per wavefront (fewer when 16 rows exceed the staging buffer),
+        // one lattice per grid layer, and as many 64-shift chunks per workgroup
+        // as leave kCorrTarget workgroups (five 1024^2 lattices with 256, 512, 1024
+        // and 2048 workgroups: 25.1, 22.5, 21.5 and 25.3 us)
         CorrLattices cl{};
         for (uint32_t a = 0; a < n; ++a)
             cl.p[a] = sigma[a];
-        const uint32_t W = G.L / 64u;
-        const uint32_t R = W <= kCorr64Words / kCorrWaves ? kCorrWaves : kCorr64Words / W;
-        const dim3 grid(((uint32_t)rmax + 64u) / 64u, (G.L + R - 1u) / R, n);
+        const uint32_t over = (uint32_t)rmax / 64u + 1u, pitch = G.L / 64u + over;
+        const uint32_t R = kCorrWaves * pitch <= kCorr64Words ? kCorrWaves : kCorr64Words / pitch;
+        const uint32_t groups = (G.L + R - 1u) / R;
+        uint32_t chunks = (uint32_t)((uint64_t)over * groups * n / kCorrTarget);
+        chunks = chunks < 1u ? 1u : chunks > kCorrChunks ? kCorrChunks : chunks;
+        chunks = chunks > over ? over : chunks;
+        const dim3 grid((over + chunks - 1u) / chunks, groups, n);
         const dim3 block(64u * kCorrWaves);
         if (layout == kLayI8Row)
-            hipLaunchKernelGGL((k_corr_row64<true>), grid, block, 0, st, cl, G.L, R, rmax, out);
+            hipLaunchKernelGGL((k_corr_row64<true>), grid, block, 0, st, cl, G.L, R, chunks, rmax, out);
         else
-            hipLaunchKernelGGL((k_corr_row64<false>), grid, block, 0, st, cl, G.L, R, rmax, out);
+            hipLaunchKernelGGL((k_corr_row64<false>), grid, block, 0, st, cl, G.L, R, chunks, rmax, out);
         return hipGetLastError();
     }
     for (uint32_t a = 0; a < n && e == hipSuccess; ++a)

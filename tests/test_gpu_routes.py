@@ -386,3 +386,27 @@ def test_captured_small_run_replayed_beside_its_stream(L, layout, k):
             graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip((*pair[0], obs), want))
+
+
+@pytest.mark.parametrize("L,n,rmax", [(64, 1, 0), (64, 16, 63), (448, 3, 200), (448, 1, 447), (1024, 5, 512), (1024, 5, 511),
+                                      (1024, 1, 1023), (1024, 16, 64)])
+@pytest.mark.parametrize("layout", [sd.SD_I8, sd.SD_P64])
+def test_row_correlations_by_chunks_per_workgroup(L, n, rmax, layout):
+    # one to sixteen 64-shift chunks per workgroup, the last one partial, rows
+    # repeated once in full; exact sums
+    print(f"row correlations L={L} n={n} rmax={rmax} layout={layout}", flush=True)
+    host = [inputs.random_lattice(L, 50 + a) for a in range(n)]
+    lat = []
+    for x in host:
+        t = sd.new_lattice(L, layout)
+        raw = x if layout == sd.SD_I8 else inputs.pack_bits(x)
+        t.reshape(-1).view(torch.int8 if layout == sd.SD_I8 else torch.uint8).copy_(torch.from_numpy(raw.reshape(-1).copy()))
+        lat.append(t)
+    out = torch.full((n, rmax + 1), -1, dtype=torch.int64, device="cuda")
+    sd.sd_corr_row_many(lat, L, layout, rmax, out)
+    got = out.cpu().numpy()
+    for a in range(n):
+        x = host[a].reshape(L, L).astype(np.float64)   # circular correlation: whole numbers below 2^53
+        f = np.fft.rfft(x, axis=1)
+        want = np.rint(np.fft.irfft((f * np.conj(f)).sum(axis=0), n=L)).astype(np.int64)
+        assert np.array_equal(got[a], want[:rmax + 1]), a
