@@ -322,12 +322,14 @@ bool small_supported(int32_t L) { return L >= 8 && L <= 64 && L % 8 == 0; }
 // Wavefronts and half-steps per epoch.  A tile of 64 (half-step, word) pairs
 // is one worker's unit of work, so an epoch holds one per worker: 14 half-steps
 // of a 64^2 lattice, 60 of a 32^2 one on 16 wavefronts; when there are more
-// workgroups than CUs two share a CU (8 wavefronts and half the LDS each).
+// workgroups than CUs two share a CU (10 wavefronts and half the LDS each: with
+// two walkers the most workers whose scratch leaves a tile for every one; 512
+// samples of 32^2 with 7, 8, 9 and 10 wavefronts 9.9, 9.3, 9.2 and 8.8 ms).
 // Lattices of few words stop at kMaxEpoch, where the walker is the slower side.
 hipError_t launch_small(SmallArgs a, uint32_t blocks, bool pair, uint32_t n_cu, size_t max_lds, hipStream_t st) {
     constexpr uint32_t kMaxEpoch = 64;
     const bool share = blocks > n_cu;
-    const uint32_t waves = share ? 8u : 16u;
+    const uint32_t waves = share ? 10u : 16u;
     const uint32_t walkers = pair ? 2u : 1u;
     const size_t budget = share ? max_lds / 2 : max_lds;
     const size_t scratch = sizeof(ClassList) * (waves - walkers);

@@ -147,7 +147,7 @@ def test_small_lattices_drawn_ahead(oracle, L, J, q):
 
 @pytest.mark.parametrize("L", [8, 32, 48, 64])
 def test_exact_samples_shared_and_alone(oracle, L):
-    # more pairs than CUs (two workgroups of 8 wavefronts share a CU) against
+    # more pairs than CUs (two workgroups share a CU) against
     # the same pairs alone (16 wavefronts), and one pair against the oracle;
     # at T_max = 16 most pairs stay open
     J, q, n = 0.3, 0.8, 300
