@@ -875,11 +875,20 @@ static bool wide_tiles(int layout, const Geom& G, bool paired) {
 uint32_t half_step_blocks(int layout, const Geom& G, bool paired, uint32_t max_blocks) {
     // one workgroup per four wavefront tiles; at most kMaxBlocks by default,
     // at most max_blocks when the caller gives a cap
-    const uint32_t wave_tile = wide_tiles(layout, G, paired) ? kMaxWaveTile : 64u;
+    const bool wide = wide_tiles(layout, G, paired);
+    const uint32_t wave_tile = wide ? kMaxWaveTile : 64u;
     const uint32_t tiles = (G.n_groups + wave_tile - 1) / wave_tile;
     uint32_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     blocks = blocks ? blocks : 1u;
-    const uint32_t cap = max_blocks ? max_blocks : kMaxBlocks;
+    // Wide tiles: 1536 workgroups are resident, so 2048 leave the last third of
+    // a large launch to 512 of them.  Two full rounds from 3072 up, and more
+    // and shorter ones where every wavefront has several tiles (us per
+    // half-step with 2048, 3072 and 4096 workgroups, records every 10 steps and
+    // every step: 12288^2 21.0 24.2, 21.2 24.4, 21.2 24.6; 16384^2 33.3 36.3,
+    // 31.8 36.2, 32.2 37.7; 19968^2 47.5 51.3, 45.5 50.4, 44.5 50.4; 32768^2
+    // 114.9 122.0, 110.7 118.9, 108.2 117.6).
+    const uint32_t rule = !wide || blocks <= 3072u ? kMaxBlocks : blocks < 6000u ? 3072u : 4096u;
+    const uint32_t cap = max_blocks ? max_blocks : rule;
     return blocks > cap ? cap : blocks;
 }
 

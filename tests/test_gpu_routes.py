@@ -69,10 +69,11 @@ def test_int8_windows(oracle, L, offset):
 
 
 @pytest.mark.parametrize("L,layout", [(6784, sd.SD_P64), (6848, sd.SD_P64), (8192, sd.SD_P64), (6848, sd.SD_P32),
-                                      (6720, sd.SD_P32)])
+                                      (6720, sd.SD_P32), (14144, sd.SD_P64), (14208, sd.SD_P64), (19904, sd.SD_P64)])
 def test_wide_and_one_word_tiles_agree(L, layout):
-    # below and above the size from which packed lattices take wide tiles; the
-    # runs of sd_run_many too short for whole steps take one-word tiles
+    # below and above the size from which packed lattices take wide tiles, and
+    # those from which they take more workgroups; the runs of sd_run_many too
+    # short for whole steps take one-word tiles
     print(f"tiles L={L} layout={layout}", flush=True)
     lat = [sd.new_lattice(L, layout) for _ in range(4)]
     for x in (lat[0], lat[2]):
