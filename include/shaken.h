@@ -126,8 +126,10 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
  * use two grid-wide launches per step and, with obs, one more launch per chunk
  * of records, whose partial sums wait in a 512 KiB device buffer the library
  * allocates once per (device, stream) and keeps, or, where rows are whole
- * 64-bit words up to L = 4096, whole steps as in sd_run_many; the result is the
- * same bit for bit)
+ * 64-bit words up to L = 4096, whole steps as in sd_run_many; under stream
+ * capture no buffer of the library enters the graph, which may be replayed on
+ * any stream: records are added up by atomics; the result is the same bit for
+ * bit)
  * sigma (device) is updated, tau (device, same size) receives the last
  * half-step-A lattice (its input content is ignored).  If obs (device) is not
  * NULL it receives, after every obs_every-th step, the int64 triple
@@ -182,8 +184,9 @@ SD_API sd_status sd_run_noalloc(void* sigma, void* tau, int32_t L, int32_t layou
  * n_chains.  obs (device) NULL, or n_chains x (k_steps / obs_every) records
  * of (M, A, B), chain-major: obs[3 * (a * (k_steps / obs_every) + r) + {0,1,2}]
  * is sd_run's record r of chain a.  Records go through the same per-(device,
- * stream) partial-sum buffer as sd_run (allocated on first use and kept), so
- * a first call with records cannot be made under stream capture.  flags:
+ * stream) partial-sum buffer as sd_run (allocated on first use and kept), and
+ * a first call with records cannot be made under stream capture (later captured
+ * ones add their records up by atomics and leave the buffer alone).  flags:
  * SD_FLAG_COMPLEMENT_RNG, SD_FLAG_GENERAL_COMPARE.  EINVAL: bad sizes or
  * pointers, overlapping lattices, obs without obs_every, step0 + k_steps
  * above 2^29.

@@ -233,7 +233,17 @@ static hipError_t launch_small_chain(void* sigma, void* tau, int32_t L, bool int
     return launch_small(a, 1, false, n_cu, max_lds, st);
 }
 
-Workspace* partials_workspace(hipStream_t st) {
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
+// The stream's workspace; make: one that does not exist yet is made.
+static Workspace* stream_workspace(hipStream_t st, bool make) {
     static std::mutex mu;
     static std::map<std::pair<int, hipStream_t>, Workspace*> spaces;   // kept until the process ends
     int dev = 0;
@@ -244,11 +254,8 @@ Workspace* partials_workspace(hipStream_t st) {
     const auto it = spaces.find(key);
     if (it != spaces.end())
         return it->second;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
+    if (!make)
         return nullptr;
-    }
     int64_t* p = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&p), kPartialsWords * sizeof(int64_t)) != hipSuccess) {
         (void)hipGetLastError();
@@ -260,21 +267,12 @@ Workspace* partials_workspace(hipStream_t st) {
     return w;
 }
 
-static bool capturing(hipStream_t st) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return cs != hipStreamCaptureStatusNone;
-}
+// A graph may be replayed on any stream, beside the one it was captured on:
+// what it would share with that stream's calls, it must not hold.
+Workspace* partials_workspace(hipStream_t st) { return capturing(st) ? nullptr : stream_workspace(st, true); }
 
-void* ahead_scratch(Workspace& ws, hipStream_t st) {
+void* ahead_scratch(Workspace& ws) {
     static std::atomic<uint32_t> made{0};
-    // a graph may be replayed beside the stream it was captured on: it takes
-    // none of the stream's scratch
-    if (capturing(st))
-        return nullptr;
     if (ws.ahead)
         return ws.ahead;
     if (made.fetch_add(1) >= kAheadBuffers) {
@@ -311,7 +309,7 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
     if (!ws)
         return hipSuccess;
     std::unique_lock<std::mutex> hold(ws->mu);   // keeps this call's use of the scratch contiguous on the stream
-    void* scratch = ahead_scratch(*ws, st);
+    void* scratch = ahead_scratch(*ws);
     if (!scratch)
         return hipSuccess;
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
@@ -365,8 +363,8 @@ sd_status scratch_ptr(const char* name, int64_t** out) {
 
 // The step loop of several chains in the grid kernels (or of one): whole steps,
 // several per launch, where rows are whole words, else half-steps; records
-// through partials (kPartialsWords int64; n_rec > 0 needs a record's sums of
-// either kernel to fit).
+// through partials (kPartialsWords int64, which a record's sums of either kernel
+// must fit), or by atomics without (partials null).
 static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, bool whole_words, bool paired, int32_t L,
                                 uint64_t seed, uint64_t step0, uint32_t k_steps, int64_t* obs, uint32_t n_rec,
                                 uint32_t obs_every, uint32_t flags, int64_t* partials, hipStream_t st) {
@@ -376,6 +374,8 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
     const uint64_t obs_chain = 3ull * n_rec;
     uint32_t pending = 0;
     hipError_t e = hipSuccess;
+    if (n_rec && !partials)
+        e = launch_fill_i64(obs, (size_t)mc.n_chains * obs_chain, 0, st);
     // Rows of at most 64 words: whole steps, several per launch (bands with
     // halo rows, sigma alternating between the two lattices of each chain),
     // for all but the last step, in an even number of launches so that sigma
@@ -387,7 +387,7 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
         return ed;
     const BandPlan plan = band_plan(L, mc.n_chains, n_cu);
     uint32_t depth = plan.depth;
-    if (depth && n_rec) {   // the records of one launch must fit the partial-sum buffer
+    if (depth && n_rec && partials) {   // the records of one launch must fit the partial-sum buffer
         const uint64_t per_rec = 4ull * plan.bands * mc.n_chains;
         depth = (uint32_t)std::min<uint64_t>(depth, kPartialsWords / per_rec);
     }
@@ -416,6 +416,8 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
         const uint32_t stride_b = 4u * ba.bands * ba.n_chains;
         const uint32_t chunk_b = (uint32_t)(kPartialsWords / stride_b);
         ba.rec_stride = stride_b;
+        ba.obs = obs;
+        ba.obs_chain = obs_chain;
         const bool complement = (flags & SD_FLAG_COMPLEMENT_RNG) != 0;
         uint32_t m = 0;   // steps done
         for (uint32_t j = 0; j < n_launch && e == hipSuccess; ++j) {
@@ -435,18 +437,18 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
                         ba.rec_mask |= 1u << s;
                         ++n_here;
                     }
-            if (n_here && pending + n_here > chunk_b) {
-                const uint32_t r_next = (m + obs_every) / obs_every - 1;   // first record of this launch
+            ba.rec0 = n_here ? (m + obs_every) / obs_every - 1 : 0u;   // first record of this launch
+            if (partials && n_here && pending + n_here > chunk_b) {
                 e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
-                                           r_next - pending, st);
+                                           ba.rec0 - pending, st);
                 pending = 0;
                 if (e != hipSuccess)
                     break;
             }
             e = launch_band_step(ba, klay == kLayI8Row, paired, complement,
-                                 n_here ? partials + (size_t)pending * stride_b : nullptr, st);
+                                 partials ? partials + (size_t)pending * stride_b : nullptr, st);
             m += steps;
-            pending += n_here;
+            pending += partials ? n_here : 0u;
             if (e == hipSuccess && pending && j + 1 == n_launch) {
                 e = launch_obs_finish_many(partials, ba.bands, mc.n_chains, pending, stride_b, obs, obs_chain,
                                            m / obs_every - pending, st);
@@ -457,15 +459,15 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
     for (uint32_t m = n_fused; m < k_steps && e == hipSuccess; ++m) {
         const uint64_t n = step0 + m;
         base.t = (uint32_t)(2 * n);
-        e = launch_half_step_many(klay, 0, mc, G, base, paired, nullptr, st);
+        e = launch_half_step_many(klay, 0, mc, G, base, paired, nullptr, nullptr, st);
         if (e != hipSuccess)
             break;
         base.t = (uint32_t)(2 * n + 1);
         const bool rec = n_rec && (m + 1) % obs_every == 0 && (m + 1) / obs_every <= n_rec;
-        e = launch_half_step_many(klay, 1, mc, G, base, paired, rec ? partials + (size_t)pending * stride : nullptr,
-                                  st);
-        if (rec && e == hipSuccess) {
-            const uint32_t r = (m + 1) / obs_every - 1;
+        const uint32_t r = rec ? (m + 1) / obs_every - 1 : 0u;
+        e = launch_half_step_many(klay, 1, mc, G, base, paired, rec ? obs + 3u * (size_t)r : nullptr,
+                                  rec && partials ? partials + (size_t)pending * stride : nullptr, st);
+        if (rec && partials && e == hipSuccess) {
             ++pending;
             if (pending == chunk || r + 1 == n_rec) {
                 e = launch_obs_finish_many(partials, mc.blocks_per_chain, mc.n_chains, pending, stride, obs,
@@ -572,7 +574,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     // against this: 512^2 3.8 -> 1.6, 1024^2 3.9 -> 1.7, 2048^2 4.0 -> 2.2,
     // 4096^2 5.9 -> 3.9).
     const bool whole_words = klay == kLayI8Row || (klay == kLayP64 && words_aligned(sigma, tau));
-    if (ch.mode != 2 && whole_words && k_steps >= 3 && (!n_rec || partials) &&
+    if (ch.mode != 2 && whole_words && k_steps >= 3 &&
         !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE))) {
         uint32_t n_cu = 0;
         size_t max_lds = 0;
@@ -586,6 +588,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
             mc.stream[0] = stream;
             mc.n_chains = 1;
             mc.blocks_per_chain = many_blocks_per_chain(G);
+            mc.obs_chain = 3ull * n_rec;
             e = run_many_grid(mc, G, klay, true, thresholds_paired(mc.T[0]), L, seed, step0, k_steps, obs, n_rec,
                               obs_every, flags, partials, st);
             return e == hipSuccess ? SD_OK : hip_fail(e, name);
@@ -617,7 +620,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
             break;
         dp.t = (uint32_t)(2 * n + 1);
         if (n_rec && (m + 1) % obs_every == 0 && !partials) {
-            // no workspace (first use under stream capture): atomics into the record
+            // no workspace (stream capture): atomics into the record
             e = launch_half_step(klay, 1, tau, sigma, G, dp, obs + 3u * (size_t)((m + 1) / obs_every - 1), st,
                                  ch.blocks, nullptr, general);
         } else if (n_rec && (m + 1) % obs_every == 0) {
@@ -772,6 +775,7 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
     mc.n_chains = (uint32_t)n_chains;
     mc.blocks_per_chain = many_blocks_per_chain(G);
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
+    mc.obs_chain = 3ull * n_rec;
     const uint32_t stride = 4u * mc.blocks_per_chain * mc.n_chains;   // partial sums of one record
     if (n_rec && stride > kPartialsWords)
         return fail(SD_EINVAL, "%s: %u chains of %u workgroups need more partial sums per record than the %zu of "
@@ -794,11 +798,13 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
     std::unique_lock<std::mutex> hold;   // keeps this call's use of the workspace contiguous on the stream
     if (n_rec) {
         Workspace* ws = partials_workspace(st);
-        if (!ws)
+        if (!ws && !(capturing(st) && stream_workspace(st, false)))
             return fail(SD_EHIP, "%s: no partial-sum buffer for this stream (stream capture before the first "
                         "eager call on it, or out of device memory)", name);
-        hold = std::unique_lock<std::mutex>(ws->mu);
-        partials = ws->p;
+        if (ws) {   // a captured run takes atomics
+            hold = std::unique_lock<std::mutex>(ws->mu);
+            partials = ws->p;
+        }
     }
     const bool whole_words = (layout == SD_P64 && L % 64 == 0) || klay == kLayI8Row;
     const hipError_t e = run_many_grid(mc, G, klay, whole_words, paired, L, seed, step0, k_steps, obs, n_rec, obs_every,

@@ -209,7 +209,8 @@ __device__ __forceinline__ void band_half(const uint64_t* src, uint64_t* dst, ui
 // 64-bit words.  OBS: for every step s (from 0) with bit s of ba.rec_mask, the
 // workgroup's (#+1, #differences to up + right, #to the partner, #sites) of
 // its own rows go to partials + k * ba.rec_stride + 4 * blockIdx.x, k the
-// number of recorded steps before s in this launch.
+// number of recorded steps before s in this launch, or as M, A, B by atomics
+// into the chain's record ba.rec0 + k when partials is null.
 template <bool INT8, bool PAIRED, bool COMPLEMENT, bool OBS>
 __global__ __launch_bounds__(kBandMaxThreads) void k_band_step(BandArgs ba, int64_t* __restrict__ partials) {
     __shared__ BandShared sh;
@@ -267,11 +268,21 @@ __global__ __launch_bounds__(kBandMaxThreads) void k_band_step(BandArgs ba, int6
             // the next half-step A's barrier, so the reset cannot race
             if (recorded) {
                 if (threadIdx.x == 0) {
-                    int64_t* p = partials + (size_t)rec * ba.rec_stride + 4u * (size_t)blockIdx.x;
-                    p[0] = (int64_t)sh.obs[0];
-                    p[1] = (int64_t)sh.obs[1];
-                    p[2] = (int64_t)sh.obs[2];
-                    p[3] = (int64_t)R * L;
+                    const int64_t v0 = (int64_t)sh.obs[0], v1 = (int64_t)sh.obs[1], v2 = (int64_t)sh.obs[2];
+                    const int64_t sites = (int64_t)R * L;
+                    if (partials) {
+                        int64_t* p = partials + (size_t)rec * ba.rec_stride + 4u * (size_t)blockIdx.x;
+                        p[0] = v0;
+                        p[1] = v1;
+                        p[2] = v2;
+                        p[3] = sites;
+                    } else {
+                        unsigned long long* o = reinterpret_cast<unsigned long long*>(
+                            ba.obs + chain * ba.obs_chain + 3u * (size_t)(ba.rec0 + rec));
+                        atomicAdd(o + 0, (unsigned long long)(2 * v0 - sites));
+                        atomicAdd(o + 1, (unsigned long long)(2 * sites - 2 * v1));
+                        atomicAdd(o + 2, (unsigned long long)(sites - 2 * v2));
+                    }
                     sh.obs[0] = sh.obs[1] = sh.obs[2] = 0;
                 }
                 ++rec;
@@ -347,12 +358,12 @@ uint32_t band_threads(uint32_t R, uint32_t W, uint32_t steps) {
 hipError_t launch_band_step(const BandArgs& ba, bool int8, bool paired, bool complement, int64_t* partials,
                             hipStream_t st) {
     if (int8) {
-        if (partials)
+        if (ba.rec_mask)
             launch_band_t<true, true>(ba, paired, complement, partials, st);
         else
             launch_band_t<true, false>(ba, paired, complement, partials, st);
     } else {
-        if (partials)
+        if (ba.rec_mask)
             launch_band_t<false, true>(ba, paired, complement, partials, st);
         else
             launch_band_t<false, false>(ba, paired, complement, partials, st);

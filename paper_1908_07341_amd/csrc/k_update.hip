@@ -613,7 +613,7 @@ __device__ __forceinline__ void draw_listed(const DrawParams& dp, const uint32_t
 // half-step of chain `chain`, with its own lattices, threshold table and
 // stream id (the per-chain values are wavefront-uniform kernel arguments).
 // Partial sums of recorded steps go to partials[4 * workgroup ...],
-// chain-major, or (one chain, partials null) by atomics into obs.
+// chain-major, or (partials null) by atomics into the chain's record.
 template <int LAYOUT, int WHICH, bool PAIRED, bool COMPLEMENT, bool OBS>
 __global__ __launch_bounds__(256) void k_half_step_many(ManyChains mc, Geom G, DrawParams base,
                                                         int64_t* __restrict__ obs, int64_t* __restrict__ partials) {
@@ -696,7 +696,7 @@ __global__ __launch_bounds__(256) void k_half_step_many(ManyChains mc, Geom G, D
             if (partials)
                 partials[4u * (size_t)blockIdx.x + threadIdx.x] = t;
             else if (threadIdx.x < 3)
-                atomicAdd(reinterpret_cast<unsigned long long*>(obs + threadIdx.x),
+                atomicAdd(reinterpret_cast<unsigned long long*>(obs + chain * mc.obs_chain + threadIdx.x),
                           (unsigned long long)(threadIdx.x == 0 ? 2 * t - n : (threadIdx.x == 1 ? 2 * n : n) - 2 * t));
         }
     }
@@ -986,7 +986,7 @@ static hipError_t launch_one_word(int layout, int which, const ManyChains& mc, c
     case LAY:                                                                                               \
         if (which == 0)                                                                                     \
             launch_many_mode<LAY, 0, false>(paired, complement, grid, st, mc, G, base, nullptr, nullptr);  \
-        else if (obs == nullptr && partials == nullptr)                                                     \
+        else if (obs == nullptr)                                                                            \
             launch_many_mode<LAY, 1, false>(paired, complement, grid, st, mc, G, base, nullptr, nullptr);  \
         else                                                                                                \
             launch_many_mode<LAY, 1, true>(paired, complement, grid, st, mc, G, base, obs, partials);      \
@@ -1005,8 +1005,8 @@ static hipError_t launch_one_word(int layout, int which, const ManyChains& mc, c
 }
 
 hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
-                                 bool paired, int64_t* partials, hipStream_t st) {
-    return launch_one_word(layout, which, mc, G, base, paired, nullptr, partials, st);
+                                 bool paired, int64_t* obs, int64_t* partials, hipStream_t st) {
+    return launch_one_word(layout, which, mc, G, base, paired, obs, partials, st);
 }
 
 hipError_t launch_obs_finish_many(const int64_t* partials, uint32_t n_blocks, uint32_t n_chains, uint32_t n_rec,

@@ -39,8 +39,9 @@ SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stre
 
 // Device scratch of kPartialsWords int64 for per-workgroup partial sums, one
 // per (device, stream), allocated on first use and kept for the process.
-// Null when it does not exist yet and cannot be made now (the stream is
-// being captured, or the allocation failed); callers then use atomics.  A
+// Null while the stream is being captured (a graph that held p would share it
+// with the stream's own calls wherever it is replayed), or when it cannot be
+// made (the allocation failed); callers then use atomics.  A
 // call holds mu while it enqueues the launches that write and read p, so
 // that calls from several host threads on one stream do not interleave
 // their use of the slots.
@@ -54,10 +55,10 @@ Workspace* partials_workspace(hipStream_t st);
 
 // Scratch of the draw-ahead runs (class masks of two rounds), kept with the
 // workspace; the caller holds ws.mu.  At most kAheadBuffers exist in a process
-// (256 MiB); null past that, under capture, or out of memory, and the caller
-// takes the kernels that need none.
+// (256 MiB); null past that or out of memory, and the caller takes the kernels
+// that need none.
 constexpr size_t kAheadBytes = 16u << 20;
 constexpr uint32_t kAheadBuffers = 16;
-void* ahead_scratch(Workspace& ws, hipStream_t st);
+void* ahead_scratch(Workspace& ws);
 
 }  // namespace sd

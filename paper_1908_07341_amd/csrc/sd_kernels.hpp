@@ -80,15 +80,18 @@ struct ManyChains {
     uint32_t stream[kManyMax];
     uint32_t n_chains;
     uint32_t blocks_per_chain;
+    uint64_t obs_chain;   // int64 between the records of consecutive chains
 };
 // Workgroups per chain of a multi-chain half-step (64-word tiles, four per
 // workgroup, at most kMaxBlocks).
 uint32_t many_blocks_per_chain(const Geom& G);
 // which = 0: tau_a <- sigma_a, which = 1: sigma_a <- tau_a for every chain a;
-// with partials (which = 1 only) the workgroups of chain a leave their
-// partial sums at partials + 4 * (a * blocks_per_chain + block).
+// with obs (which = 1 only: chain 0's record, chain a's a * obs_chain further) the
+// workgroups of chain a leave their partial sums at
+// partials + 4 * (a * blocks_per_chain + block), or add them into the zeroed
+// records by atomics when partials is null.
 hipError_t launch_half_step_many(int layout, int which, const ManyChains& mc, const Geom& G, const DrawParams& base,
-                                 bool paired, int64_t* partials, hipStream_t st);
+                                 bool paired, int64_t* obs, int64_t* partials, hipStream_t st);
 // Writes records rec0 .. rec0 + n_rec - 1 of every chain: record r of chain a
 // from the partials at partials + r * stride + 4 * a * n_blocks, into
 // obs + a * obs_chain + 3 * (rec0 + r).
@@ -119,6 +122,9 @@ struct BandArgs {
     uint32_t threads;    // workgroup size: 64 per tile of the widest half-step
     uint32_t rec_mask;   // bit s: record step s of the launch
     uint32_t rec_stride; // int64 between the partial sums of consecutive records
+    uint32_t rec0;       // the launch's first record
+    int64_t* obs;        // record r of chain a: obs + a * obs_chain + 3 r
+    uint64_t obs_chain;
 };
 // Bands per chain (0: L does not take the whole-step kernel) and steps per
 // launch for n_chains chains on n_cu CUs.
@@ -128,8 +134,9 @@ struct BandPlan {
 BandPlan band_plan(int32_t L, uint32_t n_chains, uint32_t n_cu);
 // Workgroup size for `steps` steps of bands of R rows of W words.
 uint32_t band_threads(uint32_t R, uint32_t W, uint32_t steps);
-// partials (non-null when rec_mask is not zero): the sums of recorded step k
-// of the launch at partials + k * rec_stride + 4 b for workgroup b.
+// Recorded step k of the launch (rec_mask): workgroup b's sums to
+// partials + k * rec_stride + 4 b, or by atomics into the zeroed records
+// rec0 + k when partials is null.
 hipError_t launch_band_step(const BandArgs& ba, bool int8, bool paired, bool complement, int64_t* partials,
                             hipStream_t st);
 hipError_t launch_init(int layout, void* dst, const Geom& G, int const_up, bool random, const DrawParams& dp,

@@ -389,6 +389,86 @@ def test_captured_small_run_replayed_beside_its_stream(L, layout, k):
         assert all(torch.equal(a, b) for a, b in zip((*pair[0], obs), want))
 
 
+@pytest.mark.parametrize("L,layout,n,k", [(100, sd.SD_I8, 1, 12), (512, sd.SD_P64, 1, 40), (448, sd.SD_I8, 1, 9),
+                                          (6848, sd.SD_P64, 1, 3), (512, sd.SD_P64, 5, 40), (520, sd.SD_P64, 3, 6)])
+def test_captured_records_replayed_beside_their_stream(L, layout, n, k):
+    # recorded runs of every form that keeps partial sums when called eagerly
+    # (one-word tiles, bands, wide tiles; one chain and several), captured on a
+    # stream that has its partial-sum buffer and replayed on another while
+    # recorded eager runs use that buffer; whole numbers: exact
+    print(f"captured records L={L} layout={layout} n={n}", flush=True)
+    J, q, ids = [0.3 + 0.05 * a for a in range(n)], [0.8] * n, [a + 2 for a in range(n)]
+    first = [sd.new_lattice(L, layout) for _ in range(n)]
+    for a in range(n):
+        sd.sd_init(first[a], L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, a)
+    sets = [[[torch.zeros_like(x) for x in first] for _ in range(2)] for _ in range(2)]
+    obs = [torch.full((n, k, 3), -1, dtype=torch.int64, device="cuda") for _ in range(2)]
+
+    def run(i, step0):
+        for x, y in zip(sets[i][0], first):
+            x.copy_(y)
+        if n == 1:
+            sd.sd_run(sets[i][0][0], sets[i][1][0], L, layout, J[0], q[0], SEED, ids[0], step0, k, obs[i], 1)
+        else:
+            sd.sd_run_many(sets[i][0], sets[i][1], L, layout, J, q, SEED, ids, step0, k, obs[i], 1)
+
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    want = []
+    for step0 in (0, 1000):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            run(0, step0)
+        torch.cuda.synchronize()
+        want.append([t.clone() for t in (*sets[0][0], *sets[0][1], obs[0])])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run(0, 0)
+    for _ in range(4):
+        for o in obs:
+            o.fill_(-1)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            for _ in range(3):
+                run(1, 1000)
+        with torch.cuda.stream(other):
+            graph.replay()
+        torch.cuda.synchronize()
+        for i in range(2):
+            assert all(torch.equal(a, b) for a, b in zip((*sets[i][0], *sets[i][1], obs[i]), want[i])), i
+
+
+def test_captured_counts_replayed_beside_their_stream():
+    # the log-likelihood counts keep partial sums of the same buffer
+    n, k, L = 6, 20, 128
+    start = torch.empty((n, L * L // 64), dtype=torch.int64, device="cuda")
+    for a in range(n):
+        sd.sd_init(start[a], L, sd.SD_P64, sd.SD_INIT_RANDOM, 0.5, SEED, a)
+    traj = [torch.empty((n, 2 * k + 1, L * L // 64), dtype=torch.int64, device="cuda") for _ in range(2)]
+    for i in range(2):
+        sd.sd_trajectories(start, traj[i], n, L, sd.SD_P64, 0.4, 0.5 + i, SEED, 0, 0, k)
+    out = [torch.zeros(12, dtype=torch.int64, device="cuda") for _ in range(2)]
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for i in range(2):
+        sd.sd_loglik_counts(traj[i], n, 2 * k + 1, L, out[i], hip_stream=stream)
+    torch.cuda.synchronize()
+    want = [o.clone() for o in out]
+    assert int(want[0].sum()) == 2 * k * n * L * L
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        sd.sd_loglik_counts(traj[0], n, 2 * k + 1, L, out[0])
+    for _ in range(4):
+        for o in out:
+            o.fill_(-1)
+        torch.cuda.synchronize()
+        for _ in range(3):
+            sd.sd_loglik_counts(traj[1], n, 2 * k + 1, L, out[1], hip_stream=stream)
+        with torch.cuda.stream(other):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
 @pytest.mark.parametrize("L,n,rmax", [(64, 1, 0), (64, 16, 63), (448, 3, 200), (448, 1, 447), (1024, 5, 512), (1024, 5, 511),
                                       (1024, 1, 1023), (1024, 16, 64)])
 @pytest.mark.parametrize("layout", [sd.SD_I8, sd.SD_P64])
