@@ -28,7 +28,9 @@
  *   - pointers named "device" must be device memory (hipMalloc or torch CUDA
  *     tensors); the library never frees, keeps or reallocates caller memory;
  *   - `stream` is a hipStream_t passed as void* (NULL = default stream); work is
- *     enqueued asynchronously on it, except where a function says otherwise;
+ *     enqueued asynchronously on it, except where a function says otherwise.
+ *     hipStreamPerThread is taken from any number of threads (calls on it that
+ *     use a buffer of the library follow one another on the device);
  *   - every function validates its arguments before enqueuing anything and
  *     returns SD_EINVAL (or SD_EUNSUPPORTED) without side effects on bad
  *     arguments; SD_EHIP reports a HIP runtime error (asynchronous errors of

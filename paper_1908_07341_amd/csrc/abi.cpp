@@ -263,13 +263,38 @@ static Workspace* stream_workspace(hipStream_t st, bool make) {
     }
     Workspace* w = new Workspace;
     w->p = p;
+    if (st == hipStreamPerThread && hipEventCreateWithFlags(&w->last_use, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        w->lost = true;
+    }
     spaces[key] = w;
     return w;
 }
 
 // A graph may be replayed on any stream, beside the one it was captured on:
 // what it would share with that stream's calls, it must not hold.
-Workspace* partials_workspace(hipStream_t st) { return capturing(st) ? nullptr : stream_workspace(st, true); }
+WorkspaceUse::WorkspaceUse(hipStream_t st) : st_(st) {
+    ws_ = capturing(st) ? nullptr : stream_workspace(st, true);
+    if (!ws_)
+        return;
+    ws_->mu.lock();
+    if (st == hipStreamPerThread && (ws_->lost || hipStreamWaitEvent(st, ws_->last_use, 0) != hipSuccess)) {
+        (void)hipGetLastError();
+        ws_->mu.unlock();
+        ws_ = nullptr;
+    }
+}
+
+void WorkspaceUse::release() {
+    if (!ws_)
+        return;
+    if (st_ == hipStreamPerThread && hipEventRecord(ws_->last_use, st_) != hipSuccess) {
+        (void)hipGetLastError();
+        ws_->lost = true;
+    }
+    ws_->mu.unlock();
+    ws_ = nullptr;
+}
 
 void* ahead_scratch(Workspace& ws) {
     static std::atomic<uint32_t> made{0};
@@ -305,11 +330,10 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
                                    uint32_t k_steps, int64_t* obs, uint32_t obs_every, uint32_t flags, hipStream_t st,
                                    bool* done) {
     *done = false;
-    Workspace* ws = partials_workspace(st);
-    if (!ws)
+    const WorkspaceUse use(st);
+    if (!use.get())
         return hipSuccess;
-    std::unique_lock<std::mutex> hold(ws->mu);   // keeps this call's use of the scratch contiguous on the stream
-    void* scratch = ahead_scratch(*ws);
+    void* scratch = ahead_scratch(*use.get());
     if (!scratch)
         return hipSuccess;
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
@@ -557,17 +581,14 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     const Geom G = make_geom(L, klay);
     hipError_t e = hipSuccess;
     int64_t* partials = nullptr;
-    std::unique_lock<std::mutex> hold;   // keeps this call's use of the workspace contiguous on the stream
+    WorkspaceUse use;
     if (n_rec && no_alloc) {
         const sd_status ss = scratch_ptr(name, &partials);
         if (ss != SD_OK)
             return ss;
     } else if (n_rec) {
-        Workspace* ws = partials_workspace(st);
-        if (ws) {
-            hold = std::unique_lock<std::mutex>(ws->mu);
-            partials = ws->p;
-        }
+        use = WorkspaceUse(st);
+        partials = use.get() ? use.get()->p : nullptr;
     }
     // Rows of whole words up to 4096^2: whole steps in bands of rows, several
     // per launch, as sd_run_many runs them (us per half-step, a launch each
@@ -795,16 +816,13 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
             return SD_OK;
     }
     int64_t* partials = nullptr;
-    std::unique_lock<std::mutex> hold;   // keeps this call's use of the workspace contiguous on the stream
+    WorkspaceUse use;
     if (n_rec) {
-        Workspace* ws = partials_workspace(st);
-        if (!ws && !(capturing(st) && stream_workspace(st, false)))
+        use = WorkspaceUse(st);
+        if (!use.get() && !(capturing(st) && stream_workspace(st, false)))
             return fail(SD_EHIP, "%s: no partial-sum buffer for this stream (stream capture before the first "
                         "eager call on it, or out of device memory)", name);
-        if (ws) {   // a captured run takes atomics
-            hold = std::unique_lock<std::mutex>(ws->mu);
-            partials = ws->p;
-        }
+        partials = use.get() ? use.get()->p : nullptr;   // null: a captured run takes atomics
     }
     const bool whole_words = (layout == SD_P64 && L % 64 == 0) || klay == kLayI8Row;
     const hipError_t e = run_many_grid(mc, G, klay, whole_words, paired, L, seed, step0, k_steps, obs, n_rec, obs_every,

@@ -39,19 +39,43 @@ SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stre
 
 // Device scratch of kPartialsWords int64 for per-workgroup partial sums, one
 // per (device, stream), allocated on first use and kept for the process.
-// Null while the stream is being captured (a graph that held p would share it
-// with the stream's own calls wherever it is replayed), or when it cannot be
-// made (the allocation failed); callers then use atomics.  A
-// call holds mu while it enqueues the launches that write and read p, so
-// that calls from several host threads on one stream do not interleave
-// their use of the slots.
 constexpr size_t kPartialsWords = 65536;
 struct Workspace {
     int64_t* p = nullptr;
     void* ahead = nullptr;   // kAheadBytes, made by the first run that draws ahead (ahead_scratch)
     std::mutex mu;
+    hipEvent_t last_use = nullptr;   // hipStreamPerThread only: behind the last call's work
+    bool lost = false;               // ... could not be recorded: later calls have nothing to wait for
 };
-Workspace* partials_workspace(hipStream_t st);
+
+// A call's use of its stream's workspace, held while it enqueues the launches
+// that write and read it, so that calls from several host threads on one
+// stream do not interleave.  get() is null while the stream is being captured
+// (a graph that held p would share it with the stream's own calls wherever it
+// is replayed), or when the workspace cannot be made (the allocation failed);
+// callers then use atomics.  hipStreamPerThread is one handle but another queue
+// in every host thread: a call on it waits on the device for the last user's
+// work and leaves an event behind its own.
+class WorkspaceUse {
+public:
+    WorkspaceUse() = default;
+    explicit WorkspaceUse(hipStream_t st);
+    ~WorkspaceUse() { release(); }
+    WorkspaceUse(const WorkspaceUse&) = delete;
+    WorkspaceUse& operator=(WorkspaceUse&& o) {
+        release();
+        ws_ = o.ws_;
+        st_ = o.st_;
+        o.ws_ = nullptr;
+        return *this;
+    }
+    Workspace* get() const { return ws_; }
+
+private:
+    void release();
+    Workspace* ws_ = nullptr;
+    hipStream_t st_ = nullptr;
+};
 
 // Scratch of the draw-ahead runs (class masks of two rounds), kept with the
 // workspace; the caller holds ws.mu.  At most kAheadBuffers exist in a process

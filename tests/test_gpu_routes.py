@@ -1,5 +1,7 @@
 """GPU parity of the size-dependent kernel variants at the edges of their
 ranges."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -467,6 +469,55 @@ def test_captured_counts_replayed_beside_their_stream():
             graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+@pytest.mark.parametrize("L,layout,k,many", [(64, sd.SD_I8, 60, False), (200, sd.SD_P64, 40, False), (300, sd.SD_I8, 20, False),
+                                             (100, sd.SD_I8, 30, True), (512, sd.SD_P64, 30, False), (640, sd.SD_P64, 20, True)])
+def test_threads_on_the_per_thread_stream(L, layout, k, many):
+    # hipStreamPerThread is one handle, but another queue in every host thread:
+    # threads that draw ahead, or keep partial sums of records, on it at the same
+    # time get the chains and records that each gets alone
+    print(f"per-thread stream L={L} layout={layout} many={many}", flush=True)
+    per_thread, n_threads, n_sets = 2, 4, 6   # the handle's value is hipStreamPerThread's
+    first = sd.new_lattice(L, layout)
+    sd.sd_init(first, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+
+    def run(sigma, tau, obs, stream_id, hip_stream=None):
+        if many:
+            sd.sd_run_many([sigma], [tau], L, layout, [0.4], [0.6], SEED, [stream_id], 0, k, obs, 1, hip_stream=hip_stream)
+        else:
+            sd.sd_run(sigma, tau, L, layout, 0.4, 0.6, SEED, stream_id, 0, k, obs, 1, hip_stream=hip_stream)
+
+    def sets(n):
+        return [(first.clone(), torch.zeros_like(first), torch.full((k, 3), -1, dtype=torch.int64, device="cuda"))
+                for _ in range(n)]
+
+    want = sets(n_threads)
+    for i, w in enumerate(want):
+        run(*w, 10 + i)
+    got = [sets(n_sets) for _ in range(n_threads)]
+    torch.cuda.synchronize()
+    errors, ready = [], threading.Barrier(n_threads)
+
+    def work(i):
+        try:
+            ready.wait(60)
+            for g in got[i]:
+                run(*g, 10 + i, hip_stream=per_thread)
+            torch.cuda.synchronize()
+        except Exception as e:   # reported by the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(n_threads)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(90)
+    assert not errors, errors
+    torch.cuda.synchronize()
+    for i in range(n_threads):
+        for g in got[i]:
+            assert all(torch.equal(a, b) for a, b in zip(g, want[i])), i
 
 
 @pytest.mark.parametrize("L,n,rmax", [(64, 1, 0), (64, 16, 63), (448, 3, 200), (448, 1, 447), (1024, 5, 512), (1024, 5, 511),
