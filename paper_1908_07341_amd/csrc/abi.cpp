@@ -233,7 +233,7 @@ static hipError_t launch_small_chain(void* sigma, void* tau, int32_t L, bool int
     return launch_small(a, 1, false, n_cu, max_lds, st);
 }
 
-static bool capturing(hipStream_t st) {
+bool capturing(hipStream_t st) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
         (void)hipGetLastError();

@@ -508,6 +508,16 @@ sd_status sd_batch_init(sd_batch_plan* plan, void* lattices, int32_t kind, doubl
     sd_status s = check_lattice(lattices, (int32_t)plan->descs[0].L, plan->layout, "sd_batch_init");
     if (s != SD_OK)
         return s;
+    // a graph may outlive the plan, whose tables the one launch reads: captured,
+    // a launch per chain that holds the caller's lattice alone
+    if (capturing(static_cast<hipStream_t>(hip_stream))) {
+        for (int32_t c = 0; c < plan->n_chains && s == SD_OK; ++c) {
+            const ChainDesc& d = plan->descs[(size_t)c];
+            s = sd_init(static_cast<uint8_t*>(lattices) + d.sig_offset, (int32_t)d.L, plan->layout, kind, p_up,
+                        plan->seed, d.stream, hip_stream);
+        }
+        return s;
+    }
     DrawParams dp;
     bool random = false, up = false;
     s = init_params("sd_batch_init", kind, p_up, plan->seed, 0u, &dp, &random, &up);

@@ -30,6 +30,8 @@ sd_status init_params(const char* name, int32_t kind, double p_up, uint64_t seed
 sd_status check_lattice(const void* p, int32_t L, int32_t layout, const char* name);
 DrawParams dynamics_params(double J, double q, uint64_t seed, uint32_t stream, uint32_t t, uint32_t flags);
 
+// The stream is being captured into a graph (or cannot be asked).
+bool capturing(hipStream_t st);
 // The current device's CUs and LDS bytes a workgroup may have.
 hipError_t device_limits(uint32_t* n_cu, size_t* max_lds);
 // Arguments of the small-lattice kernel for k_steps steps from step0; the

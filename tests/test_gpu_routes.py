@@ -51,6 +51,32 @@ def test_batch_init_equals_sd_init_per_chain(layout, offset, kind, p_up):
     plan.close()
 
 
+@pytest.mark.parametrize("layout", [sd.SD_P64, sd.SD_I8])
+def test_captured_batch_init_outlives_its_plan(layout):
+    # the graph holds the caller's lattices and nothing of the plan, whose
+    # device tables are freed, and their memory used again, before the replays
+    sizes = [64, 200, 8, 64]
+    plan = sd.sd_batch_plan_create([0.4] * 4, [0.6] * 4, sizes, [3 * a for a in range(4)], layout=layout, seed=SEED, k_steps=1,
+                                   obs_every=0)
+    nb = sd.sd_batch_lattice_bytes(plan)
+    want = torch.zeros(nb, dtype=torch.uint8, device="cuda")
+    sd.sd_batch_init(plan, want, sd.SD_INIT_RANDOM, 0.3)
+    buf = torch.zeros_like(want)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        sd.sd_batch_init(plan, buf, sd.SD_INIT_RANDOM, 0.3)
+    plan.close()
+    other = sd.sd_batch_plan_create([0.1] * 4, [0.2] * 4, sizes[::-1], [50 + a for a in range(4)], layout=layout, seed=1,
+                                    k_steps=1, obs_every=0)
+    for _ in range(3):
+        buf.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(buf, want)
+    other.close()
+
+
 @pytest.mark.parametrize("L", [7, 8, 9, 11, 31, 63, 65, 127, 333])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_int8_windows(oracle, L, offset):
