@@ -242,6 +242,19 @@ bool capturing(hipStream_t st) {
     return cs != hipStreamCaptureStatusNone;
 }
 
+// hipMalloc for buffers that are made by the first call that wants them.  In the
+// default mode an allocation invalidates what any thread is capturing on any
+// stream; this thread's own stream is not being captured here.
+static hipError_t malloc_beside_captures(void** p, size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess)
+        return e;
+    e = hipMalloc(p, bytes);
+    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+    return e == hipSuccess ? back : e;
+}
+
 // The stream's workspace; make: one that does not exist yet is made.
 static Workspace* stream_workspace(hipStream_t st, bool make) {
     static std::mutex mu;
@@ -257,7 +270,7 @@ static Workspace* stream_workspace(hipStream_t st, bool make) {
     if (!make)
         return nullptr;
     int64_t* p = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&p), kPartialsWords * sizeof(int64_t)) != hipSuccess) {
+    if (malloc_beside_captures(reinterpret_cast<void**>(&p), kPartialsWords * sizeof(int64_t)) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
@@ -304,7 +317,7 @@ void* ahead_scratch(Workspace& ws) {
         made.fetch_sub(1);
         return nullptr;
     }
-    if (hipMalloc(&ws.ahead, kAheadBytes) != hipSuccess) {
+    if (malloc_beside_captures(&ws.ahead, kAheadBytes) != hipSuccess) {
         (void)hipGetLastError();
         ws.ahead = nullptr;
         made.fetch_sub(1);

@@ -1,5 +1,6 @@
 """GPU parity of the size-dependent kernel variants at the edges of their
 ranges."""
+import ctypes
 import threading
 
 import numpy as np
@@ -544,6 +545,46 @@ def test_threads_on_the_per_thread_stream(L, layout, k, many):
     for i in range(n_threads):
         for g in got[i]:
             assert all(torch.equal(a, b) for a, b in zip(g, want[i])), i
+
+
+@pytest.mark.parametrize("L,layout", [(64, sd.SD_I8), (200, sd.SD_P64), (512, sd.SD_P64)])
+def test_first_run_on_a_stream_beside_a_capture(L, layout):
+    # one thread captures (in the mode that forbids unsafe calls in every
+    # thread) while another makes its first runs on a stream, which make the
+    # stream's buffers: the capture goes through and the runs are right
+    print(f"first run beside a capture L={L} layout={layout}", flush=True)
+    k = 40
+    first = sd.new_lattice(L, layout)
+    sd.sd_init(first, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    sets = [(first.clone(), torch.zeros_like(first), torch.full((k, 3), -1, dtype=torch.int64, device="cuda"))
+            for _ in range(2)]
+    sd.sd_run(*sets[0][:2], L, layout, 0.4, 0.6, SEED, 1, 0, k, sets[0][2], 1)
+    x = torch.zeros(1000, device="cuda")
+    capture, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    handle = ctypes.c_void_p()
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0   # a handle the library has not seen
+    torch.cuda.synchronize()
+    errors = []
+
+    def work():
+        try:
+            sd.sd_run(*sets[1][:2], L, layout, 0.4, 0.6, SEED, 1, 0, k, sets[1][2], 1, hip_stream=handle.value)
+        except Exception as e:   # reported by the main thread
+            errors.append(e)
+
+    thread = threading.Thread(target=work)
+    with torch.cuda.graph(graph, stream=capture):
+        x += 1
+        thread.start()
+        thread.join(60)
+        x += 1
+    assert not errors, errors
+    graph.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 2).all())
+    assert all(torch.equal(a, b) for a, b in zip(*sets))
+    assert hip.hipStreamDestroy(handle) == 0
 
 
 @pytest.mark.parametrize("L,n,rmax", [(64, 1, 0), (64, 16, 63), (448, 3, 200), (448, 1, 447), (1024, 5, 512), (1024, 5, 511),
