@@ -502,7 +502,22 @@ SD_API sd_status sd_batch_bucket_times(sd_batch_plan* plan, int32_t bucket, floa
 SD_API void sd_batch_plan_destroy(sd_batch_plan* plan);
 
 /*
- * Diagnostics.  sd_debug_fastdiv returns n / d (d >= 1) computed with the
+ * Diagnostics.  sd_debug_last_route tells which kernels the calling thread's
+ * last sd_run, sd_run_noalloc or sd_run_many took (an sd_route); the chains do
+ * not depend on it.  Host only.
+ */
+typedef enum {
+    SD_ROUTE_NONE = 0,       /* no call yet, or the last one was refused or had no steps */
+    SD_ROUTE_SMALL = 1,      /* drawn ahead by the chain's own workgroup */
+    SD_ROUTE_AHEAD = 2,      /* drawn ahead by the whole device */
+    SD_ROUTE_LDS = 3,        /* one workgroup, both lattices in LDS */
+    SD_ROUTE_BANDS = 4,      /* whole steps in bands of rows */
+    SD_ROUTE_HALF_STEPS = 5  /* a launch per half-step */
+} sd_route;
+SD_API int32_t sd_debug_last_route(void);
+
+/*
+ * sd_debug_fastdiv returns n / d (d >= 1) computed with the
  * multiply-shift division the kernels use for row and column indices; 0 for
  * d == 0.  Host only, synchronous.
  */

@@ -22,6 +22,8 @@ SD_FLAG_COMPLEMENT_RNG = 1
 SD_FLAG_GLOBAL_KERNELS = 2
 SD_FLAG_MOMENTS = 4
 SD_FLAG_GENERAL_COMPARE = 8
+(SD_ROUTE_NONE, SD_ROUTE_SMALL, SD_ROUTE_AHEAD, SD_ROUTE_LDS, SD_ROUTE_BANDS,
+ SD_ROUTE_HALF_STEPS) = range(6)
 
 
 class sd_chain_desc(ctypes.Structure):
@@ -71,6 +73,7 @@ SIGNATURES = {
     "sd_tune": (_I32, [_I32, _I32, ctypes.c_char_p, _VP]),
     "sd_tuned_choice": (_I32, [_I32, _I32, ctypes.POINTER(_I32), ctypes.POINTER(_I32), ctypes.POINTER(_I32),
                                ctypes.POINTER(_I32)]),
+    "sd_debug_last_route": (_I32, []),
     "sd_debug_fastdiv": (_U32, [_U32, _U32]),
 }
 
@@ -446,6 +449,10 @@ def sd_tuned_choice(L: int, layout: int):
     v = [ctypes.c_int32() for _ in range(4)]
     _check(lib().sd_tuned_choice(L, layout, *[ctypes.byref(x) for x in v]))
     return tuple(int(x.value) for x in v)
+
+
+def sd_debug_last_route() -> int:
+    return int(lib().sd_debug_last_route())
 
 
 def sd_debug_fastdiv(n: int, d: int) -> int:

@@ -25,6 +25,7 @@
 namespace sd {
 
 thread_local std::string g_last_error;
+static thread_local sd_route g_last_route = SD_ROUTE_NONE;
 
 sd_status fail(sd_status s, const char* fmt, ...) {
     char buf[512];
@@ -367,6 +368,7 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
     a.obs = n_rec ? obs : nullptr;
     a.obs_chain = 3ull * n_rec;
     a.obs_every = n_rec ? obs_every : 1u;
+    g_last_route = SD_ROUTE_AHEAD;
     return run_ahead(a, step0, k_steps, scratch, kAheadBytes, st, done);
 }
 
@@ -435,6 +437,7 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
     n_launch += n_launch % 2;
     if (n_launch > n_fused)   // one step per launch and an odd count: leave one more step to the half-steps
         n_launch = --n_fused;
+    g_last_route = n_fused ? SD_ROUTE_BANDS : SD_ROUTE_HALF_STEPS;
     if (n_fused) {
         BandArgs ba;
         std::memset(&ba, 0, sizeof ba);
@@ -531,6 +534,7 @@ constexpr uint64_t kAheadDraws = 2048;
 sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t layout, double J, double q,
                     uint64_t seed, uint32_t stream, uint64_t step0, uint32_t k_steps, int64_t* obs,
                     uint32_t obs_every, uint32_t flags, void* hip_stream, bool no_alloc) {
+    g_last_route = SD_ROUTE_NONE;
     sd_status s = check_lattice(sigma, L, layout, name);
     if (s == SD_OK)
         s = check_lattice(tau, L, layout, name);
@@ -573,6 +577,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
             return SD_OK;
     }
     if (ahead_ok && small_supported(L)) {
+        g_last_route = SD_ROUTE_SMALL;
         const hipError_t e = launch_small_chain(sigma, tau, L, layout == SD_I8, J, q, seed, stream, step0, k_steps,
                                                 k_steps >= obs_every ? obs : nullptr, obs_every, flags, st);
         return e == hipSuccess ? SD_OK : hip_fail(e, name);
@@ -587,6 +592,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     if (lds_ok) {
         if (k_steps == 0)
             return SD_OK;
+        g_last_route = SD_ROUTE_LDS;
         hipError_t e = launch_single_chain_lds(sigma, tau, L, klay == kLayI8Row, J, q, seed, stream, step0, k_steps,
                                                n_rec ? obs : nullptr, obs_every, flags, ch.threads, st);
         return e == hipSuccess ? SD_OK : hip_fail(e, name);
@@ -630,6 +636,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
         if (e != hipSuccess)
             return hip_fail(e, name);
     }
+    g_last_route = k_steps ? SD_ROUTE_HALF_STEPS : SD_ROUTE_NONE;
     // the table and keys once; only the time index changes from step to step
     const DrawParams base = dynamics_params(J, q, seed, stream, 0u, flags & SD_FLAG_COMPLEMENT_RNG);
     const bool general = (flags & SD_FLAG_GENERAL_COMPARE) != 0;
@@ -757,6 +764,7 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
                       const double* J, const double* q, uint64_t seed, const uint32_t* streams, uint64_t step0,
                       uint32_t k_steps, int64_t* obs, uint32_t obs_every, uint32_t flags, void* hip_stream) {
     const char* name = "sd_run_many";
+    g_last_route = SD_ROUTE_NONE;
     if (n_chains < 1 || n_chains > (int32_t)kManyMax)
         return fail(SD_EINVAL, "%s: n_chains must lie in [1, %u]", name, kManyMax);
     if (!sigma || !tau || !J || !q || !streams)
@@ -1068,6 +1076,8 @@ sd_status sd_tuned_choice(int32_t L, int32_t layout, int32_t* mode, int32_t* wid
     if (threads) *threads = (int32_t)c.threads;
     return SD_OK;
 }
+
+int32_t sd_debug_last_route(void) { return g_last_route; }
 
 uint32_t sd_debug_fastdiv(uint32_t n, uint32_t d) {
     if (d == 0)

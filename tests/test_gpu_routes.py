@@ -243,6 +243,31 @@ def test_several_chains_drawn_ahead(L, layout, n):
         assert torch.equal(one, sig[a]) and torch.equal(two, tau[a]) and torch.equal(rec, obs[a])
 
 
+@pytest.mark.parametrize("L,layout,k,route", [
+    (8, sd.SD_P64, 1100, sd.SD_ROUTE_AHEAD), (8, sd.SD_P64, 1000, sd.SD_ROUTE_SMALL), (32, sd.SD_P32, 300, sd.SD_ROUTE_AHEAD),
+    (32, sd.SD_P64, 63, sd.SD_ROUTE_SMALL), (64, sd.SD_I8, 16, sd.SD_ROUTE_AHEAD), (64, sd.SD_I8, 15, sd.SD_ROUTE_SMALL),
+    (9, sd.SD_I8, 40, sd.SD_ROUTE_AHEAD), (65, sd.SD_I8, 33, sd.SD_ROUTE_AHEAD), (136, sd.SD_P64, 30, sd.SD_ROUTE_AHEAD),
+    (360, sd.SD_P64, 20, sd.SD_ROUTE_AHEAD), (362, sd.SD_I8, 20, sd.SD_ROUTE_AHEAD), (363, sd.SD_I8, 3, sd.SD_ROUTE_HALF_STEPS),
+    (368, sd.SD_P64, 3, sd.SD_ROUTE_HALF_STEPS), (384, sd.SD_P64, 3, sd.SD_ROUTE_BANDS), (384, sd.SD_I8, 2, sd.SD_ROUTE_HALF_STEPS),
+    (4096, sd.SD_P64, 3, sd.SD_ROUTE_BANDS), (4160, sd.SD_P64, 3, sd.SD_ROUTE_HALF_STEPS)])
+def test_route_by_size(L, layout, k, route):
+    # the kernels that the runs of the tests around this one take, at the sizes
+    # where they change hands
+    print(f"route L={L} layout={layout} k={k}", flush=True)
+    sigma, tau = sd.new_lattice(L, layout), sd.new_lattice(L, layout)
+    sd.sd_init(sigma, L, layout, sd.SD_INIT_UP)
+    sd.sd_run(sigma, tau, L, layout, 0.4, 0.6, SEED, 1, 0, k)
+    assert sd.sd_debug_last_route() == route
+    if route != sd.SD_ROUTE_SMALL:   # a call of several chains has no route of its own for short runs
+        sd.sd_run_many([sigma], [tau], L, layout, [0.4], [0.6], SEED, [1], 0, k)
+        assert sd.sd_debug_last_route() == route
+    sd.sd_run(sigma, tau, L, layout, 0.4, 0.6, SEED, 1, 0, k, None, 0, sd.SD_FLAG_GLOBAL_KERNELS)
+    assert sd.sd_debug_last_route() == sd.SD_ROUTE_HALF_STEPS
+    with pytest.raises(sd.ShakenError):
+        sd.sd_run(sigma, sigma, L, layout, 0.4, 0.6, SEED, 1, 0, k)
+    assert sd.sd_debug_last_route() == sd.SD_ROUTE_NONE
+
+
 def test_more_streams_than_scratch_buffers():
     # the scratch of drawn-ahead runs is made for a bounded number of streams;
     # runs on further ones take other kernels and give the same chains
