@@ -121,9 +121,9 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
  * (lattices of up to 2048 64-site words, L = 362 and below, are drawn ahead:
  * the device computes, round by round, whether each site's uniform lies below
  * each of the six thresholds, and one workgroup picks the chain's bits, through
- * a 16 MiB device buffer the library allocates once per (device, stream) for
- * at most 16 streams and keeps; without it (under stream capture, on further
- * streams) and for lattices of 64 words in short runs a single
+ * a 16 MiB device buffer the library keeps for each of the first 16 streams of
+ * a device, and four that further streams take in turn; without one (under
+ * stream capture) and for lattices of 64 words in short runs a single
  * workgroup with the lattices in LDS does both, where they fit; larger lattices
  * use two grid-wide launches per step and, with obs, one more launch per chunk
  * of records, whose partial sums wait in a 512 KiB device buffer the library

@@ -4,7 +4,6 @@
 #include "shaken.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -310,20 +309,73 @@ void WorkspaceUse::release() {
     ws_ = nullptr;
 }
 
-void* ahead_scratch(Workspace& ws) {
-    static std::atomic<uint32_t> made{0};
-    if (ws.ahead)
-        return ws.ahead;
-    if (made.fetch_add(1) >= kAheadBuffers) {
-        made.fetch_sub(1);
-        return nullptr;
+// A scratch buffer that calls on several streams borrow in turn.
+struct AheadShared {
+    std::mutex mu;   // held while a borrower enqueues
+    void* p = nullptr;
+    hipEvent_t last_use = nullptr;
+};
+
+AheadScratch::AheadScratch(Workspace& ws, hipStream_t st) : st_(st) {
+    struct Pool {
+        std::mutex mu;
+        uint32_t own = 0, next = 0;   // streams with a buffer of their own; the shared one to borrow next
+        AheadShared shared[kAheadShared];
+    };
+    static std::mutex mu;
+    static std::map<int, Pool*> pools;   // kept until the process ends
+    p_ = ws.ahead;
+    int dev = 0;
+    if (p_ || hipGetDevice(&dev) != hipSuccess)
+        return;
+    Pool* pool = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        Pool*& at = pools[dev];
+        if (!at)
+            at = new Pool;
+        pool = at;
     }
-    if (malloc_beside_captures(&ws.ahead, kAheadBytes) != hipSuccess) {
+    {
+        std::lock_guard<std::mutex> lock(pool->mu);
+        if (pool->own < kAheadBuffers) {
+            if (malloc_beside_captures(&ws.ahead, kAheadBytes) == hipSuccess) {
+                ++pool->own;
+                p_ = ws.ahead;
+            } else {
+                (void)hipGetLastError();
+                ws.ahead = nullptr;
+            }
+            return;
+        }
+        shared_ = &pool->shared[pool->next++ % kAheadShared];
+    }
+    shared_->mu.lock();
+    AheadShared& s = *shared_;
+    hipError_t e = s.last_use ? hipSuccess : hipEventCreateWithFlags(&s.last_use, hipEventDisableTiming);
+    if (e == hipSuccess && !s.p)
+        e = malloc_beside_captures(&s.p, kAheadBytes);
+    if (e == hipSuccess)
+        e = hipStreamWaitEvent(st, s.last_use, 0);
+    if (e == hipSuccess) {
+        p_ = s.p;
+        return;
+    }
+    (void)hipGetLastError();
+    s.mu.unlock();
+    shared_ = nullptr;
+}
+
+AheadScratch::~AheadScratch() {
+    if (!shared_)
+        return;
+    // without the event nothing tells the next borrower when this one is done:
+    // the buffer is left behind
+    if (hipEventRecord(shared_->last_use, st_) != hipSuccess) {
         (void)hipGetLastError();
-        ws.ahead = nullptr;
-        made.fetch_sub(1);
+        shared_->p = nullptr;
     }
-    return ws.ahead;
+    shared_->mu.unlock();
 }
 
 // 64-bit words at their alignment, which 32-bit-word lattices may lack.
@@ -347,8 +399,8 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
     const WorkspaceUse use(st);
     if (!use.get())
         return hipSuccess;
-    void* scratch = ahead_scratch(*use.get());
-    if (!scratch)
+    const AheadScratch scratch(*use.get(), st);
+    if (!scratch.get())
         return hipSuccess;
     const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
     AheadArgs a;
@@ -369,7 +421,7 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
     a.obs_chain = 3ull * n_rec;
     a.obs_every = n_rec ? obs_every : 1u;
     g_last_route = SD_ROUTE_AHEAD;
-    return run_ahead(a, step0, k_steps, scratch, kAheadBytes, st, done);
+    return run_ahead(a, step0, k_steps, scratch.get(), kAheadBytes, st, done);
 }
 
 // Scratch memory of sd_run_noalloc: a file-scope device array (each device

@@ -44,7 +44,7 @@ SmallArgs small_args(int32_t L, double J, double q, uint64_t seed, uint32_t stre
 constexpr size_t kPartialsWords = 65536;
 struct Workspace {
     int64_t* p = nullptr;
-    void* ahead = nullptr;   // kAheadBytes, made by the first run that draws ahead (ahead_scratch)
+    void* ahead = nullptr;   // kAheadBytes, made by the first run that draws ahead (AheadScratch)
     std::mutex mu;
     hipEvent_t last_use = nullptr;   // hipStreamPerThread only: behind the last call's work
     bool lost = false;               // ... could not be recorded: later calls have nothing to wait for
@@ -79,12 +79,28 @@ private:
     hipStream_t st_ = nullptr;
 };
 
-// Scratch of the draw-ahead runs (class masks of two rounds), kept with the
-// workspace; the caller holds ws.mu.  At most kAheadBuffers exist in a process
-// (256 MiB); null past that or out of memory, and the caller takes the kernels
-// that need none.
+// Scratch of the draw-ahead runs (class masks of two rounds), held while a call
+// enqueues.  The first kAheadBuffers streams of a device keep a buffer each with
+// their workspace (the caller holds it); calls on later ones borrow one of
+// kAheadShared, each behind an event that its last borrower left, so that
+// speed does not depend on which streams came first, used ones and destroyed
+// ones alike, and a device holds 320 MiB at most.  (An event per call costs a
+// stream 2.9 us, which the streams with buffers of their own need not pay.)
+// get() is null out of memory, and the caller takes the kernels that need none.
 constexpr size_t kAheadBytes = 16u << 20;
-constexpr uint32_t kAheadBuffers = 16;
-void* ahead_scratch(Workspace& ws);
+constexpr uint32_t kAheadBuffers = 16, kAheadShared = 4;
+struct AheadShared;
+class AheadScratch {
+public:
+    AheadScratch(Workspace& ws, hipStream_t st);
+    ~AheadScratch();
+    AheadScratch(const AheadScratch&) = delete;
+    void* get() const { return p_; }
+
+private:
+    void* p_ = nullptr;
+    AheadShared* shared_ = nullptr;   // borrowed from
+    hipStream_t st_ = nullptr;
+};
 
 }  // namespace sd

@@ -288,6 +288,37 @@ def test_more_streams_than_scratch_buffers():
         assert all(torch.equal(x, y) for x, y in zip(o, out[0]))
 
 
+def test_every_stream_draws_ahead():
+    # more streams than scratch buffers, busy at the same time with chains of
+    # their own, destroyed and made anew: all draw ahead, and no run takes another's buffer
+    L, k, n = 200, 40, 24
+    first = sd.new_lattice(L, sd.SD_P64)
+    sd.sd_init(first, L, sd.SD_P64, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    hip = ctypes.CDLL("libamdhip64.so")
+
+    def new():
+        return first.clone(), torch.zeros_like(first), torch.full((k, 3), -1, dtype=torch.int64, device="cuda")
+
+    want = [new() for _ in range(n)]
+    for i, w in enumerate(want):
+        sd.sd_run(w[0], w[1], L, sd.SD_P64, 0.4, 0.6, SEED, i, 0, k, w[2], 1, sd.SD_FLAG_GLOBAL_KERNELS)
+    for _ in range(2):
+        streams = [ctypes.c_void_p() for _ in range(n)]
+        for s in streams:
+            assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+        got = [[new() for _ in range(3)] for _ in range(n)]
+        torch.cuda.synchronize()
+        for r in range(3):
+            for i, s in enumerate(streams):
+                g = got[i][r]
+                sd.sd_run(g[0], g[1], L, sd.SD_P64, 0.4, 0.6, SEED, i, 0, k, g[2], 1, hip_stream=s.value)
+                assert sd.sd_debug_last_route() == sd.SD_ROUTE_AHEAD, i
+        torch.cuda.synchronize()
+        for i, s in enumerate(streams):
+            assert all(torch.equal(a, b) for g in got[i] for a, b in zip(g, want[i])), i
+            assert hip.hipStreamDestroy(s) == 0
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
