@@ -206,9 +206,9 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
  * and the number of workgroups).  Each candidate runs a few steps on scratch
  * lattices (allocated and freed here) with HIP events; the fastest is used by
  * every later sd_run of this process with these (L, layout) and stored under
- * a "run:<arch>:L=..:layout=.." key in the JSON file tune_cache_path (NULL:
- * not stored); a later sd_tune finding the key there takes it without
- * measuring.  Synchronises the stream.  Results of sd_run do not depend on
+ * a "run2:<arch>:L=..:layout=.." key in the JSON file tune_cache_path (NULL:
+ * not stored; the number tells the library's sets of kernels apart); a later
+ * sd_tune finding the key there takes it without measuring.  Synchronises the stream.  Results of sd_run do not depend on
  * the choice.
  */
 SD_API sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* hip_stream);

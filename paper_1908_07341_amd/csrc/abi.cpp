@@ -984,7 +984,11 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess)
         return hip_fail(e, "sd_tune");
-    const std::string key = "run:" + device_arch() + ":L=" + std::to_string(L) + ":layout=" + std::to_string(layout);
+    // run2: the second set of kernels.  A choice made among others is no choice
+    // among these: a mode 2 entry from before the runs of several half-steps a
+    // launch would keep them off, with workgroups counted for wider tiles (2048^2: 64
+    // where the rule wants 256).  Raised whenever candidates or tiles change.
+    const std::string key = "run2:" + device_arch() + ":L=" + std::to_string(L) + ":layout=" + std::to_string(layout);
     auto encode = [](const RunChoice& c) -> long {
         return (long)c.mode | ((long)(c.width == 32) << 2) | ((long)c.blocks << 3) | ((long)(c.threads / 64) << 24);
     };

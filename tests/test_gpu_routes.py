@@ -1,6 +1,7 @@
 """GPU parity of the size-dependent kernel variants at the edges of their
 ranges."""
 import ctypes
+import json
 import threading
 
 import numpy as np
@@ -317,6 +318,22 @@ def test_every_stream_draws_ahead():
         for i, s in enumerate(streams):
             assert all(torch.equal(a, b) for g in got[i] for a, b in zip(g, want[i])), i
             assert hip.hipStreamDestroy(s) == 0
+
+
+def test_tuned_choices_of_other_kernel_sets_are_measured_again(tmp_path):
+    # an entry that an earlier library left (one launch per half-step, 16
+    # workgroups for 256-word tiles) is no choice among the present kernels
+    L, layout, path = 768, sd.SD_P64, str(tmp_path / "tune.json")
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    old = 2 | (16 << 3) | (4 << 24)
+    with open(path, "w") as f:
+        json.dump({f"run:{arch}:L={L}:layout={layout}": old}, f)
+    sd.sd_tune(L, layout, path)
+    mode, _, blocks, _ = sd.sd_tuned_choice(L, layout)
+    assert (mode, blocks) != (2, 16)
+    entries = json.load(open(path))
+    assert entries[f"run:{arch}:L={L}:layout={layout}"] == old   # left to the library that wrote it
+    assert f"run2:{arch}:L={L}:layout={layout}" in entries
 
 
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
