@@ -203,7 +203,9 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
  * (drawn ahead, or whole steps in bands of rows) where it has them for this L,
  * or one grid-wide launch per half-step (64- or 32-bit word kernels when
  * L % 64 == 0 — the same bytes —
- * and the number of workgroups).  Each candidate runs a few steps on scratch
+ * and the number of workgroups); for sizes that are drawn ahead also how
+ * sd_run_noalloc and captured runs, which cannot be, execute them (the workgroup
+ * size of the kernel with the lattices in LDS, or the grid).  Each candidate runs a few steps on scratch
  * lattices (allocated and freed here) with HIP events; the fastest is used by
  * every later sd_run of this process with these (L, layout) and stored under
  * a "run2:<arch>:L=..:layout=.." key in the JSON file tune_cache_path (NULL:

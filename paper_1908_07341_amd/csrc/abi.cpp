@@ -173,6 +173,9 @@ struct RunChoice {
                             // 2: grid kernels
     int width = 64;         // packed layouts with L % 64 == 0: 64- or 32-bit word kernels
     uint32_t blocks = 0;    // grid kernels: workgroups (0 = default)
+    // runs that cannot draw ahead by the whole device (sd_run_noalloc, captured
+    // runs, the six-class compare) of sizes that otherwise do:
+    int mode_free = 0;      // as mode, 1 being the kernels that need no scratch
     uint32_t threads = 256; // LDS kernel: workgroup size
 };
 
@@ -613,11 +616,12 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     // more, and lattices past 64 words, with the whole device drawing (k_ahead,
     // needs scratch), the others and those without scratch in one workgroup if
     // they have at most 64 words (k_small).  The six-class cross-check keeps the general kernels.
-    const bool ahead_ok = ahead_lattice(L, layout, sigma, tau) && ch.mode != 2 &&
+    const bool ahead_ok = ahead_lattice(L, layout, sigma, tau) &&
                           !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE));
     if (ahead_ok && k_steps == 0)
         return SD_OK;
-    if (ahead_ok && !no_alloc && (!small_supported(L) || 2ull * k_steps * lattice_words((uint32_t)L) >= kAheadDraws)) {
+    if (ahead_ok && !no_alloc && ch.mode != 2 &&
+        (!small_supported(L) || 2ull * k_steps * lattice_words((uint32_t)L) >= kAheadDraws)) {
         uint32_t T[1][6];
         threshold_table(J, q, T[0]);
         bool done = false;
@@ -628,7 +632,8 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
         if (done)
             return SD_OK;
     }
-    if (ahead_ok && small_supported(L)) {
+    const int mode = !ahead_size(L) || (ahead_ok && !no_alloc && ch.mode == 2 && !capturing(st)) ? ch.mode : ch.mode_free;
+    if (ahead_ok && mode != 2 && small_supported(L)) {
         g_last_route = SD_ROUTE_SMALL;
         const hipError_t e = launch_small_chain(sigma, tau, L, layout == SD_I8, J, q, seed, stream, step0, k_steps,
                                                 k_steps >= obs_every ? obs : nullptr, obs_every, flags, st);
@@ -640,7 +645,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
     const bool lds_ok = (klay == kLayP64 || klay == kLayI8Row || (klay == kLayP32 && L % 64 == 0) ||
                          klay == kLayBits) &&
-                        n_words <= kSingleLdsMaxWords && ch.mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS);
+                        n_words <= kSingleLdsMaxWords && mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS);
     if (lds_ok) {
         if (k_steps == 0)
             return SD_OK;
@@ -666,7 +671,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     // against this: 512^2 3.8 -> 1.6, 1024^2 3.9 -> 1.7, 2048^2 4.0 -> 2.2,
     // 4096^2 5.9 -> 3.9).
     const bool whole_words = klay == kLayI8Row || (klay == kLayP64 && words_aligned(sigma, tau));
-    if (ch.mode != 2 && whole_words && k_steps >= 3 &&
+    if (mode != 2 && whole_words && k_steps >= 3 &&
         !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE))) {
         uint32_t n_cu = 0;
         size_t max_lds = 0;
@@ -990,7 +995,8 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
     // where the rule wants 256).  Raised whenever candidates or tiles change.
     const std::string key = "run2:" + device_arch() + ":L=" + std::to_string(L) + ":layout=" + std::to_string(layout);
     auto encode = [](const RunChoice& c) -> long {
-        return (long)c.mode | ((long)(c.width == 32) << 2) | ((long)c.blocks << 3) | ((long)(c.threads / 64) << 24);
+        return (long)c.mode | ((long)(c.width == 32) << 2) | ((long)c.blocks << 3) | ((long)(c.threads / 64) << 24) |
+               ((long)c.mode_free << 32);
     };
     auto decode = [](long v) {
         RunChoice c;
@@ -1000,6 +1006,7 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
         c.threads = (uint32_t)(((v >> 24) & 0xFF) * 64);
         if (c.threads == 0)
             c.threads = 256;
+        c.mode_free = (int)((v >> 32) & 3);
         return c;
     };
     const long cached = tune_cache_get(tune_cache_path, key);
@@ -1021,6 +1028,22 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
         c.mode = 1;
         cands.push_back(c);
     }
+    // the same without scratch, where that is another route: workgroups of the
+    // LDS kernel, or k_small and the bands, which have no choice
+    const size_t first_free = cands.size();
+    if (ahead_size(L)) {
+        const bool lds = !small_supported(L) && n_words <= kSingleLdsMaxWords && L % 8 == 0 &&
+                         (layout == SD_I8 ? L % 64 == 0 : layout == SD_P64 || L % 64 == 0);
+        for (uint32_t t : {128u, 256u, 512u}) {
+            if (!lds && (t != 256u || !(small_supported(L) || band_plan(L, 1u, n_cu).bands)))
+                continue;
+            RunChoice c;
+            c.mode_free = 1;
+            c.threads = t;
+            cands.push_back(c);
+        }
+    }
+    const size_t first_grid = cands.size();
     for (int width : {64, 32}) {
         if (width == 32 && (layout == SD_I8 || L % 64 != 0))
             continue;
@@ -1039,7 +1062,7 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
                 continue;
             last = launched;
             RunChoice c;
-            c.mode = 2;
+            c.mode = c.mode_free = 2;
             c.width = width;
             c.blocks = launched;
             cands.push_back(c);
@@ -1076,7 +1099,8 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
             float ms = -1.0f;
             e = hipEventRecord(e0, st);
             if (e != hipSuccess) break;
-            s = sd_run(sig, tau, L, layout, 0.5, 0.5, 1, 0, 0, k, nullptr, 0, 0, hip_stream);
+            s = run_chain("sd_tune", sig, tau, L, layout, 0.5, 0.5, 1, 0, 0, k, nullptr, 0, 0, hip_stream,
+                          ci >= first_free && ci < first_grid);
             if (s != SD_OK) break;
             e = hipEventRecord(e1, st);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1086,12 +1110,26 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
                 fastest[ci] = ms;
         }
     }
+    // the fastest of cands[from .. to) and the fastest grid; -1: none was timed
+    auto fastest_of = [&](size_t from, size_t to) {
+        int at = -1;
+        for (size_t ci = 0; ci < cands.size(); ++ci)
+            if (((ci >= from && ci < to) || ci >= first_grid) && fastest[ci] > 0.0f &&
+                (at < 0 || fastest[ci] < fastest[(size_t)at]))
+                at = (int)ci;
+        return at;
+    };
     RunChoice best;
-    double best_t = -1.0;
-    for (size_t ci = 0; ci < cands.size(); ++ci) {
-        if (fastest[ci] > 0.0f && (best_t < 0.0 || fastest[ci] < best_t)) {
-            best_t = fastest[ci];
-            best = cands[ci];
+    const int with = fastest_of(0, first_free), without = fastest_of(first_free, first_grid);
+    const double best_t = with < 0 ? -1.0 : (double)fastest[(size_t)with];
+    if (with >= 0) {
+        best = cands[(size_t)with];
+        const RunChoice& f = cands[(size_t)(without < 0 ? with : without)];
+        best.mode_free = f.mode_free;
+        best.threads = f.threads;
+        if (f.mode_free == 2) {   // the fastest grid, in either case
+            best.width = f.width;
+            best.blocks = f.blocks;
         }
     }
     if (e0) (void)hipEventDestroy(e0);

@@ -336,6 +336,37 @@ def test_tuned_choices_of_other_kernel_sets_are_measured_again(tmp_path):
     assert f"run2:{arch}:L={L}:layout={layout}" in entries
 
 
+@pytest.mark.parametrize("L,layout,route", [(64, sd.SD_P64, sd.SD_ROUTE_SMALL), (192, sd.SD_P64, sd.SD_ROUTE_LDS),
+                                            (256, sd.SD_P64, sd.SD_ROUTE_LDS), (200, sd.SD_P64, sd.SD_ROUTE_LDS),
+                                            (320, sd.SD_P64, sd.SD_ROUTE_BANDS), (101, sd.SD_I8, sd.SD_ROUTE_HALF_STEPS)])
+def test_tuned_runs_without_scratch(tmp_path, L, layout, route):
+    # sizes that draw ahead when they can: runs that cannot (no allocation, or
+    # captured) are tuned among the kernels that they can take, and the eager
+    # runs stay drawn ahead; sixteen tiles of 256^2 want eight wavefronts
+    print(f"tuned without scratch L={L} layout={layout}", flush=True)
+    path, k = str(tmp_path / "tune.json"), 20
+    sd.sd_tune(L, layout, path)
+    choice = sd.sd_tuned_choice(L, layout)
+    print("tuned", choice, open(path).read(), flush=True)
+    assert choice[0] == 1
+    if L == 256:
+        assert choice[3] == 512
+    first = sd.new_lattice(L, layout)
+    sd.sd_init(first, L, layout, sd.SD_INIT_RANDOM, 0.5, SEED, 1)
+    out = []
+    for run, flags, want in ((sd.sd_run, 0, sd.SD_ROUTE_AHEAD), (sd.sd_run_noalloc, 0, route),
+                             (sd.sd_run, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS)):
+        sigma, tau = first.clone(), torch.zeros_like(first)
+        obs = torch.full((k, 3), -1, dtype=torch.int64, device="cuda")
+        run(sigma, tau, L, layout, 0.4, 0.6, SEED, 1, 0, k, obs, 1, flags)
+        assert sd.sd_debug_last_route() == want
+        out.append((sigma, tau, obs))
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(o, out[0]))
+    sd.sd_tune(L, layout, path)   # from the cache
+    assert sd.sd_tuned_choice(L, layout) == choice
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
