@@ -581,6 +581,22 @@ static hipError_t run_many_grid(const ManyChains& mc, const Geom& G, int klay, b
 // 100 steps 25 against 20).
 constexpr uint64_t kAheadDraws = 2048;
 
+// The shortest runs past 64 words pay more for drawing ahead, a launch each to
+// draw, to walk and to take records, with one workgroup walking, than they save.
+// One step goes to the LDS kernel where that takes the lattice (us a call, drawn
+// ahead against it: 128^2 9.6 7.5, recorded 13.8 8.7; 200^2 15.5 10.5, 18.8 11.0),
+// and past 512 words to half-steps where it does not (333^2 int8 23.1 13.3,
+// recorded 27.2 19.6; 200^2 int8 18.1 10.5; up to there drawn ahead, 180^2 int8
+// 16.2 18.4, 127^2 13.9 19.1).  Two recorded steps go to the LDS kernel where it
+// has four tiles or fewer (128^2 13.6 10.6; 136^2 and up drawn ahead).
+static bool ahead_steps(uint32_t n_words, uint32_t k_steps, bool records, bool lds) {
+    if (n_words <= 64u || k_steps > 2u)
+        return true;
+    if (k_steps == 1u)
+        return !lds && n_words <= 512u;
+    return !(records && lds && n_words <= 256u);
+}
+
 // The step loop behind sd_run and sd_run_noalloc.  The grid kernels of a
 // recorded half-step B leave per-workgroup partial sums in a device buffer of
 // kPartialsWords int64: the per-(device, stream) workspace for sd_run (null
@@ -612,15 +628,19 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                                         : kLayI8Any)
                                  : kernel_layout(L, layout, sigma);
     const RunChoice ch = run_choice(L, layout);
+    const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
+    const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
+    const bool lds_size = n_words <= kSingleLdsMaxWords &&
+                          (klay == kLayP64 || klay == kLayI8Row || (klay == kLayP32 && L % 64 == 0) || klay == kLayBits);
     // Small lattices draw ahead of the chain: runs of kAheadDraws word draws and
     // more, and lattices past 64 words, with the whole device drawing (k_ahead,
-    // needs scratch), the others and those without scratch in one workgroup if
+    // needs scratch, see ahead_steps), the others and those without scratch in one workgroup if
     // they have at most 64 words (k_small).  The six-class cross-check keeps the general kernels.
     const bool ahead_ok = ahead_lattice(L, layout, sigma, tau) &&
                           !(flags & (SD_FLAG_GLOBAL_KERNELS | SD_FLAG_GENERAL_COMPARE));
     if (ahead_ok && k_steps == 0)
         return SD_OK;
-    if (ahead_ok && !no_alloc && ch.mode != 2 &&
+    if (ahead_ok && !no_alloc && ch.mode != 2 && ahead_steps(n_words, k_steps, n_rec != 0, lds_size) &&
         (!small_supported(L) || 2ull * k_steps * lattice_words((uint32_t)L) >= kAheadDraws)) {
         uint32_t T[1][6];
         threshold_table(J, q, T[0]);
@@ -641,12 +661,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     }
     if (layout != SD_I8 && L % 64 == 0)
         klay = ch.width == 32 ? kLayP32 : kLayP64;
-    const uint32_t n_rec = obs ? k_steps / obs_every : 0u;
-    const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
-    const bool lds_ok = (klay == kLayP64 || klay == kLayI8Row || (klay == kLayP32 && L % 64 == 0) ||
-                         klay == kLayBits) &&
-                        n_words <= kSingleLdsMaxWords && mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS);
-    if (lds_ok) {
+    if (lds_size && mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS)) {
         if (k_steps == 0)
             return SD_OK;
         g_last_route = SD_ROUTE_LDS;
@@ -881,7 +896,8 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
                     "the scratch buffer", name, mc.n_chains, mc.blocks_per_chain, kPartialsWords);
     if (k_steps == 0)
         return SD_OK;
-    bool ahead = !(flags & SD_FLAG_GENERAL_COMPARE);
+    bool ahead = !(flags & SD_FLAG_GENERAL_COMPARE) &&
+                 ahead_steps((uint32_t)(((uint64_t)L * (uint64_t)L) / 64u), k_steps, n_rec != 0, false);
     for (int32_t c = 0; c < n_chains; ++c)
         ahead = ahead && ahead_lattice(L, layout, sigma[c], tau[c]);
     if (ahead) {

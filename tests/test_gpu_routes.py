@@ -367,6 +367,38 @@ def test_tuned_runs_without_scratch(tmp_path, L, layout, route):
     assert sd.sd_tuned_choice(L, layout) == choice
 
 
+@pytest.mark.parametrize("L,layout,k,every,route,many", [
+    (64, sd.SD_I8, 1, 1, sd.SD_ROUTE_SMALL, sd.SD_ROUTE_AHEAD), (33, sd.SD_I8, 1, 1, sd.SD_ROUTE_AHEAD, sd.SD_ROUTE_AHEAD),
+    (72, sd.SD_P64, 1, 1, sd.SD_ROUTE_LDS, sd.SD_ROUTE_AHEAD), (88, sd.SD_P64, 1, 0, sd.SD_ROUTE_LDS, sd.SD_ROUTE_AHEAD),
+    (181, sd.SD_I8, 1, 1, sd.SD_ROUTE_AHEAD, sd.SD_ROUTE_AHEAD), (182, sd.SD_I8, 1, 1, sd.SD_ROUTE_HALF_STEPS, sd.SD_ROUTE_HALF_STEPS),
+    (128, sd.SD_I8, 2, 1, sd.SD_ROUTE_LDS, sd.SD_ROUTE_AHEAD), (128, sd.SD_I8, 2, 0, sd.SD_ROUTE_AHEAD, sd.SD_ROUTE_AHEAD),
+    (136, sd.SD_P64, 2, 1, sd.SD_ROUTE_AHEAD, sd.SD_ROUTE_AHEAD), (96, sd.SD_P32, 2, 1, sd.SD_ROUTE_AHEAD, sd.SD_ROUTE_AHEAD),
+    (248, sd.SD_P64, 1, 1, sd.SD_ROUTE_LDS, sd.SD_ROUTE_HALF_STEPS), (360, sd.SD_P64, 1, 1, sd.SD_ROUTE_HALF_STEPS, sd.SD_ROUTE_HALF_STEPS),
+    (333, sd.SD_I8, 1, 0, sd.SD_ROUTE_HALF_STEPS, sd.SD_ROUTE_HALF_STEPS)])
+def test_short_runs(oracle, L, layout, k, every, route, many):
+    # runs too short to be drawn ahead, on each side of the rule
+    print(f"short run L={L} layout={layout} k={k} every={every}", flush=True)
+    start = inputs.random_lattice(L, L)
+    host = start if layout == sd.SD_I8 else inputs.pack_bits(start)
+    host = torch.from_numpy(host.reshape(-1).copy()).cuda()
+    sig, tau, rec = oracle.run(start, 0.4, 0.7, SEED, 3, 5, k, obs_every=every)
+    for call, want in (("run", route), ("many", many)):
+        sigma, t = sd.new_lattice(L, layout), sd.new_lattice(L, layout)
+        flat = [x.reshape(-1).view(host.dtype) for x in (sigma, t)]
+        flat[0].copy_(host)
+        obs = torch.full((k // every if every else 0, 3), -1, dtype=torch.int64, device="cuda")
+        if call == "run":
+            sd.sd_run(sigma, t, L, layout, 0.4, 0.7, SEED, 3, 5, k, obs if every else None, every)
+        else:
+            sd.sd_run_many([sigma], [t], L, layout, [0.4], [0.7], SEED, [3], 5, k, obs if every else None, every)
+        assert sd.sd_debug_last_route() == want, call
+        for x, w in zip(flat, (sig, tau)):
+            have = x.cpu().numpy()
+            assert np.array_equal(have.reshape(L, L) if layout == sd.SD_I8 else inputs.unpack_bits(have, L), w), call
+        if every:
+            assert np.array_equal(obs.cpu().numpy(), rec), call
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
