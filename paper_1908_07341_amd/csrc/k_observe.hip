@@ -253,6 +253,9 @@ __global__ __launch_bounds__(1024) void k_corr_row64(CorrLattices cl, uint32_t L
 // == 1: out need not be zeroed first), else added by one atomic.
 // Packed: rows are L / 32 words (L % 32 == 0); the partner row's bits from
 // column l on are a funnel shift of two of its words.
+// Sites are bound by the vector unit: row and column wrap by a compare, as the
+// rows of a workgroup's threads differ and a remainder of each took much
+// of the time (512^2 int8, l <= 256: 157 -> 94 us).
 template <int PACKED>
 __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigma, Geom G, int32_t lmax,
                                                     uint32_t row_shift, int64_t* __restrict__ out) {
@@ -264,12 +267,13 @@ __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigm
     const uint32_t rows = blockDim.x >> row_shift;                 // rows the block takes at once
     const uint32_t cols = 1u << row_shift, col = threadIdx.x & (cols - 1u);
     const uint32_t row0 = blockIdx.y * rows + (threadIdx.x >> row_shift), row_step = gridDim.y * rows;
+    auto wrap = [L](uint32_t x) { return x < L ? x : x - L; };   // x mod L for x < 2 L
     if constexpr (PACKED == 1) {
         const uint32_t* s = static_cast<const uint32_t*>(sigma);
         const uint32_t W = L / 32u;
         const uint32_t sh = l & 31u;
         for (uint32_t j = row0; j < L; j += row_step) {
-            const uint32_t jp = dir == 0 ? (j + l) % L : (j + L - l) % L;
+            const uint32_t jp = wrap(dir == 0 ? j + l : j + L - l);
             const uint32_t* row = s + (size_t)j * W;
             const uint32_t* prow = s + (size_t)jp * W;
             for (uint32_t k = col; k < W; k += cols) {
@@ -283,9 +287,9 @@ __global__ __launch_bounds__(256) void k_corr_diag(const void* __restrict__ sigm
         }
     } else {
         for (uint32_t j = row0; j < L; j += row_step) {
-            const uint32_t jp = dir == 0 ? (j + l) % L : (j + L - l) % L;
+            const uint32_t jp = wrap(dir == 0 ? j + l : j + L - l);
             for (uint32_t i = col; i < L; i += cols) {
-                const uint32_t ip = (i + l) % L;
+                const uint32_t ip = wrap(i + l);
                 const size_t a = (size_t)j * L + i, b = (size_t)jp * L + ip;
                 if constexpr (PACKED == 2) {
                     const uint64_t* s = static_cast<const uint64_t*>(sigma);
@@ -340,13 +344,14 @@ hipError_t launch_corr_diag(int layout, const void* sigma, const Geom& G, int32_
     uint32_t row_shift = 0;
     while (row_shift < 8u && (1u << row_shift) < width)
         ++row_shift;
-    // One workgroup per sum up to kDiagItems words (or sites) a lattice: one
-    // launch instead of two, no atomics (32^2 packed, l <= 16: 8.8 us with the
-    // zeroing and a workgroup per row, 3.4 so); larger lattices split their rows
-    // over about kMaxBlocks workgroups.
-    constexpr uint64_t kDiagItems = 8192;
+    // One workgroup per sum up to 8192 words or 6144 sites a lattice: one launch
+    // instead of two, no atomics (32^2 packed, l <= 16: 8.8 us with the zeroing
+    // and a workgroup per row, 3.4 so); larger lattices split their rows over
+    // about kMaxBlocks workgroups (one workgroup against several, l <= 0 and 64:
+    // 80^2 int8 10.4 and 10.7 us, 91^2 split 8.5 and 7.8).
+    const uint64_t most = layout == kLayP64 || layout == kLayP32 ? 8192u : 6144u;
     uint32_t row_blocks = 1u;
-    if ((uint64_t)width * G.L > kDiagItems) {
+    if ((uint64_t)width * G.L > most) {
         const uint32_t groups = (G.L + (256u >> row_shift) - 1u) / (256u >> row_shift);
         row_blocks = kMaxBlocks / n;
         row_blocks = row_blocks < groups ? row_blocks : groups;

@@ -415,6 +415,21 @@ def test_diagonal_correlations_one_or_many_workgroups(oracle, L, layout):
         assert np.array_equal(out.cpu().numpy().reshape(-1), oracle.corr_diag(lat, lmax).reshape(-1))
 
 
+@pytest.mark.parametrize("L,layout", [(78, sd.SD_I8), (79, sd.SD_I8), (72, sd.SD_P64), (80, sd.SD_P64), (255, sd.SD_I8),
+                                      (257, sd.SD_I8)])
+def test_diagonal_correlations_of_sites(oracle, L, layout):
+    # lattices taken site by site, on each side of one workgroup per sum and of
+    # a row per workgroup; every shift wraps somewhere
+    print(f"diagonals of sites L={L} layout={layout}", flush=True)
+    lat = inputs.random_lattice(L, L + 2)
+    host = lat if layout == sd.SD_I8 else inputs.pack_bits(lat)
+    dev = torch.from_numpy(host.reshape(-1).copy()).cuda()
+    for lmax in (1, L - 1):
+        out = torch.full((2, lmax + 1), 12345, dtype=torch.int64, device="cuda")
+        sd.sd_corr_diag(dev, L, layout, lmax, out)
+        assert np.array_equal(out.cpu().numpy().reshape(-1), oracle.corr_diag(lat, lmax).reshape(-1))
+
+
 @pytest.mark.parametrize("L,layout,n,k", [(384, sd.SD_P64, 1, 3), (448, sd.SD_I8, 7, 20), (512, sd.SD_P64, 1, 30),
                                           (576, sd.SD_I8, 5, 9), (1024, sd.SD_P64, 16, 5), (2112, sd.SD_P64, 1, 12),
                                           (4032, sd.SD_P64, 3, 4), (4096, sd.SD_I8, 1, 6)])
