@@ -378,7 +378,9 @@ __global__ __launch_bounds__(kObsThreads) void k_replica_observe(const uint64_t*
 #pragma unroll
         for (uint32_t b = 0; b < kObsPlanes; ++b)
             P[x][b] = 0u;
-    for (uint32_t k = 0; k < kObsSites; k += 4) {
+    // a workgroup with few sites has no more rounds than those take
+    const uint32_t rounds = (n - s0 + kObsThreads - 1u) / kObsThreads;
+    for (uint32_t k = 0; k < kObsSites && k < rounds; k += 4) {
         uint64_t w[4][4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
