@@ -118,7 +118,8 @@ SD_API sd_status sd_half_step(const void* src, void* dst, int32_t L, int32_t lay
 
 /*
  * k_steps full steps of one chain, steps step0 .. step0+k_steps-1, in place:
- * (lattices of up to 2048 64-site words, L = 362 and below, are drawn ahead:
+ * (lattices of up to 2048 64-site words, L = 362 and below, are drawn ahead,
+ * the shortest runs excepted:
  * the device computes, round by round, whether each site's uniform lies below
  * each of the six thresholds, and one workgroup picks the chain's bits, through
  * a 16 MiB device buffer the library keeps for each of the first 16 streams of
@@ -171,8 +172,9 @@ SD_API sd_status sd_run_noalloc(void* sigma, void* tau, int32_t L, int32_t layou
  * streams[a], step0, k_steps, ...), but every launch covers all the chains,
  * so that lattices of a few thousand words, which alone fill a small part of
  * the device, run together at the launch rate of one.  Lattices of up to 2048
- * words are drawn ahead, one workgroup per chain, as in sd_run.  Larger ones
- * whose rows are whole 64-bit words, at most 64 of them (packed, or int8 with
+ * words are drawn ahead, one workgroup per chain, as in sd_run (not one step of
+ * more than 512 words, nor ten steps and more of nine chains and more of 320^2,
+ * which go as larger ones do).  Larger ones whose rows are whole 64-bit words, at most 64 of them (packed, or int8 with
  * 16-byte aligned lattices), run all but the last step as whole steps, up to
  * eight per launch: each workgroup takes a band of rows
  * plus one halo row per step on each side into LDS and recomputes the halo

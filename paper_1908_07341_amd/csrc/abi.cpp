@@ -896,8 +896,17 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
                     "the scratch buffer", name, mc.n_chains, mc.blocks_per_chain, kPartialsWords);
     if (k_steps == 0)
         return SD_OK;
-    bool ahead = !(flags & SD_FLAG_GENERAL_COMPARE) &&
-                 ahead_steps((uint32_t)(((uint64_t)L * (uint64_t)L) / 64u), k_steps, n_rec != 0, false);
+    const bool whole_words = (layout == SD_P64 && L % 64 == 0) || klay == kLayI8Row;
+    const uint32_t n_words = (uint32_t)(((uint64_t)L * (uint64_t)L) / 64u);
+    bool ahead = !(flags & SD_FLAG_GENERAL_COMPARE) && ahead_steps(n_words, k_steps, n_rec != 0, false);
+    // Past one word a thread of the walker, nine chains and more leave the scratch
+    // to rounds of ten half-steps and fewer; whole steps in bands, where rows are
+    // whole words (320^2), are quicker in runs of ten steps and more (100 steps,
+    // recorded, drawn ahead against bands: 8 chains 354 and 354 us, 9 364 and 356,
+    // 16 523 and 375; 5 steps of 16 44 and 47).  Rows of other lengths have no
+    // bands, and one word a thread walks faster (256^2: ahead at every count).
+    if (whole_words && n_words > 1024u && n_chains > 8 && k_steps >= 10u)
+        ahead = false;
     for (int32_t c = 0; c < n_chains; ++c)
         ahead = ahead && ahead_lattice(L, layout, sigma[c], tau[c]);
     if (ahead) {
@@ -918,7 +927,6 @@ sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_chains, in
                         "eager call on it, or out of device memory)", name);
         partials = use.get() ? use.get()->p : nullptr;   // null: a captured run takes atomics
     }
-    const bool whole_words = (layout == SD_P64 && L % 64 == 0) || klay == kLayI8Row;
     const hipError_t e = run_many_grid(mc, G, klay, whole_words, paired, L, seed, step0, k_steps, obs, n_rec, obs_every,
                                        flags, partials, st);
     return e == hipSuccess ? SD_OK : hip_fail(e, name);

@@ -399,6 +399,40 @@ def test_short_runs(oracle, L, layout, k, every, route, many):
             assert np.array_equal(obs.cpu().numpy(), rec), call
 
 
+@pytest.mark.parametrize("L,layout,n,k,every,route", [
+    (320, sd.SD_P64, 8, 10, 3, sd.SD_ROUTE_AHEAD), (320, sd.SD_P64, 9, 10, 3, sd.SD_ROUTE_BANDS), (320, sd.SD_I8, 16, 9, 2, sd.SD_ROUTE_AHEAD),
+    (320, sd.SD_I8, 16, 10, 2, sd.SD_ROUTE_BANDS), (360, sd.SD_P64, 16, 11, 1, sd.SD_ROUTE_AHEAD), (362, sd.SD_I8, 16, 13, 4, sd.SD_ROUTE_AHEAD),
+    (361, sd.SD_I8, 15, 7, 0, sd.SD_ROUTE_AHEAD), (256, sd.SD_P64, 16, 21, 5, sd.SD_ROUTE_AHEAD)])
+def test_many_chains_of_the_largest_drawn_ahead(oracle, L, layout, n, k, every, route):
+    # as many chains as leave rounds of four to ten half-steps, which end between
+    # records and in the middle of a ragged last round, and on each side of the
+    # rule that sends rows of whole words to the bands; the first and last chain
+    # against the oracle
+    print(f"many chains L={L} layout={layout} n={n} k={k}", flush=True)
+    J, q, ids = [0.2 + 0.05 * a for a in range(n)], [1.2 - 0.05 * a for a in range(n)], [3 * a + 1 for a in range(n)]
+    starts = [inputs.random_lattice(L, 100 + a) for a in range(n)]
+    sig, tau = [], []
+    for x in starts:
+        host = x if layout == sd.SD_I8 else inputs.pack_bits(x)
+        t = sd.new_lattice(L, layout)
+        t.reshape(-1).view(torch.int8 if layout == sd.SD_I8 else torch.uint8).copy_(torch.from_numpy(host.reshape(-1).copy()))
+        sig.append(t)
+        tau.append(torch.zeros_like(t))
+    obs = torch.full((n, k // every if every else 0, 3), -1, dtype=torch.int64, device="cuda")
+    sd.sd_run_many(sig, tau, L, layout, J, q, SEED, ids, 2, k, obs if every else None, every)
+    assert sd.sd_debug_last_route() == route
+
+    def host(t):
+        flat = t.cpu().numpy().reshape(-1)
+        return flat.reshape(L, L) if layout == sd.SD_I8 else inputs.unpack_bits(flat.view(np.uint8), L)
+
+    for a in (0, n - 1):
+        s, t, rec = oracle.run(starts[a], J[a], q[a], SEED, ids[a], 2, k, obs_every=every)
+        assert np.array_equal(host(sig[a]), s) and np.array_equal(host(tau[a]), t), a
+        if every:
+            assert np.array_equal(obs[a].cpu().numpy(), rec), a
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
