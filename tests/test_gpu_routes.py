@@ -433,6 +433,35 @@ def test_many_chains_of_the_largest_drawn_ahead(oracle, L, layout, n, k, every, 
             assert np.array_equal(obs[a].cpu().numpy(), rec), a
 
 
+@pytest.mark.parametrize("L,layout,k,every,flags,route", [
+    (32, sd.SD_P32, 300, 7, 0, sd.SD_ROUTE_AHEAD), (64, sd.SD_I8, 130, 1, 0, sd.SD_ROUTE_AHEAD), (33, sd.SD_I8, 40, 3, 0, sd.SD_ROUTE_AHEAD),
+    (128, sd.SD_P64, 300, 11, 0, sd.SD_ROUTE_AHEAD), (100, sd.SD_I8, 50, 1, 0, sd.SD_ROUTE_AHEAD), (150, sd.SD_I8, 40, 2, 0, sd.SD_ROUTE_AHEAD),
+    (192, sd.SD_P64, 60, 5, 0, sd.SD_ROUTE_AHEAD), (200, sd.SD_P64, 60, 1, 0, sd.SD_ROUTE_AHEAD), (256, sd.SD_I8, 40, 1, 0, sd.SD_ROUTE_AHEAD),
+    (320, sd.SD_P64, 45, 4, 0, sd.SD_ROUTE_AHEAD), (333, sd.SD_I8, 45, 1, 0, sd.SD_ROUTE_AHEAD), (384, sd.SD_P64, 20, 3, 0, sd.SD_ROUTE_BANDS),
+    (448, sd.SD_I8, 11, 1, 0, sd.SD_ROUTE_BANDS), (704, sd.SD_P64, 9, 2, 0, sd.SD_ROUTE_BANDS), (2112, sd.SD_P64, 4, 1, 0, sd.SD_ROUTE_BANDS),
+    (100, sd.SD_I8, 5, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS), (333, sd.SD_I8, 5, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS),
+    (200, sd.SD_P64, 5, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS), (448, sd.SD_I8, 3, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS),
+    (96, sd.SD_P32, 5, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS), (704, sd.SD_P64, 3, 1, sd.SD_FLAG_GLOBAL_KERNELS, sd.SD_ROUTE_HALF_STEPS)])
+def test_every_form_against_the_oracle(oracle, L, layout, k, every, flags, route):
+    # each form of the walker, the bands and the one-word tiles that the tests
+    # around this one compare with each other, once against the oracle
+    print(f"form L={L} layout={layout} k={k} flags={flags}", flush=True)
+    start = inputs.random_lattice(L, L + 7)
+    host = start if layout == sd.SD_I8 else inputs.pack_bits(start)
+    host = torch.from_numpy(host.reshape(-1).copy()).cuda()
+    sigma, tau = sd.new_lattice(L, layout), sd.new_lattice(L, layout)
+    flat = [x.reshape(-1).view(host.dtype) for x in (sigma, tau)]
+    flat[0].copy_(host)
+    obs = torch.full((k // every, 3), -1, dtype=torch.int64, device="cuda")
+    sd.sd_run(sigma, tau, L, layout, 0.45, 0.8, SEED, 6, 9, k, obs, every, flags)
+    assert sd.sd_debug_last_route() == route
+    sig, t, rec = oracle.run(start, 0.45, 0.8, SEED, 6, 9, k, obs_every=every)
+    for x, w in zip(flat, (sig, t)):
+        have = x.cpu().numpy()
+        assert np.array_equal(have.reshape(L, L) if layout == sd.SD_I8 else inputs.unpack_bits(have, L), w)
+    assert np.array_equal(obs.cpu().numpy(), rec)
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
