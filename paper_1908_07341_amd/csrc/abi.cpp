@@ -424,7 +424,9 @@ static hipError_t run_chains_ahead(void* const* sigma, void* const* tau, uint32_
     a.obs_chain = 3ull * n_rec;
     a.obs_every = n_rec ? obs_every : 1u;
     g_last_route = SD_ROUTE_AHEAD;
-    return run_ahead(a, step0, k_steps, scratch.get(), kAheadBytes, st, done);
+    *done = true;
+    static_assert(kAheadBytes >= kAheadMinBytes, "scratch of a run");
+    return run_ahead(a, step0, k_steps, scratch.get(), kAheadBytes, st);
 }
 
 // Scratch memory of sd_run_noalloc: a file-scope device array (each device

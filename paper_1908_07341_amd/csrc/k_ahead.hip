@@ -411,8 +411,8 @@ hipError_t launch_ahead(const AheadArgs& a, hipStream_t st) {
     const bool words = a.L % 64u == 0;
     if (a.n <= 256u)
         return words ? launch_ahead_t<kFormWords, 1, 8, 256>(a, st) : launch_ahead_t<kFormString, 1, 8, 256>(a, st);
-    if (a.n <= 512u)
-        return words ? launch_ahead_t<kFormWords, 1, 8, 512>(a, st) : launch_ahead_t<kFormString, 1, 8, 512>(a, st);
+    if (a.n <= 512u)   // no side has rows of whole words here: 128^2 is 256 words, 192^2 576
+        return launch_ahead_t<kFormString, 1, 8, 512>(a, st);
     if (a.n <= 1024u)
         return words ? launch_ahead_t<kFormWords, 1, 4, 1024>(a, st) : launch_ahead_t<kFormString, 1, 4, 1024>(a, st);
     return words ? launch_ahead_t<kFormWords, 2, 2, 1024>(a, st) : launch_ahead_t<kFormString, 2, 2, 1024>(a, st);
@@ -420,14 +420,8 @@ hipError_t launch_ahead(const AheadArgs& a, hipStream_t st) {
 
 }  // namespace
 
-size_t ahead_bytes(uint32_t n, uint32_t n_chains, uint32_t H, bool records) {
-    return sizeof(uint64_t) * n_chains * n * ((size_t)2 * H * (records ? 7u : 6u) + 2u);
-}
-
-hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratch, size_t bytes, hipStream_t st,
-                     bool* done) {
-    constexpr uint32_t kMaxRound = 512, kMinRound = 4, kMaxDrawBlocks = 1024, kMaxRecBlocks = 512;
-    *done = false;
+hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratch, size_t bytes, hipStream_t st) {
+    constexpr uint32_t kMaxRound = 512, kMaxDrawBlocks = 1024, kMaxRecBlocks = 512;
     a.N = a.L * a.L;
     a.n = (a.N + 63u) / 64u;
     a.div_n = make_fastdiv(a.n);
@@ -436,8 +430,6 @@ hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratc
     const uint32_t total = 2u * k_steps;
     // equal rounds, as long as the scratch allows
     const size_t per = sizeof(uint64_t) * a.n_chains * a.n;
-    if (bytes / per < 2u + 2u * kMinRound * 7u)
-        return hipSuccess;
     uint64_t most = (bytes / per - 2u) / (2u * (records ? 7u : 6u));
     most = most < kMaxRound ? most & ~1ull : kMaxRound;
     const uint32_t rounds = (uint32_t)((total + most - 1u) / most);
@@ -472,7 +464,6 @@ hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratc
         a.rec_blocks = a.rec_blocks < kMaxRecBlocks ? a.rec_blocks : kMaxRecBlocks;
         e = launch_ahead(a, st);
     }
-    *done = true;
     return e;
 }
 

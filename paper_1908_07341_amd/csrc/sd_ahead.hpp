@@ -8,7 +8,8 @@ namespace sd {
 // Lattices the kernel takes: up to two words per thread of a workgroup.  (Four
 // words a thread spill: 512^2 3.5 us a half-step against 2.6 for five chains in
 // the whole-step kernel.)
-inline bool ahead_size(int32_t L) { return L >= 8 && ((uint64_t)L * (uint64_t)L + 63u) / 64u <= 2048u; }
+constexpr uint32_t kAheadMaxWords = 2048;
+inline bool ahead_size(int32_t L) { return L >= 8 && ((uint64_t)L * (uint64_t)L + 63u) / 64u <= kAheadMaxWords; }
 
 // A call's run of several chains of one size in rounds: launch r draws the
 // class masks of round r, walks the chains through round r - 1 and takes the
@@ -36,13 +37,12 @@ struct AheadArgs {
     uint32_t rec_step, rec_count, rec_slot, rec_blocks;   // rec_step: steps done before the round
 };
 
-// Bytes a run needs for rounds of H half-steps (masks, history, state).
-size_t ahead_bytes(uint32_t n, uint32_t n_chains, uint32_t H, bool records);
+// Scratch that holds rounds of four half-steps of the most and largest chains
+// (two slots of six masks and the new word per half-step, and the two lattices).
+constexpr size_t kAheadMinBytes = sizeof(uint64_t) * kManyMax * kAheadMaxWords * (2u * 4u * 7u + 2u);
 // Runs every round of k_steps steps from step step0; the caller fills the
-// chains, keys, geometry (L, int8_io), and records, and gives `bytes` of
-// scratch (8-byte aligned device memory).  False in *done when the scratch is
-// too small for rounds of kAheadMinRound half-steps: nothing was enqueued.
-hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratch, size_t bytes, hipStream_t st,
-                     bool* done);
+// chains, keys, geometry (L, int8_io), and records, and gives `bytes` >=
+// kAheadMinBytes of scratch (16-byte aligned device memory).
+hipError_t run_ahead(AheadArgs a, uint64_t step0, uint32_t k_steps, void* scratch, size_t bytes, hipStream_t st);
 
 }  // namespace sd
