@@ -96,7 +96,7 @@ __device__ __forceinline__ Span make_span(uint32_t pos, uint32_t N) {
 __device__ __forceinline__ uint64_t pack64(uint32_t lo, uint32_t hi) { return (uint64_t)lo | ((uint64_t)hi << 32); }
 
 __device__ __forceinline__ uint64_t span_bits(const uint64_t* lat, const Span& s) {
-    const uint32_t* d = reinterpret_cast<const uint32_t*>(lat) + s.q;
+    const lds_dword* d = reinterpret_cast<const lds_dword*>(lat) + s.q;
     const uint32_t d0 = d[0], d1 = d[1], d2 = d[2];
     uint64_t v = pack64(__builtin_amdgcn_alignbit(d1, d0, s.sh), __builtin_amdgcn_alignbit(d2, d1, s.sh));
     if (s.room < 64u)
@@ -142,7 +142,7 @@ __device__ __forceinline__ void fetch_neighbours(uint64_t c, const uint64_t* lat
     if constexpr (FORM == kFormRow64 || FORM == kFormRow32) {
         row_neighbours<FORM, WHICH>(c, n1, n2);
     } else {
-        const uint32_t side = reinterpret_cast<const uint32_t*>(lat)[f.side];
+        const uint32_t side = reinterpret_cast<const lds_dword*>(lat)[f.side];
         n1 = FORM == kFormWords ? lat[f.row.q] : span_bits(lat, f.row);
         const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
         n2 = WHICH == 0 ? pack64(__builtin_amdgcn_alignbit(lo, side, 31), __builtin_amdgcn_alignbit(hi, lo, 31))

@@ -77,8 +77,8 @@ __device__ __forceinline__ void class_tails(uint32_t key0, uint32_t key1, uint32
         const uint32_t lo = (b & 1u) ? y.x1 : y.x0, hi = (b & 1u) ? y.x3 : y.x2;
         const uint32_t tail = (((b & 2u) ? hi : lo) ^ rng_xor) >> 8;
         const uint32_t bit = 1u << (b & 31u);
-        uint32_t* m = reinterpret_cast<uint32_t*>(m64) + (b >> 5);
-        const uint32_t* q = reinterpret_cast<const uint32_t*>(&w.eq[0][l]) + (b >> 5);
+        lds_dword* m = reinterpret_cast<lds_dword*>(m64) + (b >> 5);
+        const lds_dword* q = reinterpret_cast<const lds_dword*>(&w.eq[0][l]) + (b >> 5);
         uint32_t open[6];
 #pragma unroll
         for (uint32_t k = 0; k < 6; ++k)
