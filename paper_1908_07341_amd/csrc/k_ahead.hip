@@ -16,8 +16,8 @@
 // 1000 words on the 48 bytes of masks per word that one CU must read (256^2:
 // 49 KB a half-step, 0.32 us at 64 bytes a clock).  us per half-step, the
 // best other kernel against this one: 64^2 0.37 -> 0.07, 128^2 3.4 -> 0.18,
-// 200^2 4.2 -> 0.53, 256^2 3.7 -> 0.46, 333^2 int8 6.9 -> 1.25; five chains of
-// 256^2 in whole steps 1.5 -> 0.8.
+// 200^2 4.2 -> 0.53, 256^2 3.7 -> 0.46, 333^2 int8 6.9 -> 1.25 (recorded 0.69,
+// 0.62 and 1.40); five chains of 256^2 in whole steps 1.5 -> 0.8.
 //
 // No workgroup of a launch waits for another: rounds are separate launches on
 // the stream, and each slot of masks or words is written in one launch and

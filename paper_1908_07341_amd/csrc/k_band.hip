@@ -44,8 +44,8 @@ struct BandShared {
     uint32_t T24[6];
 };
 
-// A thread's counts of one half-step (at most 2 per site of a band of at
-// most 1280 words): 32 bits hold them.
+// A thread's counts of one half-step (at most 2 per site of the
+// kBandMaxRowsWords words in LDS): 32 bits hold them.
 struct BandSums {
     uint32_t pc = 0, dpair = 0, dself = 0;
 };

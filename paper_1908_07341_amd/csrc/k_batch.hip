@@ -222,8 +222,8 @@ __device__ __forceinline__ void lds_half_step(const HalfCtx<BITS>& h, const Draw
     }
     for (uint32_t tile = threadIdx.x >> 6; tile < n_tiles; tile += n_waves) {
         const uint32_t g = 64u * tile + lane;
-        // rows of whole words hold L * L / 64 = 64 * L * (L / 64) words: every
-        // tile is full
+        // lattices whose rows are whole words hold L * L / 64 = 64 (L / 64)^2
+        // words: every tile is full
         const bool active = !BITS || g < h.n_words;
         const uint32_t ga = active ? g : h.n_words - 1u;   // a word to read and draw in any case
         uint64_t c, n1, n2;
@@ -314,16 +314,16 @@ __device__ __forceinline__ ObsSums lds_observe(const uint64_t* sig, const uint64
     return acc;
 }
 
-// Steps of one chain.  Paired chains fold the observables into half-step B;
-// the general compare (rare: some field is exactly zero) leaves them to a
-// separate pass so that its register count stays low.
 // Copy of an LDS lattice to global memory (the workgroup's threads).
 __device__ __forceinline__ void store_lattice(uint64_t* out, const uint64_t* lat, uint32_t n_words) {
     for (uint32_t g = threadIdx.x; g < n_words; g += blockDim.x)
         out[g] = lat[g];
 }
 
-// mom (used by thread 0 only): the chain's running sums in moments mode.
+// Steps of one chain.  Paired chains fold the observables into half-step B;
+// the general compare (only under its flag) leaves them to a separate pass so
+// that its register count stays low.  mom (used by thread 0 only): the chain's
+// running sums in moments mode.
 template <bool PAIRED, bool COMPLEMENT, bool BITS>
 __device__ __forceinline__ void run_steps(const BatchArgs& a, const HalfCtx<BITS>& hA, const HalfCtx<BITS>& hB,
                                           DrawParams dp,

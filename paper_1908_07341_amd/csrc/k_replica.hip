@@ -33,6 +33,8 @@
 // half-step (the scan with its tails in the site's own lane: 34; tables with
 // the same tails: 26.2), of which 14 us is the traffic at the rate of a copy;
 // 512^2, where a batch is two groups: 15.6 -> 6.8 us (14.2 in full batches).
+// 8^2 is one group, whose tables cost more than the scan did (4.7 us against
+// 3.9), in calls that their launches bound (4 steps 37.3 and 38.2 us).
 #include "sd_replica.hpp"
 
 namespace sd {

@@ -12,9 +12,10 @@
 // new word.  What such a chain waits for is the dependence of a half-step on
 // the last one; drawing ahead leaves about 30 instructions in that chain
 // instead of a whole draw (four plane calls, the scan, the tails, a workgroup
-// barrier).  The walker takes 0.053 us a half-step at 32^2 and 0.062 at 64^2;
-// the workers bound both, 0.092 us and 0.37 (a whole draw per half-step took
-// 1.2-1.5 us).  Long runs of one chain leave the drawing to the whole device
+// barrier).  The walker takes 0.053 us a half-step at 32^2 and 0.062 at 64^2,
+// whose rows are halves and wholes of a register; on other sides the neighbours
+// are windows of the lattice in LDS, and it takes 0.155.  The workers bound 32^2
+// and 64^2, 0.092 us and 0.37 (a whole draw per half-step took 1.2-1.5 us).  Long runs of one chain leave the drawing to the whole device
 // (k_ahead.hip).
 //
 // Coupled pairs (coupling from the past, section 3.2) share their uniforms, so

@@ -92,8 +92,7 @@ __device__ __forceinline__ void class_tails(uint32_t key0, uint32_t key1, uint32
 
 // The class masks of the tile's words: this lane's is group g at half-step
 // index t, its masks go to out[k * stride] (LDS).  Sites whose top byte equals
-// a threshold's are listed, one per lane and round of ballots, and their tails
-// drawn one per lane.  UNIFORM_T: t is the same for the whole wavefront.
+// a threshold's are listed and their tails drawn one per lane.  UNIFORM_T: t is the same for the whole wavefront.
 template <bool UNIFORM_T, class At>
 __device__ __forceinline__ void class_masks(uint32_t key0, uint32_t key1, uint32_t stream, uint32_t t, uint32_t g,
                                             uint32_t rng_xor, const uint32_t* Tk, bool active, ClassList& w,
