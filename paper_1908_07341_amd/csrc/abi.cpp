@@ -661,8 +661,10 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                                                 k_steps >= obs_every ? obs : nullptr, obs_every, flags, st);
         return e == hipSuccess ? SD_OK : hip_fail(e, name);
     }
+    // word width and grid of the choice are those of its half-step launches
     if (layout != SD_I8 && L % 64 == 0)
-        klay = ch.width == 32 ? kLayP32 : kLayP64;
+        klay = mode == 2 && ch.width == 32 ? kLayP32 : kLayP64;
+    const uint32_t max_blocks = mode == 2 ? ch.blocks : 0u;
     if (lds_size && mode != 2 && !(flags & SD_FLAG_GLOBAL_KERNELS)) {
         if (k_steps == 0)
             return SD_OK;
@@ -717,7 +719,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
     // Each record's workgroup sums go to a slot of their own in the partials
     // workspace; one finishing launch adds a whole chunk of records, so that
     // frequent records cost no third launch per step.
-    const uint32_t blocks = half_step_blocks(klay, G, !general && thresholds_paired(base.T), ch.blocks);
+    const uint32_t blocks = half_step_blocks(klay, G, !general && thresholds_paired(base.T), max_blocks);
     const uint32_t stride = 4u * blocks;
     if (n_rec && stride > kPartialsWords)
         return fail(SD_EINVAL, "%s: %u workgroups need %u partial sums per record, more than the %zu of the "
@@ -730,17 +732,17 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
         const uint64_t n = step0 + m;
         DrawParams dp = base;
         dp.t = (uint32_t)(2 * n);
-        e = launch_half_step(klay, 0, sigma, tau, G, dp, nullptr, st, ch.blocks, nullptr, general);
+        e = launch_half_step(klay, 0, sigma, tau, G, dp, nullptr, st, max_blocks, nullptr, general);
         if (e != hipSuccess)
             break;
         dp.t = (uint32_t)(2 * n + 1);
         if (n_rec && (m + 1) % obs_every == 0 && !partials) {
             // no workspace (stream capture): atomics into the record
             e = launch_half_step(klay, 1, tau, sigma, G, dp, obs + 3u * (size_t)((m + 1) / obs_every - 1), st,
-                                 ch.blocks, nullptr, general);
+                                 max_blocks, nullptr, general);
         } else if (n_rec && (m + 1) % obs_every == 0) {
             const uint32_t r = (m + 1) / obs_every - 1;
-            e = launch_half_step(klay, 1, tau, sigma, G, dp, obs + 3u * (size_t)r, st, ch.blocks,
+            e = launch_half_step(klay, 1, tau, sigma, G, dp, obs + 3u * (size_t)r, st, max_blocks,
                                  partials + (size_t)pending * stride, general, false);
             ++pending;
             if (e == hipSuccess && (pending == chunk || r + 1 == n_rec)) {
@@ -748,7 +750,7 @@ sd_status run_chain(const char* name, void* sigma, void* tau, int32_t L, int32_t
                 pending = 0;
             }
         } else {
-            e = launch_half_step(klay, 1, tau, sigma, G, dp, nullptr, st, ch.blocks, nullptr, general);
+            e = launch_half_step(klay, 1, tau, sigma, G, dp, nullptr, st, max_blocks, nullptr, general);
         }
     }
     return e == hipSuccess ? SD_OK : hip_fail(e, name);
@@ -1153,7 +1155,7 @@ sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* 
         const RunChoice& f = cands[(size_t)(without < 0 ? with : without)];
         best.mode_free = f.mode_free;
         best.threads = f.threads;
-        if (f.mode_free == 2) {   // the fastest grid, in either case
+        if (f.mode_free == 2) {   // the fastest grid, which mode 2 of either kind takes
             best.width = f.width;
             best.blocks = f.blocks;
         }
@@ -1182,7 +1184,11 @@ sd_status sd_tuned_choice(int32_t L, int32_t layout, int32_t* mode, int32_t* wid
                           int32_t* threads) {
     if (!layout_supported(L, layout))
         return fail(SD_EINVAL, "sd_tuned_choice: unsupported (L=%d, layout=%d)", L, layout);
-    const RunChoice c = run_choice(L, layout);
+    RunChoice c = run_choice(L, layout);
+    if (c.mode != 2) {   // the built-in grid
+        c.width = 64;
+        c.blocks = 0;
+    }
     if (mode) *mode = c.mode;
     if (width) *width = c.width;
     if (blocks) {

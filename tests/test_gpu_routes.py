@@ -462,6 +462,22 @@ def test_every_form_against_the_oracle(oracle, L, layout, k, every, flags, route
     assert np.array_equal(obs.cpu().numpy(), rec)
 
 
+@pytest.mark.parametrize("L,layout", [(512, sd.SD_P64), (640, sd.SD_P64), (1024, sd.SD_I8), (2048, sd.SD_P64)])
+def test_tuned_whole_steps_stay_in_bands(tmp_path, L, layout):
+    # the grid that the tuner keeps for half-step launches, of either word width,
+    # does not take a tuned run off the whole steps, which are twice as quick
+    print(f"tuned bands L={L} layout={layout}", flush=True)
+    sd.sd_tune(L, layout, str(tmp_path / "tune.json"))
+    choice = sd.sd_tuned_choice(L, layout)
+    print("tuned", choice, flush=True)
+    assert choice[0] == 1
+    sigma, tau = sd.new_lattice(L, layout), sd.new_lattice(L, layout)
+    sd.sd_init(sigma, L, layout, sd.SD_INIT_UP)
+    for run in (sd.sd_run, sd.sd_run_noalloc):
+        run(sigma, tau, L, layout, 0.4, 0.6, SEED, 1, 0, 5)
+        assert sd.sd_debug_last_route() == sd.SD_ROUTE_BANDS
+
+
 @pytest.mark.parametrize("L,layout", [(8, sd.SD_P64), (17, sd.SD_I8), (24, sd.SD_P64), (32, sd.SD_P32), (90, sd.SD_I8),
                                       (91, sd.SD_I8), (96, sd.SD_P64), (104, sd.SD_P64), (512, sd.SD_P64),
                                       (544, sd.SD_P32)])
