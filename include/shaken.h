@@ -174,9 +174,9 @@ SD_API sd_status sd_run_noalloc(void* sigma, void* tau, int32_t L, int32_t layou
  * the device, run together at the launch rate of one.  Lattices of up to 2048
  * words are drawn ahead, one workgroup per chain, as in sd_run (not one step of
  * more than 512 words, nor ten steps and more of nine chains and more of 320^2,
- * which go as larger ones do).  Larger ones whose rows are whole 64-bit words, at most 64 of them (packed, or int8 with
- * 16-byte aligned lattices), run all but the last step as whole steps, up to
- * eight per launch: each workgroup takes a band of rows
+ * which go as larger ones do).  Larger ones whose rows are whole 64-bit words,
+ * at most 64 of them (packed, or int8 with 16-byte aligned lattices), run all
+ * but the last step as whole steps, up to eight per launch: each workgroup takes a band of rows
  * plus one halo row per step on each side into LDS and recomputes the halo
  * from the same counter-based uniforms (sections 2 and 4: eqs. (15)-(16)
  * drawn site by site), so results do not change; tau's memory holds sigma
@@ -207,13 +207,13 @@ SD_API sd_status sd_run_many(void* const* sigma, void* const* tau, int32_t n_cha
  * L % 64 == 0 — the same bytes —
  * and the number of workgroups); for sizes that are drawn ahead also how
  * sd_run_noalloc and captured runs, which cannot be, execute them (the workgroup
- * size of the kernel with the lattices in LDS, or the grid).  Each candidate runs a few steps on scratch
- * lattices (allocated and freed here) with HIP events; the fastest is used by
+ * size of the kernel with the lattices in LDS, or the grid).  Each candidate
+ * runs a few steps on scratch lattices (allocated and freed here) with HIP events; the fastest is used by
  * every later sd_run of this process with these (L, layout) and stored under
  * a "run2:<arch>:L=..:layout=.." key in the JSON file tune_cache_path (NULL:
  * not stored; the number tells the library's sets of kernels apart); a later
- * sd_tune finding the key there takes it without measuring.  Synchronises the stream.  Results of sd_run do not depend on
- * the choice.
+ * sd_tune finding the key there takes it without measuring.  Synchronises the
+ * stream.  Results of sd_run do not depend on the choice.
  */
 SD_API sd_status sd_tune(int32_t L, int32_t layout, const char* tune_cache_path, void* hip_stream);
 
